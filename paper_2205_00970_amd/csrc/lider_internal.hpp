@@ -183,21 +183,19 @@ __device__ inline int64_t locate(const Model* Mp, const double* leaves, const in
   return pos_of(lf[0], lf[1], M.L, x);
 }
 
-// Extended hashkey distance of two m-bit hashkeys (Section 4.2), scaled by
-// C = 2^B to an exact integer: KL * 2^B + KD_e, with KL the non-prefix length
-// and KD_e the absolute difference of the (at most) B bits right after the
-// common prefix read as binary numbers.
-__host__ __device__ inline int64_t dist_e_scaled(uint64_t a, uint64_t b, int m, int B) {
-  const uint64_t x = a ^ b;
+// Extended hashkey distance of two binary hashkeys of at most LIDER_MAX_M bits
+// (Section 4.2), scaled by C = 2^B (B <= 16) to an exact integer: KL * 2^B +
+// KD_e, with KL the non-prefix length and KD_e the absolute difference of the
+// (at most) B bits right after the common prefix read as binary numbers.  The
+// largest value, 16 * 2^16 + 2^16 - 1, fits int32.
+__device__ inline int32_t dist_e_scaled(uint64_t a, uint64_t b, int32_t B) {
+  const uint32_t ua = uint32_t(a), ub = uint32_t(b), x = ua ^ ub;
   if (x == 0) return 0;
-  int p = 63;  // most significant differing bit (bit 0 = least significant)
-  while (!((x >> p) & 1u)) --p;
-  const int nb = B < p + 1 ? B : p + 1;
-  const uint64_t mask = (uint64_t(1) << nb) - 1;
-  const int64_t v1 = int64_t((a >> (p + 1 - nb)) & mask), v2 = int64_t((b >> (p + 1 - nb)) & mask);
-  const int64_t kl = p + 1;  // non-prefix length: m minus the common prefix m - 1 - p
-  (void)m;
-  return kl * (int64_t(1) << B) + (v1 > v2 ? v1 - v2 : v2 - v1);
+  const int32_t kl = 32 - __clz(int32_t(x));  // non-prefix length
+  const int32_t nb = min(B, kl), sh = kl - nb;
+  const uint32_t mask = (1u << nb) - 1u;
+  const int32_t v1 = int32_t((ua >> sh) & mask), v2 = int32_t((ub >> sh) & mask);
+  return (kl << B) + abs(v1 - v2);
 }
 
 // Rigorous bound on |fl32(a.b) - a.b| for a length-d fp32 dot product summed in

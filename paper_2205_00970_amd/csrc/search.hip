@@ -1179,28 +1179,54 @@ __global__ __launch_bounds__(256) void pair_mask_kernel(
   }
 }
 
+// Inclusive prefix maximum over the 64 lanes of a wave (all lanes active), the
+// DPP pattern of dpp_min_u32 read at every lane.
+__device__ inline int32_t dpp_prefix_max_i32(int32_t v) {
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
+  return v;
+}
+
 // dist_e-guided bi-directional expansion (Sections 3.3.1, 4.2), one wave per
 // item (a query's layer-1 window, or a (query, cluster) pair).  From the
 // predicted location the range grows one position at a time on the side whose
 // next hashkey is closer to the query's in dist_e (ties to the left, the other
-// side once one is exhausted) until min(r, L) positions are taken.  The wave
-// scores the next 64 candidates of a side at once into LDS; lane 0 runs the
-// sequential two-pointer decisions over them and the exhausted side is
-// refilled.  Only the window start changes (the length is min(r, L)).
-// Item t belongs to hashkey array h = t % H, whose keys start at
-// keys + h * kstride.  Layer 1: items are (query, array) windows, the array is
-// the centroids retriever's keys (L = C) and the l1 rows are updated too; else
-// items are (pair, array) windows and the array of cluster j starts at off[j].
-constexpr int64_t kNoDist = INT64_MAX;
+// side once one is exhausted) until min(r, L) positions are taken.
+//
+// Taking the smaller head of two sequences a (left) and b (right) is a merge
+// of their running maxima A_i = max a_0..a_i and B_j = max b_0..b_j whatever
+// the order inside a and b: an a_i below A_i = a_k directly follows a_k, which
+// was taken because a_k <= b_j; so a_i <= b_j <= B_j and A_i <= B_j decide alike
+// (and the same with the sides exchanged).  Of the first T merged positions,
+// the left ones number the l in [0, T) with A_l <= B_{T-1-l} (A_l never falls
+// and B_{T-1-l} never rises with l), so a wave decides up to kExpandStep
+// positions at once: each lane forms the distances of 4 consecutive positions
+// of both sides, two wave scans give the running maxima, and T comparisons
+// and a count replace T decisions one after another.  Longer ranges carry
+// the maxima of what was taken into the next step.  It is bound by the
+// latency of the key loads: 1M x 768, 10,000 queries, c = 8, r = 256 (326 MB of
+// keys from L2): 558 us by one lane's decisions over 64 positions at a time,
+// 76 us now; layer 1 (r1 = 256) 93 -> 13 us.
+//
+// Only the window start changes (the length is min(r, L)).  Item t belongs to
+// hashkey array h = t % H, whose keys start at keys + h * kstride.  Layer 1:
+// items are (query, array) windows, the array is the centroids retriever's
+// keys (L = C) and the l1 rows are updated too; else items are (pair, array)
+// windows and the array of cluster j starts at off[j].
+constexpr int32_t kNoDist = INT32_MAX;  // past the end of a side
+constexpr int kExpandStep = 256;        // positions decided per step
 
 __global__ __launch_bounds__(256) void expand_kernel(const uint64_t* __restrict__ keys,
                                                      const int64_t* __restrict__ off, int64_t L1,
                                                      Pair* __restrict__ items, int64_t nitems,
-                                                     const uint64_t* __restrict__ kq, int32_t r,
-                                                     int32_t m, int32_t B,
+                                                     const uint64_t* __restrict__ kq, int32_t B,
                                                      int32_t* __restrict__ l1, int32_t H,
                                                      int64_t kstride) {
-  __shared__ int64_t dl[4][64], dr[4][64];
+  __shared__ __attribute__((aligned(16))) int32_t sa[4][kExpandStep], sb[4][kExpandStep];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t t = int64_t(blockIdx.x) * 4 + wave;
   if (t >= nitems) return;
@@ -1208,48 +1234,55 @@ __global__ __launch_bounds__(256) void expand_kernel(const uint64_t* __restrict_
   if (pr.j < 0 || pr.len <= 0) return;
   const uint64_t* kh = keys + (t % H) * kstride;
   const uint64_t* ka = off ? kh + off[pr.j] : kh;
-  const int64_t L = off ? off[pr.j + 1] - off[pr.j] : L1;
-  const int64_t take = pr.len;  // = min(r, L)
+  const int32_t L = int32_t(off ? off[pr.j + 1] - off[pr.j] : L1);
+  const int32_t take = pr.len;  // = min(r, L)
   const uint64_t Kq = kq[t];
-  int64_t lo = pr.pos - 1, hi = pr.pos + 1, got = 1;
-  int il = 64, ir = 64;
+  int32_t lo = pr.pos - 1, hi = pr.pos + 1, got = 1;
+  int32_t ca = 0, cb = 0;  // running maxima of the positions taken on each side
   while (got < take) {
-    if (il == 64) {
-      const int64_t p = lo - lane;
-      dl[wave][lane] = p >= 0 ? dist_e_scaled(ka[p], Kq, m, B) : kNoDist;
-      il = 0;
+    const int32_t T = min(take - got, int32_t(kExpandStep));
+    int32_t a[4], b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int32_t x = 4 * lane + e;
+      const int32_t pl = lo - x, ph = hi + x;
+      a[e] = x < T && pl >= 0 ? dist_e_scaled(ka[pl], Kq, B) : kNoDist;
+      b[e] = x < T && ph < L ? dist_e_scaled(ka[ph], Kq, B) : kNoDist;
     }
-    if (ir == 64) {
-      const int64_t p = hi + lane;
-      dr[wave][lane] = p < L ? dist_e_scaled(ka[p], Kq, m, B) : kNoDist;
-      ir = 0;
+#pragma unroll
+    for (int e = 1; e < 4; ++e) {
+      a[e] = max(a[e], a[e - 1]);
+      b[e] = max(b[e], b[e - 1]);
     }
+    const int32_t ia = __shfl_up(dpp_prefix_max_i32(a[3]), 1);
+    const int32_t ib = __shfl_up(dpp_prefix_max_i32(b[3]), 1);
+    const int32_t xa = lane ? max(ca, ia) : ca, xb = lane ? max(cb, ib) : cb;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      a[e] = max(a[e], xa);
+      b[e] = max(b[e], xb);
+    }
+    *reinterpret_cast<int4*>(&sa[wave][4 * lane]) = int4{a[0], a[1], a[2], a[3]};
+    *reinterpret_cast<int4*>(&sb[wave][4 * lane]) = int4{b[0], b[1], b[2], b[3]};
     __threadfence_block();
     __builtin_amdgcn_wave_barrier();
-    if (lane == 0) {
-      while (got < take && il < 64 && ir < 64) {
-        const int64_t a = dl[wave][il], b = dr[wave][ir];
-        if (a != kNoDist && (b == kNoDist || a <= b)) {
-          ++il;
-          --lo;
-        } else {
-          ++ir;
-          ++hi;
-        }
-        ++got;
-      }
+    int32_t left = 0;  // positions of this step taken on the left
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int32_t x = 4 * lane + e;
+      left += __popcll(__ballot(x < T && a[e] <= sb[wave][x < T ? T - 1 - x : 0]));
     }
-    lo = __shfl(lo, 0);
-    hi = __shfl(hi, 0);
-    got = __shfl(got, 0);
-    il = __shfl(il, 0);
-    ir = __shfl(ir, 0);
+    if (left > 0) ca = sa[wave][left - 1];
+    if (left < T) cb = sb[wave][T - left - 1];
+    lo -= left;
+    hi += T - left;
+    got += T;
     __threadfence_block();
     __builtin_amdgcn_wave_barrier();
   }
   if (lane == 0) {
-    items[t].s = int32_t(lo + 1);
-    if (l1) l1[3 * t + 1] = int32_t(lo + 1);
+    items[t].s = lo + 1;
+    if (l1) l1[3 * t + 1] = lo + 1;
   }
 }
 
@@ -4158,8 +4191,8 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     hipLaunchKernelGGL(l1_kernel, dim3(unsigned((nl1 + 255) / 256)), dim3(256), 0, st, la);
   if (o.expand_bits > 0)
     hipLaunchKernelGGL(expand_kernel, dim3(unsigned((nl1 + 3) / 4)), dim3(256), 0, st,
-                       ix.l1_keys, (const int64_t*)nullptr, int64_t(C), l1pairs, nl1, kq, p.r1,
-                       m, o.expand_bits, l1, H, int64_t(C));
+                       ix.l1_keys, (const int64_t*)nullptr, int64_t(C), l1pairs, nl1, kq,
+                       o.expand_bits, l1, H, int64_t(C));
   const unsigned qgrid = unsigned(std::min<int64_t>(nq, 65535));
   const unsigned wgrid = unsigned(std::min<int64_t>((nq + 3) / 4, 65535));
   // the window each routing kernel reads: (l1w[wst q + 1], l1w[wst q + 2]);
@@ -4238,7 +4271,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
                      o.expand_bits > 0 ? kq : (uint64_t*)nullptr);
   if (o.expand_bits > 0)
     hipLaunchKernelGGL(expand_kernel, dim3(unsigned((np * H + 3) / 4)), dim3(256), 0, st,
-                       ix.keys, ix.off, int64_t(0), H > 1 ? pw : pairs, np * H, kq, r, m,
+                       ix.keys, ix.off, int64_t(0), H > 1 ? pw : pairs, np * H, kq,
                        o.expand_bits, (int32_t*)nullptr, H, ix.n);
   if (C <= kFusedScanMax) {
     hipLaunchKernelGGL(scan_scatter_kernel, dim3(unsigned(std::max<int64_t>(1, (np + 255) / 256))),
