@@ -841,7 +841,7 @@ int lider_kmeans_assign(const float* X_dev, int64_t n, int32_t d, const float* c
   void* scr = nullptr;
   int32_t* changed = nullptr;
   int rc = LIDER_OK;
-  if (hipMalloc(&scr, kmeans_assign_scratch(n, C)) != hipSuccess)
+  if (hipMalloc(&scr, kmeans_assign_scratch(n, d, C)) != hipSuccess)
     rc = set_error(LIDER_ENOMEM, "out of device memory (k-means scratch)");
   if (rc == LIDER_OK) rc = alloc(&changed, 64, "counter");
   if (rc == LIDER_OK) rc = check_hip(hipMemsetAsync(changed, 0, 256, st), "zero");

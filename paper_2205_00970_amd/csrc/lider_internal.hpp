@@ -302,7 +302,7 @@ int run_kmeans(Index& ix, const float* X, const int64_t* init_host, int32_t iter
 int run_kmeans_assign(const float* X, int64_t n, int32_t d, const float* cent, int32_t C,
                       int32_t* assign, const int32_t* prev, int32_t* changed, void* scratch,
                       hipStream_t st);
-size_t kmeans_assign_scratch(int64_t n, int32_t C);
+size_t kmeans_assign_scratch(int64_t n, int32_t d, int32_t C);
 int run_centroid_means(const float* X, int64_t n, int32_t d, const int32_t* assign, int32_t C,
                        float* cent, void* scratch, size_t scratch_bytes, hipStream_t st);
 size_t centroid_means_scratch(int64_t n, int32_t C);

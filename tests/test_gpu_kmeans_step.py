@@ -1,0 +1,42 @@
+"""The k-means assignment product at the edges of its tiles (256 points, 256
+centroids, 32 dimensions), with ties, unaligned rows and extreme values,
+against the FP64 oracle's argmin (equal everywhere)."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,C,d", [(1, 1, 1), (1, 2, 3), (255, 255, 31), (256, 256, 32), (257, 257, 33),
+                                   (1000, 600, 100), (513, 1025, 130), (4000, 37, 96), (70000, 16, 64)])
+def test_tile_edges_and_ties(n, C, d):
+    import torch
+    from paper_2205_00970_amd import lider
+    g = np.random.default_rng(n + C + d)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    cent = g.standard_normal((C, d)).astype(np.float32)
+    if C > 3:  # equal centroids: ties to the smaller id
+        cent[C // 2] = cent[1]
+        cent[C - 1] = cent[0]
+    assert np.array_equal(lider.kmeans_assign(torch.from_numpy(X).cuda(), torch.from_numpy(cent).cuda()).cpu().numpy(),
+                          oracle.kmeans_assign(X, cent))
+    # rows and centroids at addresses that are not multiples of 16 bytes
+    buf = torch.empty(n * d + 1, device="cuda")
+    buf[1:] = torch.from_numpy(X.reshape(-1)).cuda()
+    cbuf = torch.empty(C * d + 1, device="cuda")
+    cbuf[1:] = torch.from_numpy(cent.reshape(-1)).cuda()
+    assert np.array_equal(lider.kmeans_assign(buf[1:].view(n, d), cbuf[1:].view(C, d)).cpu().numpy(),
+                          oracle.kmeans_assign(X, cent))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-15, 1e12, 1e18])
+def test_extreme_magnitudes(scale):
+    import torch
+    from paper_2205_00970_amd import lider
+    g = np.random.default_rng(7)
+    X = (scale * g.standard_normal((300, 64))).astype(np.float32)
+    cent = (scale * g.standard_normal((40, 64))).astype(np.float32)
+    assert np.array_equal(lider.kmeans_assign(torch.from_numpy(X).cuda(), torch.from_numpy(cent).cuda()).cpu().numpy(),
+                          oracle.kmeans_assign(X, cent))
