@@ -23,6 +23,12 @@ __global__ void zero_i32_kernel2(int32_t* p, int64_t cnt) {
     p[t] = 0;
 }
 
+__global__ void fill_i32_kernel(int32_t* p, int64_t cnt, int32_t v) {
+  for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < cnt;
+       t += int64_t(gridDim.x) * blockDim.x)
+    p[t] = v;
+}
+
 // Centroids per column tile of the assignment product (and rows per tile).
 constexpr int kAsgTile = 256;
 
@@ -121,24 +127,34 @@ struct AssignOut {
   int32_t* amb_count;
 };
 
-// Decides one point from its best and second-best value and |x|^2 (fp32), or
-// queues it.  The split values x = h + l + r (|x - h| <= u |x|, |l| <= u (1 +
-// u) |x|, |r| <= u^2 |x|, u = 2^-8) and the products h h + h l + l h leave x.mu
-// within ((2 (1 + u)^2 + 1) u^2 + dot_err_coef(3 d) (1 + u)^2 (1 + 2 u)) |x|
-// |mu|, plus absolute terms for parts below 2^-126; |mu|^2 in fp32 is within
-// dot_err_coef(d) |mu|^2, and the fp32 combination adds 2^-22.
-__device__ inline void assign_decide(const AssignOut& o, int64_t row, const Best& b, float ssr) {
-  const double gam = double(o.d + 2) * 5.9604644775390625e-08;
+// Bound of the error of a value g_j of the split product for a point with
+// |x| <= xn and centroids with |mu| <= M.  The split values x = h + l + r (|x -
+// h| <= u |x|, |l| <= u (1 + u) |x|, |r| <= u^2 |x|, u = 2^-8) and the products
+// h h + h l + l h leave x.mu within ((2 (1 + u)^2 + 1) u^2 + dot_err_coef(3 d)
+// (1 + u)^2 (1 + 2 u)) |x| |mu|, plus absolute terms for parts below 2^-126;
+// |mu|^2 in fp32 is within dot_err_coef(d) |mu|^2, the fp32 combination adds
+// 2^-22, and the FP64 reference has its own rounding.
+__device__ inline double assign_err(int32_t d, double xn, double M) {
   const double u = 0.00390625;
   const double dotc = ((2.0 * (1.0 + u) * (1.0 + u) + 1.0) * u * u +
-                       dot_err_coef(3 * o.d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u)) * 1.01;
-  const double M = double(__uint_as_float(*o.maxbits));
-  const double xn = sqrt(double(ssr) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07);
-  const double E = (dot_err_coef(o.d) + 2.384185791015625e-07) * M * M +
-                   2.0 * (dotc + 2.384185791015625e-07) * xn * M +
-                   6.0 * sqrt(double(o.d)) * 1.1754943508222875e-38 * (xn + M) +
-                   double(o.d + 2) * 8.881784197001252e-16 * (xn + M) * (xn + M) +
-                   6.0 * double(o.d) * 7.888609052210118e-31;
+                       dot_err_coef(3 * d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u)) * 1.01;
+  return (dot_err_coef(d) + 2.384185791015625e-07) * M * M +
+         2.0 * (dotc + 2.384185791015625e-07) * xn * M +
+         6.0 * sqrt(double(d)) * 1.1754943508222875e-38 * (xn + M) +
+         double(d + 2) * 8.881784197001252e-16 * (xn + M) * (xn + M) +
+         6.0 * double(d) * 7.888609052210118e-31;
+}
+
+// Upper bound of |x| from its fp32 square sum.
+__device__ inline double norm_above(float ss, int32_t d) {
+  const double gam = double(d + 2) * 5.9604644775390625e-08;
+  return sqrt(double(ss) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07);
+}
+
+// Decides one point from its best and second-best value and |x|^2 (fp32), or
+// queues it.
+__device__ inline void assign_decide(const AssignOut& o, int64_t row, const Best& b, float ssr) {
+  const double E = assign_err(o.d, norm_above(ssr, o.d), double(__uint_as_float(*o.maxbits)));
   const double gap = double(b.sv) - double(b.bv);
   if (o.C == 1 || gap > 4.0 * E) {
     const int32_t bi = o.C == 1 ? 0 : b.bi;
@@ -167,8 +183,8 @@ __device__ inline void assign_decide(const AssignOut& o, int64_t row, const Best
 // last round of 469 workgroups on 256 CUs is allowed for).
 // The values of a tile are reduced over the wave's columns (registers, then
 // DPP rotations over the 16 lanes of a point) and merged into the point's
-// best in LDS, so no value is stored.  One group: decided here, else the
-// groups' bests are merged by assign_merge_kernel.
+// best in LDS, so no value is stored.  Decided here without `part`, else part
+// receives each group's best (value, centroid, second value, |x|^2).
 template <bool VEC>
 __global__ __launch_bounds__(512, 2) void assign_kernel(
     const float* __restrict__ X, int64_t n, int32_t d, const bf16x8* __restrict__ cs,
@@ -307,7 +323,7 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
   if (tid < kAsgTile && row0 + tid < n) {
     const Best v = best_merge(Best{sbv[0][tid], sbi[0][tid], ssv[0][tid]},
                               Best{sbv[1][tid], sbi[1][tid], ssv[1][tid]});
-    if (G == 1)
+    if (!part)
       assign_decide(o, row0 + tid, v, sss[tid]);
     else
       part[int64_t(g) * n + row0 + tid] = float4{v.bv, __int_as_float(v.bi), v.sv, sss[tid]};
@@ -399,40 +415,76 @@ size_t kmeans_assign_scratch(int64_t n, int32_t d, int32_t C) {
          (G > 1 ? size_t(G) * n * sizeof(float4) : 0);
 }
 
-int run_kmeans_assign(const float* X, int64_t n, int32_t d, const float* cent, int32_t C,
-                      int32_t* assign, const int32_t* prev, int32_t* changed, void* scratch,
-                      hipStream_t st) {
+struct AsgScratch {
+  float* cnorm;
+  uint32_t* maxbits;
+  int32_t* amb_count;
+  int64_t* amb;
+  bf16x8* cs;
+  float4* part;
+};
+
+static AsgScratch asg_scratch(void* scratch, int64_t n, int32_t d, int32_t C) {
+  AsgScratch a;
   char* p = static_cast<char*>(scratch);
-  float* cnorm = reinterpret_cast<float*>(p);
+  a.cnorm = reinterpret_cast<float*>(p);
   p += al256((size_t(C) + kAsgTile) * 4);
-  uint32_t* maxbits = reinterpret_cast<uint32_t*>(p);
-  int32_t* amb_count = reinterpret_cast<int32_t*>(p + 4);
+  a.maxbits = reinterpret_cast<uint32_t*>(p);
+  a.amb_count = reinterpret_cast<int32_t*>(p + 4);
   p += 256;
-  int64_t* amb = reinterpret_cast<int64_t*>(p);
+  a.amb = reinterpret_cast<int64_t*>(p);
   p += al256(size_t(n) * 8);
-  bf16x8* cs = reinterpret_cast<bf16x8*>(p);
+  a.cs = reinterpret_cast<bf16x8*>(p);
   p += asg_split_bytes(C, d);
-  float4* part = reinterpret_cast<float4*>(p);
+  a.part = reinterpret_cast<float4*>(p);
+  return a;
+}
+
+// The centroids split, then the product: decided through o, or (part) every
+// group's best per point.
+static void launch_product(const float* X, int64_t n, int32_t d, const float* cent, int32_t C,
+                           const AsgScratch& a, int32_t G, const AssignOut& o, float4* part,
+                           hipStream_t st) {
   const int32_t ntiles = int32_t((int64_t(C) + kAsgTile - 1) / kAsgTile);
-  const int32_t G = asg_groups(n, C);
-  const AssignOut o{d, C, maxbits, assign, prev, changed, amb, amb_count};
   hipLaunchKernelGGL(zero_i32_kernel2, dim3(1), dim3(64), 0, st,
-                     reinterpret_cast<int32_t*>(maxbits), int64_t(2));
+                     reinterpret_cast<int32_t*>(a.maxbits), int64_t(2));
   hipLaunchKernelGGL(cent_split_kernel, dim3(unsigned(ntiles) * (kAsgTile / 4)), dim3(256), 0, st,
-                     cent, C, d, cs, cnorm, maxbits);
+                     cent, C, d, a.cs, a.cnorm, a.maxbits);
   const bool vec = (d % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
   const dim3 grid(unsigned((n + kAsgTile - 1) / kAsgTile), unsigned(G));
   if (vec)
-    hipLaunchKernelGGL(assign_kernel<true>, grid, dim3(512), 0, st, X, n, d, cs, cnorm, ntiles, o,
-                       part);
+    hipLaunchKernelGGL(assign_kernel<true>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles,
+                       o, part);
   else
-    hipLaunchKernelGGL(assign_kernel<false>, grid, dim3(512), 0, st, X, n, d, cs, cnorm, ntiles, o,
-                       part);
+    hipLaunchKernelGGL(assign_kernel<false>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles,
+                       o, part);
+}
+
+// The product alone: the groups' bests in part ([G x n]); returns G, and in
+// maxbits where the largest |mu| is.
+static int32_t launch_assign_product(const float* X, int64_t n, int32_t d, const float* cent,
+                                     int32_t C, void* scratch, float4* part,
+                                     const uint32_t** maxbits, hipStream_t st) {
+  const AsgScratch a = asg_scratch(scratch, n, d, C);
+  const int32_t G = asg_groups(n, C);
+  launch_product(X, n, d, cent, C, a, G, AssignOut{d, C, a.maxbits, nullptr, nullptr, nullptr, nullptr, nullptr},
+                 part, st);
+  *maxbits = a.maxbits;
+  return G;
+}
+
+int run_kmeans_assign(const float* X, int64_t n, int32_t d, const float* cent, int32_t C,
+                      int32_t* assign, const int32_t* prev, int32_t* changed, void* scratch,
+                      hipStream_t st) {
+  const AsgScratch a = asg_scratch(scratch, n, d, C);
+  const int32_t G = asg_groups(n, C);
+  const AssignOut o{d, C, a.maxbits, assign, prev, changed, a.amb, a.amb_count};
+  launch_product(X, n, d, cent, C, a, G, o, G > 1 ? a.part : nullptr, st);
   if (G > 1)
     hipLaunchKernelGGL(assign_merge_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st,
-                       part, n, G, o);
+                       a.part, n, G, o);
   hipLaunchKernelGGL(assign_fixup_kernel, dim3(1024), dim3(256), 0, st, X, d, cent, C, assign,
-                     prev, changed, amb, amb_count);
+                     prev, changed, a.amb, a.amb_count);
   return check_hip(hipGetLastError(), "k-means assignment kernels");
 }
 
@@ -513,48 +565,462 @@ int run_centroid_means(const float* X, int64_t n, int32_t d, const int32_t* assi
 }
 
 // ----------------------------------------------------- farthest-first seeding
-// Round t: D_i <- min(D_i, |x_i - c_{t-1}|^2) in fp32 (relative error <= e),
-// then every row whose fp32 value is within the error band of the maximum is
+// D_i = min_j |x_i - c_j|^2 over the chosen centroids in fp32 (relative error
+// <= e); every row whose fp32 value is within the error band of the maximum is
 // rescored exactly (FP64 minimum over all chosen centroids, sequential sums)
-// and the FP64 argmax (ties to the smaller id) becomes centroid t.
+// and the FP64 argmax (ties to the smaller id) becomes the next centroid.
+//
+// Reading the whole corpus once per centroid bounds the plain form (200,000 x
+// 768, 200 centroids: 207 us a round at 3 TB/s, and 89 us for the FP64
+// rescoring).  D_i only falls as centroids are added, so the next centroids
+// are found among few rows: a full pass brings an upper bound U_i of every D_i
+// up to the centroids picked so far (the assignment product: one read of the
+// corpus for all of them, plus its error bound), the rows with the largest U_i
+// (at least tau, about 1% of the rows) become the short list, their D_i are
+// formed as above, and rounds over the list alone pick centroids while the
+// error band of the list's maximum stays at or above tau -- a row outside the
+// list has D_i <= U_i < tau, so it cannot be a candidate.  The candidates of a
+// round, and so the centroids, are those of the plain form.  Where the bounds
+// are too wide for a single pick (values of D_i far below |x|^2), D_i itself is
+// kept for every row from then on.  200,000 x 768, 200 centroids: 61 ms as a
+// full pass and four launches per centroid, 5.1 ms as 5 lists (a full pass
+// 0.37 ms, a list's values 0.1 ms, a round 7 us, 20-40 us where it has to
+// decide among several candidates).
 constexpr double kFFRel = 1.1920928955078125e-07;  // 2^-23 per dimension (fp32 + FP64 side)
 
-__global__ __launch_bounds__(256) void ff_update_kernel(const float* __restrict__ X, int64_t n,
-                                                        int32_t d, const float* __restrict__ c,
-                                                        float* __restrict__ D,
-                                                        uint32_t* __restrict__ maxbits, int first) {
-  __shared__ float wmax[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float mx = 0.f;
-  for (int64_t i = int64_t(blockIdx.x) * 4 + wave; i < n; i += int64_t(gridDim.x) * 4) {
-    const float* xr = X + i * d;
-    float s = 0.f;
-    for (int l = lane; l < d; l += 64) {
-      const float t = xr[l] - c[l];
-      s += t * t;
+struct FFState {
+  int32_t t;          // centroids chosen
+  int32_t status;     // kFFRun, kFFShort or kFFMany
+  int32_t count;      // rows of the short list
+  int32_t inc;        // centroids that the list's values include
+  int32_t done;       // groups of the round's workgroups that are done
+  uint32_t maxbits;   // largest value of the round (float bits)
+  uint32_t fullmax;   // largest bound of the last full pass
+  int32_t ncand;      // candidates (kFFMany)
+  uint32_t taubits;   // smallest value of the list's rows
+  int32_t all;        // every row is on the list
+  // A round's workgroups count in 8 groups, each counter in a line of its own,
+  // and leave their largest values in slots of their own: 256 workgroups with
+  // one maximum and one counter, both at one address, spent most of a 37 us
+  // round queueing there.
+  int32_t gdone[8][32];
+  uint32_t bmax[128];
+};
+// kFFShort: the list no longer holds every possible candidate; kFFMany: more
+// candidates than the round's last workgroup rescores itself.
+enum { kFFRun = 0, kFFShort = 1, kFFMany = 2 };
+constexpr int kFFBins = 4096;       // bins of 2^11 ulp below the maximum
+// candidates, and (candidate, centroid) sums, that a round decides itself
+constexpr int kFFInline = 8, kFFPairs = 64;
+constexpr int kFFChunk = 256;       // squares of such a sum formed at a time
+constexpr int kFFRoundThreads = 1024, kFFRoundGrid = 128;
+static_assert(kFFRoundGrid % 8 == 0, "eight groups of workgroups");
+
+// Smallest fp32 value of a candidate when the largest is M.
+__device__ inline double ff_threshold(double M, int32_t d) {
+  const double e = double(d + 3) * kFFRel;
+  return M * (1.0 - 2.0 * e) / (1.0 + 2.0 * e) - double(d) * 7.888609052210118e-31;
+}
+
+// |x - c|^2 of one row by a wave (every lane returns it).
+template <bool VEC>
+__device__ inline float ff_dist(const float* __restrict__ x, const float* __restrict__ c, int32_t d,
+                                int lane) {
+  float s = 0.f;
+  if (VEC) {
+#pragma unroll 4
+    for (int32_t l = 4 * lane; l < d; l += 256) {
+      const float4 a = *reinterpret_cast<const float4*>(x + l);
+      const float4 b = *reinterpret_cast<const float4*>(c + l);
+      const float p = a.x - b.x, q = a.y - b.y, r = a.z - b.z, w = a.w - b.w;
+      s += p * p;
+      s += q * q;
+      s += r * r;
+      s += w * w;
     }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    float v = first ? s : fminf(D[i], s);
-    if (lane == 0) D[i] = v;
-    mx = fmaxf(mx, v);
+  } else {
+#pragma unroll 4
+    for (int32_t l = lane; l < d; l += 64) {
+      const float p = x[l] - c[l];
+      s += p * p;
+    }
   }
-  if (lane == 0) wmax[wave] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-    atomicMax(maxbits, __float_as_uint(m));
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  return s;
+}
+
+// sd[k] <- min(sd[k], |x - c_j|^2) of row sid[k] (k if sid is null) over the
+// centroids [c0, c1) of the launch's column (blockIdx.y, cper centroids each),
+// as atomic minima of the float bits: all bits set is no value yet, and a NaN
+// is above every value.  count null: n rows.  A wave takes 4 rows x 8
+// centroids at a time, so a centroid value read serves 4 rows and a row value
+// 8 centroids; the 32 sums of the 64 lanes are folded by exchanging halves
+// (lane l ends with row l / 16, centroid (l / 2) % 8 of them).
+template <bool VEC>
+__global__ __launch_bounds__(256) void ff_values_kernel(const float* __restrict__ X, int64_t n,
+                                                        int32_t d, const float* __restrict__ cent,
+                                                        int32_t c0, int32_t c1, int32_t cper,
+                                                        const int32_t* __restrict__ sid,
+                                                        const int32_t* __restrict__ count,
+                                                        uint32_t* __restrict__ sd) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int W = VEC ? 4 : 1;
+  const int64_t rows = count ? int64_t(*count) : n;
+  c0 += int32_t(blockIdx.y) * cper;
+  c1 = min(c1, c0 + cper);
+  for (int64_t r0 = (int64_t(blockIdx.x) * 4 + wave) * 4; r0 < rows; r0 += int64_t(gridDim.x) * 16) {
+    const float* xr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t k = min(r0 + r, rows - 1);
+      xr[r] = X + (sid ? int64_t(sid[k]) : k) * d;
+    }
+    float v = __builtin_nanf("");
+    for (int32_t c = c0; c < c1; c += 8) {
+      const float* cr[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) cr[j] = cent + int64_t(min(c + j, c1 - 1)) * d;
+      float acc[32];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) acc[u] = 0.f;
+      for (int32_t l = W * lane; l < d; l += 64 * W) {
+        float x[4][W];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (VEC)
+            *reinterpret_cast<float4*>(x[r]) = *reinterpret_cast<const float4*>(xr[r] + l);
+          else
+            x[r][0] = xr[r][l];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          float y[W];
+          if (VEC)
+            *reinterpret_cast<float4*>(y) = *reinterpret_cast<const float4*>(cr[j] + l);
+          else
+            y[0] = cr[j][l];
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+              const float p = x[r][e] - y[e];
+              acc[8 * r + j] += p * p;
+            }
+        }
+      }
+#pragma unroll
+      for (int h = 16; h > 0; h >>= 1) {  // 2 h sums -> h, lanes 2 h apart
+        const bool up = lane & (2 * h);
+#pragma unroll
+        for (int u = 0; u < h; ++u) {
+          const float keep = up ? acc[u + h] : acc[u], send = up ? acc[u] : acc[u + h];
+          acc[u] = keep + __shfl_xor(send, 2 * h);
+        }
+      }
+      float w = acc[0] + __shfl_xor(acc[0], 1);
+      for (int o = 8; o > 1; o >>= 1) w = fminf(w, __shfl_xor(w, o));  // over the 8 centroids
+      v = fminf(v, w);  // fminf drops the NaN start
+    }
+    const int64_t k = r0 + (lane >> 4);
+    if ((lane & 15) == 0 && k < rows) atomicMin(&sd[k], __float_as_uint(v) & 0x7fffffffu);
   }
 }
 
-__global__ void ff_candidates_kernel(const float* __restrict__ D, int64_t n, int32_t d,
-                                     const uint32_t* __restrict__ maxbits,
-                                     int64_t* __restrict__ cand, int32_t* __restrict__ ncand) {
-  const double e = double(d + 3) * kFFRel;
-  const double M = double(__uint_as_float(*maxbits));
-  const double T = M * (1.0 - 2.0 * e) / (1.0 + 2.0 * e) - double(d) * 7.888609052210118e-31;
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    if (double(D[i]) >= T) cand[atomicAdd(ncand, 1)] = i;
+// U_i <- min(U_i, |x_i|^2 + g + E), rounded up, from the assignment product's
+// best value g over the last centroids (the smallest over its groups); with
+// no product, U already holds the values.  The largest U_i.
+__global__ __launch_bounds__(256) void ff_bound_kernel(const float4* __restrict__ part, int64_t n,
+                                                       int32_t d, int32_t G,
+                                                       const uint32_t* __restrict__ maxbits,
+                                                       int first, float* __restrict__ U,
+                                                       FFState* __restrict__ fs) {
+  __shared__ float wmax[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float mx = 0.f;
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+    float u = 0.f;
+    if (part) {
+      float g = INFINITY, ss = 0.f;
+      for (int32_t y = 0; y < G; ++y) {
+        const float4 p = part[int64_t(y) * n + i];
+        g = fminf(g, p.x);
+        ss = p.w;
+      }
+      const double xn = norm_above(ss, d);
+      const double b = xn * xn + double(g) + assign_err(d, xn, double(__uint_as_float(*maxbits)));
+      u = float(b);
+      if (double(u) < b) u = nextafterf(u, INFINITY);
+      if (u < 0.f) u = 0.f;  // a NaN stays
+      if (!first) u = fminf(u, U[i]);
+      U[i] = u;
+    } else {
+      u = U[i];
+    }
+    mx = fmaxf(mx, u);
+  }
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if (lane == 0) wmax[wave] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicMax(&fs->fullmax, __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]))));
+}
+
+// Counts of the values by their distance below the maximum in float bits.
+__global__ __launch_bounds__(256) void ff_hist_kernel(const float* __restrict__ U, int64_t n,
+                                                      const FFState* __restrict__ fs,
+                                                      int32_t* __restrict__ hist) {
+  __shared__ int32_t h[kFFBins];
+  for (int b = threadIdx.x; b < kFFBins; b += 256) h[b] = 0;
+  __syncthreads();
+  const uint32_t M = fs->fullmax;
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+    const uint32_t v = __float_as_uint(U[i]);
+    if (v <= M && ((M - v) >> 11) < kFFBins) atomicAdd(&h[(M - v) >> 11], 1);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < kFFBins; b += 256)
+    if (h[b]) atomicAdd(&hist[b], h[b]);
+}
+
+// The list's smallest value: as many whole bins as hold at most `target` rows,
+// and at least those that hold the candidates of the next round.  Without a
+// positive threshold every row is a candidate and goes on the list.
+__global__ __launch_bounds__(1024) void ff_tau_kernel(const int32_t* __restrict__ hist, int32_t d,
+                                                      int32_t target, FFState* __restrict__ fs) {
+  __shared__ int32_t part[1024];
+  __shared__ int32_t best;
+  const int tid = threadIdx.x;
+  int32_t h[kFFBins / 1024], sum = 0;
+#pragma unroll
+  for (int u = 0; u < kFFBins / 1024; ++u) sum += h[u] = hist[tid * (kFFBins / 1024) + u];
+  part[tid] = sum;
+  if (tid == 0) best = 0;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int32_t y = tid >= o ? part[tid - o] : 0;
+    __syncthreads();
+    part[tid] += y;
+    __syncthreads();
+  }
+  int32_t cum = part[tid] - sum;
+#pragma unroll
+  for (int u = 0; u < kFFBins / 1024; ++u) {
+    cum += h[u];
+    if (cum <= target) atomicMax(&best, tid * (kFFBins / 1024) + u);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t M = fs->fullmax;
+    const double T = ff_threshold(double(__uint_as_float(M)), d);
+    fs->all = !(T > 0.0);
+    uint32_t tau = M - min(M, (uint32_t(best + 1) << 11) - 1u);  // the last bin's smallest value
+    if (T > 0.0) {
+      float tf = float(T);  // rounded down, so that T >= tau as real numbers
+      if (double(tf) > T) tf = nextafterf(tf, 0.f);
+      tau = min(tau, __float_as_uint(tf));
+    }
+    fs->taubits = tau;
+    fs->count = 0;
+    fs->inc = fs->t;
+    fs->done = 0;
+    fs->status = kFFRun;
+  }
+}
+
+// The short list: ids of the rows at or above tau, with their values, or none
+// yet (all bits set) where U is only a bound.
+__global__ __launch_bounds__(256) void ff_list_kernel(const float* __restrict__ U, int64_t n,
+                                                      int bound, int32_t* __restrict__ sid,
+                                                      uint32_t* __restrict__ sd,
+                                                      FFState* __restrict__ fs) {
+  const uint32_t tau = fs->taubits;
+  const bool all = fs->all != 0;
+  const int lane = threadIdx.x & 63;
+  const int64_t stride = int64_t(gridDim.x) * 256;
+  for (int64_t i0 = int64_t(blockIdx.x) * 256 + (threadIdx.x - lane); i0 < n; i0 += stride) {
+    const int64_t i = i0 + lane;
+    const uint32_t vb = i < n ? __float_as_uint(U[i]) : 0u;
+    const bool in = i < n && (all || (vb >= tau && vb <= 0x7f800000u));  // no NaN
+    const uint64_t m = __ballot(in);
+    if (!m) continue;
+    int32_t base = 0;
+    if (lane == 0) base = atomicAdd(&fs->count, __popcll(m));
+    base = __shfl(base, 0);
+    if (in) {
+      const int32_t at = base + __popcll(m & ((uint64_t(1) << lane) - 1));
+      sid[at] = int32_t(i);
+      sd[at] = bound ? 0xffffffffu : vb;
+    }
+  }
+}
+
+// Candidates of a round that its last workgroup left (kFFMany), for
+// ff_exact_kernel.
+__global__ void ff_candidates_kernel(const int32_t* __restrict__ sid, const float* __restrict__ sd,
+                                     int32_t d, int64_t* __restrict__ cand,
+                                     FFState* __restrict__ fs) {
+  const double T = ff_threshold(double(__uint_as_float(fs->maxbits)), d);
+  for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < fs->count;
+       k += int32_t(gridDim.x * blockDim.x))
+    if (double(sd[k]) >= T) cand[atomicAdd(&fs->ncand, 1)] = sid[k];
+}
+
+// One round over the short list: a wave per row brings the row's value up to
+// the last centroid; the workgroup that finishes last (an agent-scope counter;
+// the values pass between workgroups as agent-scope atomics) finds the
+// candidates, decides among them and writes the next centroid.  A single
+// candidate needs no rescoring.  Up to kFFInline are rescored here: fp32
+// distances to all centroids first, then the sequential FP64 sum of those that
+// can be the nearest.  It does nothing once the list is used up, so the host
+// enqueues many rounds and looks at the state once.
+template <bool VEC>
+__global__ __launch_bounds__(kFFRoundThreads) void ff_round_kernel(
+    const float* __restrict__ X, int32_t d, float* cent, int32_t C, const int32_t* __restrict__ sid,
+    float* sd, FFState* fs) {
+#pragma clang fp contract(off)
+  constexpr int NW = kFFRoundThreads / 64;
+  __shared__ float wred[NW], cval[kFFInline];
+  __shared__ int32_t s_last, s_n, s_np, cid[kFFInline];
+  __shared__ int32_t pc[kFFPairs], pj[kFFPairs];
+  __shared__ double pex[kFFPairs], sq[NW][kFFChunk];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int32_t t = fs->t, count = fs->count;
+  if (fs->status != kFFRun || t >= C) return;  // only a round's last workgroup changes these
+  const bool update = fs->inc < t;
+  const float* cl = cent + int64_t(t - 1) * d;
+  float mx = 0.f;
+  for (int32_t k = int32_t(blockIdx.x) * NW + wave; k < count; k += int32_t(gridDim.x) * NW) {
+    float v = sd[k];
+    if (update) {
+      v = fminf(v, ff_dist<VEC>(X + int64_t(sid[k]) * d, cl, d, lane));
+      if (lane == 0) __hip_atomic_store(&sd[k], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    mx = fmaxf(mx, v);
+  }
+  if (lane == 0) wred[wave] = mx;
+  // this wave's stores have reached the agent's memory before the workgroup
+  // counts as done (they are agent-scope atomics: waiting for them is enough,
+  // a release fence would write back the whole L2 once per wave)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, wred[w]);
+    __hip_atomic_store(&fs->bmax[blockIdx.x], __float_as_uint(mx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    const bool glast = __hip_atomic_fetch_add(&fs->gdone[blockIdx.x & 7][0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                       kFFRoundGrid / 8 - 1;
+    s_last = glast && __hip_atomic_fetch_add(&fs->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 7;
+    s_n = s_np = 0;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  if (tid < kFFRoundGrid) {
+    float v = __uint_as_float(__hip_atomic_load(&fs->bmax[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    if (lane == 0) wred[wave] = v;
+  }
+  if (tid < 8) fs->gdone[tid][0] = 0;
+  __syncthreads();
+  float M = wred[0];
+  for (int w = 1; w < kFFRoundGrid / 64; ++w) M = fmaxf(M, wred[w]);
+  __syncthreads();
+  const double T = ff_threshold(double(M), d);
+  const bool out = !fs->all && T < double(__uint_as_float(fs->taubits));
+  if (out) {
+    if (tid == 0) {
+      fs->status = kFFShort;
+      fs->done = 0;
+    }
+    return;
+  }
+  for (int32_t k = tid; k < count; k += kFFRoundThreads) {
+    const float v = __hip_atomic_load(&sd[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (double(v) >= T) {
+      const int slot = atomicAdd(&s_n, 1);
+      if (slot < kFFInline) {
+        cid[slot] = sid[k];
+        cval[slot] = v;
+      }
+    }
+  }
+  __syncthreads();
+  const int nc = s_n;
+  int32_t np = 0;
+  if (nc > 1 && nc <= kFFInline) {
+    // the centroids that can be a candidate's nearest: fp32 distances against
+    // the candidate's own minimum, sd
+    const double e = double(d + 3) * kFFRel;
+    for (int32_t u = wave; u < nc * t; u += NW) {
+      const int32_t c = u / t, j = u - c * t;
+      const double lim = double(cval[c]) * (1.0 + 2.0 * e) / (1.0 - 2.0 * e) + double(d) * 7.888609052210118e-31;
+      const float f = ff_dist<VEC>(X + int64_t(cid[c]) * d, cent + int64_t(j) * d, d, lane);
+      if (lane == 0 && !(double(f) > lim)) {
+        const int slot = atomicAdd(&s_np, 1);
+        if (slot < kFFPairs) {
+          pc[slot] = c;
+          pj[slot] = j;
+        }
+      }
+    }
+    __syncthreads();
+    np = s_np;
+  }
+  if (nc > kFFInline || np > kFFPairs) {
+    if (tid == 0) {
+      fs->inc = t;
+      fs->done = 0;
+      fs->ncand = 0;
+      fs->maxbits = __float_as_uint(M);
+      fs->status = kFFMany;
+    }
+    return;
+  }
+  // the sequential FP64 sum of each (candidate, centroid): a wave forms the
+  // squares 256 at a time in LDS, its lane 0 adds them in order
+  for (int32_t u = wave; u < np; u += NW) {
+    const float* xr = X + int64_t(cid[pc[u]]) * d;
+    const float* mu = cent + int64_t(pj[u]) * d;
+    double acc = 0.0;
+    for (int32_t l0 = 0; l0 < d; l0 += kFFChunk) {
+#pragma unroll
+      for (int v = 0; v < kFFChunk; v += 64) {
+        const int32_t l = l0 + v + lane;
+        const double df = l < d ? double(xr[l]) - double(mu[l]) : 0.0;
+        sq[wave][v + lane] = df * df;
+      }
+      __threadfence_block();
+      __builtin_amdgcn_wave_barrier();
+      if (lane == 0) {
+        const int32_t m = min(d - l0, int32_t(kFFChunk));
+#pragma unroll 8
+        for (int32_t l = 0; l < m; ++l) acc = acc + sq[wave][l];
+      }
+      __threadfence_block();
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (lane == 0) pex[u] = acc;
+  }
+  __syncthreads();
+  int32_t pick = nc > 0 ? cid[0] : 0;  // no candidate only with NaN input
+  if (nc > 1) {
+    double pv = -1.0;
+    for (int c = 0; c < nc; ++c) {
+      double v = INFINITY;  // the nearest centroid
+      for (int u = 0; u < np; ++u)
+        if (pc[u] == c) v = fmin(v, pex[u]);
+      if (v > pv || (v == pv && cid[c] < pick)) {
+        pv = v;
+        pick = cid[c];
+      }
+    }
+  }
+  for (int l = tid; l < d; l += kFFRoundThreads) cent[int64_t(t) * d + l] = X[int64_t(pick) * d + l];
+  if (tid == 0) {
+    fs->inc = t;
+    fs->t = t + 1;
+    fs->done = 0;
   }
 }
 
@@ -562,11 +1028,11 @@ __global__ void ff_candidates_kernel(const float* __restrict__ D, int64_t n, int
 __global__ __launch_bounds__(256) void ff_exact_kernel(const float* __restrict__ X, int32_t d,
                                                        const float* __restrict__ cent, int32_t t,
                                                        const int64_t* __restrict__ cand,
-                                                       const int32_t* __restrict__ ncand,
+                                                       const FFState* __restrict__ fs,
                                                        double* __restrict__ dex) {
 #pragma clang fp contract(off)
   __shared__ double sd[256];
-  const int32_t cnt = *ncand;
+  const int32_t cnt = fs->ncand;
   for (int32_t k = blockIdx.x; k < cnt; k += gridDim.x) {
     const float* xr = X + cand[k] * d;
     double best = INFINITY;
@@ -591,16 +1057,15 @@ __global__ __launch_bounds__(256) void ff_exact_kernel(const float* __restrict__
 }
 
 // FP64 argmax over the candidates (ties to the smaller row id); writes the
-// new centroid row, resets the per-round counters.
+// new centroid row and lets the rounds go on.
 __global__ __launch_bounds__(256) void ff_pick_kernel(const float* __restrict__ X, int32_t d,
                                                       float* __restrict__ cent, int32_t t,
-                                                      int64_t* __restrict__ cand,
-                                                      int32_t* __restrict__ ncand,
+                                                      const int64_t* __restrict__ cand,
                                                       const double* __restrict__ dex,
-                                                      uint32_t* __restrict__ maxbits) {
+                                                      FFState* __restrict__ fs) {
   __shared__ double bv[256];
   __shared__ int64_t bi[256];
-  const int32_t cnt = *ncand;
+  const int32_t cnt = fs->ncand;
   double v = -1.0;
   int64_t id = INT64_MAX;
   for (int32_t k = threadIdx.x; k < cnt; k += blockDim.x) {
@@ -629,8 +1094,8 @@ __global__ __launch_bounds__(256) void ff_pick_kernel(const float* __restrict__ 
   for (int l = threadIdx.x; l < d; l += blockDim.x) cent[int64_t(t) * d + l] = X[pick * d + l];
   __syncthreads();
   if (threadIdx.x == 0) {
-    *ncand = 0;
-    *maxbits = 0;
+    fs->t = t + 1;
+    fs->status = kFFRun;
   }
 }
 
@@ -641,6 +1106,114 @@ __global__ void gather_rows_kernel(const float* __restrict__ X, int32_t d,
   if (t >= int64_t(cnt) * d) return;
   const int64_t j = t / d;
   out[t] = X[ids[j] * d + (t - j * d)];
+}
+
+// Farthest-first centroids 1 .. C - 1 into cent (centroid 0 is there).
+// scratch: kmeans_assign_scratch(n, d, C) bytes.
+static int run_farthest(const float* X, int64_t n, int32_t d, float* cent, int32_t C, void* scratch,
+                        hipStream_t st) {
+  float *U = nullptr, *sd = nullptr;
+  int32_t *sid = nullptr, *hist = nullptr;
+  int64_t* cand = nullptr;
+  double* dex = nullptr;
+  float4* part = nullptr;
+  FFState* fs = nullptr;
+  int rc = LIDER_OK;
+  const int32_t gmax = asg_groups(n, C);  // of a product with at most C centroids
+  if (hipMalloc(&U, size_t(n) * 4) != hipSuccess || hipMalloc(&sd, size_t(n) * 4) != hipSuccess ||
+      hipMalloc(&sid, size_t(n) * 4) != hipSuccess ||
+      hipMalloc(&hist, kFFBins * 4) != hipSuccess || hipMalloc(&fs, sizeof(FFState)) != hipSuccess ||
+      hipMalloc(&part, size_t(gmax) * n * sizeof(float4)) != hipSuccess ||
+      hipMalloc(&cand, size_t(n) * 8) != hipSuccess || hipMalloc(&dex, size_t(n) * 8) != hipSuccess)
+    rc = set_error(LIDER_ENOMEM, "out of device memory: farthest-first buffers");
+  // 16-byte loads: rows of both matrices start at multiples of 16 bytes
+  const bool vec = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(cent)) & 15) == 0;
+  // About 1% of the rows, and at most 8,192 (24 MB of rows at d = 768: the
+  // list stays in the Infinity Cache and a round is as short as its launch).
+  const int32_t target = int32_t(std::min<int64_t>(8192, std::max<int64_t>(1024, n / 100)));
+  const unsigned ngrid = unsigned(std::min<int64_t>((n + 255) / 256, 256));
+  // |x - c|^2 of rows (list or all) over the centroids [c0, c1)
+  auto values = [&](int64_t rows, const int32_t* ids, const int32_t* count, int32_t c0, int32_t c1,
+                    float* out) {
+    const int32_t cper = count ? 32 : c1 - c0;
+    const dim3 grid(unsigned(std::min<int64_t>((rows + 15) / 16, 1 << 20)),
+                    unsigned((c1 - c0 + cper - 1) / cper));
+    if (vec)
+      hipLaunchKernelGGL(ff_values_kernel<true>, grid, dim3(256), 0, st, X, n, d, cent, c0, c1, cper,
+                         ids, count, reinterpret_cast<uint32_t*>(out));
+    else
+      hipLaunchKernelGGL(ff_values_kernel<false>, grid, dim3(256), 0, st, X, n, d, cent, c0, c1, cper,
+                         ids, count, reinterpret_cast<uint32_t*>(out));
+  };
+  struct {
+    int32_t t, status;
+  } h{1, kFFRun};  // the state's first words
+  static_assert(offsetof(FFState, t) == 0 && offsetof(FFState, status) == 4, "read back together");
+  int32_t base = 0, guess = 32;
+  bool direct = false;  // U holds D itself
+  if (rc == LIDER_OK) {
+    hipLaunchKernelGGL(zero_i32_kernel2, dim3(2), dim3(256), 0, st, reinterpret_cast<int32_t*>(fs),
+                       int64_t(sizeof(FFState) / 4));
+    rc = check_hip(hipMemcpyAsync(fs, &h, sizeof(h), hipMemcpyHostToDevice, st), "farthest-first state");
+  }
+  while (rc == LIDER_OK && h.t < C) {
+    // every row up to the centroids [base, t), and the next list
+    hipLaunchKernelGGL(zero_i32_kernel2, dim3(16), dim3(256), 0, st, hist, int64_t(kFFBins));
+    hipLaunchKernelGGL(zero_i32_kernel2, dim3(1), dim3(64), 0, st,
+                       reinterpret_cast<int32_t*>(&fs->fullmax), int64_t(1));
+    if (direct) {
+      if (base == 0)
+        hipLaunchKernelGGL(fill_i32_kernel, dim3(ngrid), dim3(256), 0, st,
+                           reinterpret_cast<int32_t*>(U), n, -1);
+      values(n, nullptr, nullptr, base, h.t, U);
+      hipLaunchKernelGGL(ff_bound_kernel, dim3(ngrid), dim3(256), 0, st, (const float4*)nullptr, n, d,
+                         0, (const uint32_t*)nullptr, 0, U, fs);
+    } else {
+      const uint32_t* maxbits = nullptr;
+      const int32_t G = launch_assign_product(X, n, d, cent + int64_t(base) * d, h.t - base, scratch,
+                                              part, &maxbits, st);
+      hipLaunchKernelGGL(ff_bound_kernel, dim3(ngrid), dim3(256), 0, st, part, n, d, G, maxbits,
+                         base == 0 ? 1 : 0, U, fs);
+    }
+    hipLaunchKernelGGL(ff_hist_kernel, dim3(ngrid), dim3(256), 0, st, U, n, fs, hist);
+    hipLaunchKernelGGL(ff_tau_kernel, dim3(1), dim3(1024), 0, st, hist, d, target, fs);
+    hipLaunchKernelGGL(ff_list_kernel, dim3(ngrid), dim3(256), 0, st, U, n, direct ? 0 : 1, sid,
+                       reinterpret_cast<uint32_t*>(sd), fs);
+    if (!direct) values(target, sid, &fs->count, 0, h.t, sd);
+    base = h.t;
+    do {
+      const int32_t rounds = std::min(guess, C - h.t);
+      for (int32_t u = 0; u < rounds; ++u) {
+        if (vec)
+          hipLaunchKernelGGL(ff_round_kernel<true>, dim3(kFFRoundGrid), dim3(kFFRoundThreads), 0, st,
+                             X, d, cent, C, sid, sd, fs);
+        else
+          hipLaunchKernelGGL(ff_round_kernel<false>, dim3(kFFRoundGrid), dim3(kFFRoundThreads), 0,
+                             st, X, d, cent, C, sid, sd, fs);
+      }
+      rc = check_hip(hipGetLastError(), "farthest-first seeding");
+      if (rc == LIDER_OK)
+        rc = check_hip(hipMemcpyAsync(&h, fs, sizeof(h), hipMemcpyDeviceToHost, st), "farthest-first state");
+      if (rc == LIDER_OK) rc = check_hip(hipStreamSynchronize(st), "farthest-first seeding");
+      if (rc == LIDER_OK && h.status == kFFMany) {
+        hipLaunchKernelGGL(ff_candidates_kernel, dim3(ngrid), dim3(256), 0, st, sid, sd, d, cand, fs);
+        hipLaunchKernelGGL(ff_exact_kernel, dim3(256), dim3(256), 0, st, X, d, cent, h.t, cand, fs, dex);
+        hipLaunchKernelGGL(ff_pick_kernel, dim3(1), dim3(256), 0, st, X, d, cent, h.t, cand, dex, fs);
+        ++h.t;
+        h.status = kFFRun;
+      }
+    } while (rc == LIDER_OK && h.status == kFFRun && h.t < C);
+    // rounds past the list's end return at once, but are not free
+    guess = std::min(64, std::max(8, h.t - base + (h.t - base) / 4));
+    if (h.t == base && !direct) {  // not one pick: from now on the values themselves
+      direct = true;
+      base = 0;
+    }
+  }
+  if (rc == LIDER_OK) rc = check_hip(hipStreamSynchronize(st), "farthest-first seeding");
+  for (void* p : {(void*)U, (void*)sd, (void*)sid, (void*)hist, (void*)fs, (void*)cand, (void*)dex, (void*)part})
+    if (p) (void)hipFree(p);
+  return rc;
 }
 
 // Lloyd iterations into ix.cent / ix.assign.
@@ -674,36 +1247,7 @@ int run_kmeans(Index& ix, const float* X, const int64_t* init_host, int32_t iter
     hipLaunchKernelGGL(gather_rows_kernel, dim3(unsigned((tot + 255) / 256)), dim3(256), 0, st,
                        X, d, init_dev, seeding ? 1 : C, ix.cent);
   }
-  if (rc == LIDER_OK && seeding == 1 && C > 1) {
-    float* D = nullptr;
-    int64_t* cand = nullptr;
-    double* dex = nullptr;
-    if (hipMalloc(&D, size_t(n) * 4) != hipSuccess || hipMalloc(&cand, size_t(n) * 8) != hipSuccess ||
-        hipMalloc(&dex, size_t(n) * 8) != hipSuccess)
-      fail(LIDER_ENOMEM, "farthest-first buffers");
-    int32_t* ncand = changed;  // [0] candidate count, [1] max bits
-    uint32_t* maxbits = reinterpret_cast<uint32_t*>(changed + 1);
-    if (rc == LIDER_OK) {
-      hipLaunchKernelGGL(zero_i32_kernel2, dim3(1), dim3(64), 0, st, changed, int64_t(2));
-      const unsigned ub = unsigned(std::min<int64_t>((n + 3) / 4, 8192));
-      const unsigned cb = unsigned(std::min<int64_t>((n + 255) / 256, 4096));
-      for (int32_t t = 1; t < C; ++t) {
-        hipLaunchKernelGGL(ff_update_kernel, dim3(ub), dim3(256), 0, st, X, n, d,
-                           ix.cent + int64_t(t - 1) * d, D, maxbits, t == 1 ? 1 : 0);
-        hipLaunchKernelGGL(ff_candidates_kernel, dim3(cb), dim3(256), 0, st, D, n, d, maxbits,
-                           cand, ncand);
-        hipLaunchKernelGGL(ff_exact_kernel, dim3(256), dim3(256), 0, st, X, d, ix.cent, t, cand,
-                           ncand, dex);
-        hipLaunchKernelGGL(ff_pick_kernel, dim3(1), dim3(256), 0, st, X, d, ix.cent, t, cand,
-                           ncand, dex, maxbits);
-      }
-      rc = check_hip(hipGetLastError(), "farthest-first seeding");
-      if (rc == LIDER_OK) rc = check_hip(hipStreamSynchronize(st), "farthest-first seeding");
-    }
-    if (D) hipFree(D);
-    if (cand) hipFree(cand);
-    if (dex) hipFree(dex);
-  }
+  if (rc == LIDER_OK && seeding == 1 && C > 1) rc = run_farthest(X, n, d, ix.cent, C, scr_a, st);
   int cur = 0, fin = 0;
   int32_t it = 0;
   while (rc == LIDER_OK && it < iters) {
