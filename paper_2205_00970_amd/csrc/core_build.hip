@@ -151,30 +151,49 @@ __global__ void x_kernel(const uint64_t* __restrict__ keys, const uint32_t* __re
     x[t] = rescale(keys[t], mb[seg2[t]]);
 }
 
-// Least squares of location on re-scaled key over the positions [a, e) of one
-// model whose leaf equals `leaf` (-1: all), sums in location order.
+// f(p, x[p]) over the positions [p0, p1) in order, eight loads in flight (the
+// sums that f keeps are chains, the reads are not).
+template <class Fn>
+__device__ inline void in_order(const double* __restrict__ x, int64_t p0, int64_t p1, Fn f) {
+  int64_t p = p0;
+  for (; p + 8 <= p1; p += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[p + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f(p + u, v[u]);
+  }
+  for (; p < p1; ++p) f(p, x[p]);
+}
+
+// Least squares of location on re-scaled key over the positions [p0, p1) of a
+// model that starts at a (only those whose leaf equals `leaf` when lf is
+// given), sums in location order.
 __device__ void ols_range(const double* __restrict__ x, const int32_t* __restrict__ lf, int64_t a,
-                          int64_t e, int32_t leaf, double* slope, double* icpt, int64_t* count) {
+                          int64_t p0, int64_t p1, int32_t leaf, double* slope, double* icpt,
+                          int64_t* count) {
 #pragma clang fp contract(off)
   int64_t n = 0;
   double sx = 0.0, sy = 0.0;
-  for (int64_t p = a; p < e; ++p) {
-    if (leaf >= 0 && lf[p] != leaf) continue;
-    sx = sx + x[p];
+  in_order(x, p0, p1, [&](int64_t p, double v) {
+#pragma clang fp contract(off)
+    if (lf && lf[p] != leaf) return;
+    sx = sx + v;
     sy = sy + double(p - a);
     ++n;
-  }
+  });
   *count = n;
   if (n == 0) return;
   const double mx = sx / double(n), my = sy / double(n);
   double sxx = 0.0, sxy = 0.0;
-  for (int64_t p = a; p < e; ++p) {
-    if (leaf >= 0 && lf[p] != leaf) continue;
-    const double dx = x[p] - mx;
+  in_order(x, p0, p1, [&](int64_t p, double v) {
+#pragma clang fp contract(off)
+    if (lf && lf[p] != leaf) return;
+    const double dx = v - mx;
     const double dy = double(p - a) - my;
     sxx = sxx + dx * dx;
     sxy = sxy + dx * dy;
-  }
+  });
   *slope = sxx > 0.0 ? sxy / sxx : 0.0;
   *icpt = my - (*slope) * mx;
 }
@@ -187,7 +206,7 @@ __global__ void root_kernel(Model* __restrict__ mb, int32_t nseg, const int64_t*
   if (e == a) return;
   double s = 0.0, c = 0.0;
   int64_t cnt;
-  ols_range(x, nullptr, a, e, -1, &s, &c, &cnt);
+  ols_range(x, nullptr, a, a, e, -1, &s, &c, &cnt);
   mb[j].root_a = s;
   mb[j].root_b = c;
 }
@@ -204,6 +223,12 @@ __global__ void leaf_index_kernel(const double* __restrict__ x, const uint32_t* 
 
 // One thread per (model, leaf): fit (empty leaf copies the root), then the
 // min / max of (true location - predicted location) over the leaf's items.
+// The keys of a model ascend and every operation of the leaf rule is monotone,
+// so with a root slope >= 0 a leaf's items are consecutive: the thread finds
+// them by two binary searches (200 clusters of 1,000 rows with 64 leaves: 630
+// us when every leaf scanned its whole model, 28 us now; the root fit 430 ->
+// 80 us from the loads in flight).  A negative slope (rounding alone could
+// give one) scans the model.
 __global__ void leaf_fit_kernel(const Model* __restrict__ mb, int32_t nseg, int32_t F,
                                 const int64_t* __restrict__ off, const double* __restrict__ x,
                                 const int32_t* __restrict__ lf, double* __restrict__ leaves,
@@ -218,16 +243,34 @@ __global__ void leaf_fit_kernel(const Model* __restrict__ mb, int32_t nseg, int3
   double s = 0.0, c = 0.0;
   int32_t elo = 0, ehi = 0;
   if (e > a) {
+    int64_t p0 = a, p1 = e;
+    const bool ranges = M.root_a >= 0.0;
+    if (ranges) {
+      auto first_at_least = [&](int32_t v, int64_t lo) {
+        int64_t hi = e;
+        while (lo < hi) {
+          const int64_t mid = (lo + hi) >> 1;
+          if (lf[mid] < v)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        return lo;
+      };
+      p0 = first_at_least(leaf, a);
+      p1 = first_at_least(leaf + 1, p0);
+    }
+    const int32_t* lfp = ranges ? nullptr : lf;
     int64_t cnt;
-    ols_range(x, lf, a, e, leaf, &s, &c, &cnt);
+    ols_range(x, lfp, a, p0, p1, leaf, &s, &c, &cnt);
     if (cnt == 0) {
       s = M.root_a;
       c = M.root_b;
     } else {
       bool seen = false;
-      for (int64_t p = a; p < e; ++p) {
-        if (lf[p] != leaf) continue;
-        const int64_t err = (p - a) - pos_of(s, c, M.L, x[p]);
+      in_order(x, p0, p1, [&](int64_t p, double v) {
+        if (lfp && lfp[p] != leaf) return;
+        const int64_t err = (p - a) - pos_of(s, c, M.L, v);
         if (!seen) {
           elo = ehi = int32_t(err);
           seen = true;
@@ -235,7 +278,7 @@ __global__ void leaf_fit_kernel(const Model* __restrict__ mb, int32_t nseg, int3
           elo = err < elo ? int32_t(err) : elo;
           ehi = err > ehi ? int32_t(err) : ehi;
         }
-      }
+      });
     }
   }
   leaves[2 * slot] = s;

