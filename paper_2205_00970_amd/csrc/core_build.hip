@@ -482,11 +482,15 @@ __global__ void compose_kernel(const int64_t* __restrict__ permh, int64_t n,
 // dims [32 ks + 16 h + 4 s, + 4) of row i at float offset ((b nks + ks) 2 + h)
 // 256 + 4 l.  bf16 (KS = 64): dims [64 ks + 32 h + 8 s, + 8), rounded to
 // nearest even like the row-major bf16 copy, at element offset
-// ((b nks + ks) 2 + h) 512 + 8 l.
+// ((b nks + ks) 2 + h) 512 + 8 l.  The fp32 copy also takes an upper bound of
+// max |x| over the rows (float bits, one atomicMax per workgroup).
 template <bool BF>
 __global__ __launch_bounds__(256) void tile_corpus_kernel(const float* __restrict__ X, int32_t d,
                                                           const int2* __restrict__ src,
-                                                          int64_t nblk, void* __restrict__ out) {
+                                                          int64_t nblk, void* __restrict__ out,
+                                                          uint32_t* __restrict__ maxbits) {
+  __shared__ uint32_t wmax[4];
+  uint32_t mx = 0;  // a NaN's bits are above every value
   constexpr int KS = BF ? 64 : kTileKS, EPL = BF ? 8 : 4;  // dims per k-step, per lane
   const int lane = threadIdx.x & 63;
   const int i = lane & 15, s = lane >> 4;
@@ -496,6 +500,7 @@ __global__ __launch_bounds__(256) void tile_corpus_kernel(const float* __restric
     const int2 sr = src[b];
     const bool ok = i < sr.y;
     const float* xr = X + (int64_t(sr.x) + (ok ? i : 0)) * d;
+    float ss = 0.f;
     for (int32_t ks = 0; ks < nks; ++ks)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -508,8 +513,25 @@ __global__ __launch_bounds__(256) void tile_corpus_kernel(const float* __restric
         } else {
           const float4 v = ok ? *reinterpret_cast<const float4*>(xr + k) : float4{0.f, 0.f, 0.f, 0.f};
           *reinterpret_cast<float4*>(static_cast<float*>(out) + at) = v;
+          ss += v.x * v.x;
+          ss += v.y * v.y;
+          ss += v.z * v.z;
+          ss += v.w * v.w;
         }
       }
+    if (!BF) {
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      const double gam = double(d + 2) * 5.9604644775390625e-08;
+      const float ub = float(sqrt(double(ss) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07));
+      mx = max(mx, __float_as_uint(ub) & 0x7fffffffu);
+    }
+  }
+  if (!BF) {
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, uint32_t(__shfl_xor(mx, o)));
+    if (lane == 0) wmax[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(maxbits, max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3])));
   }
 }
 
@@ -646,7 +668,8 @@ int finish_index(Index& ix) {
       }
     int2* dsrc = nullptr;
     const size_t elems = size_t(nblk) * 16 * size_t(ix.d);  // per copy
-    if (hipMalloc(&dsrc, al256(src.size() * sizeof(int2))) != hipSuccess)
+    const size_t tab = al256(src.size() * sizeof(int2));  // then the largest norm
+    if (hipMalloc(&dsrc, tab + 256) != hipSuccess)
       return set_error(LIDER_ENOMEM, "out of device memory (operand-ordered corpus)");
     // the copies are an optimisation: without room for one, the rerank reads
     // the row-major rows instead
@@ -660,14 +683,19 @@ int finish_index(Index& ix) {
     }
     rc = check_hip(hipMemcpy(dsrc, src.data(), src.size() * sizeof(int2), hipMemcpyHostToDevice),
                    "copy block table");
-    const dim3 grid(unsigned(std::min<int64_t>((nblk + 3) / 4, 65536)));
-    if (rc == LIDER_OK && ix.Xt)
+    uint32_t* mb = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(dsrc) + tab);
+    const dim3 grid(unsigned(std::min<int64_t>((nblk + 3) / 4, 8192)));
+    if (rc == LIDER_OK && ix.Xt) {
+      hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, nullptr, reinterpret_cast<int32_t*>(mb), int64_t(1), 0);
       hipLaunchKernelGGL(tile_corpus_kernel<false>, grid, dim3(256), 0, nullptr, ix.X, ix.d, dsrc,
-                         nblk, (void*)ix.Xt);
+                         nblk, (void*)ix.Xt, mb);
+    }
     if (rc == LIDER_OK && ix.Xbt)
       hipLaunchKernelGGL(tile_corpus_kernel<true>, grid, dim3(256), 0, nullptr, ix.X, ix.d, dsrc,
-                         nblk, (void*)ix.Xbt);
+                         nblk, (void*)ix.Xbt, (uint32_t*)nullptr);
     if (rc == LIDER_OK) rc = check_hip(hipGetLastError(), "operand-ordered corpus");
+    if (rc == LIDER_OK && ix.Xt)
+      rc = check_hip(hipMemcpy(&ix.x_norm_max, mb, 4, hipMemcpyDeviceToHost), "largest row norm");
     if (rc == LIDER_OK) rc = check_hip(hipDeviceSynchronize(), "operand-ordered corpus");
     (void)hipFree(dsrc);
     if (rc != LIDER_OK) return rc;

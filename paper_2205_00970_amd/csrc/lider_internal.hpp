@@ -260,6 +260,7 @@ struct Index {
   // precision form (bf16 copy): upper bounds over the rows of max |x|,
   // max |x - bf16(x)| and max |bf16(x)| (host copies)
   float xb_bound[3] = {0.f, 0.f, 0.f};
+  float x_norm_max = INFINITY;  // upper bound of max |x| (where Xt is built)
   Model* models = nullptr;     // [H x (C+1)], model h*(C+1) + C = array h of layer 1
   double* leaves = nullptr;    // [H x (C*F2 + F1) x 2]
   int32_t* leaf_err = nullptr; // [H x (C*F2 + F1) x 2]

@@ -51,6 +51,7 @@ struct Plan {
   int32_t r1, rcap, S;
   int ti, npcm;  // rerank tile table and 16-pair blocks per pass
   bool cert;     // precision form with the certified shortlist
+  bool split;    // windows scored by the split product, short lists rescored
   size_t o_scnt;
   // l1_dense_rows: layer-1 scores of every centroid (dense product), else of
   // the r1-windows (window kernel).  Several hashkey arrays: lcap = layer-1
@@ -62,6 +63,20 @@ struct Plan {
   size_t o_bkey;
   int32_t nbcap;
 };
+
+// The split window scores (fp32 search): with many pairs per tile the fp32
+// MFMA rate (1/16 of bf16's) bounds the rerank, so the windows are scored by
+// three bf16 products of the split operands instead (WgPass below) and the rows
+// within the error bound of the k-th best are rescored by the fp32 product
+// itself, in the same order of operations, so ids and scores keep every bit.
+// The rescoring gathers about k rows per query (10,000 queries, k = 10: 0.1
+// GB per place), which outweighs the gain for long result lists.
+constexpr int32_t kSplitMaxK = 16;
+constexpr int32_t kSplitCap = 62;  // rows listed per query; a longer list is found again
+// Largest row norm of an index that takes it: no part or product of the split
+// overflows while |q| |x| stays below kSplitMaxNorm (decided per query).
+constexpr float kSplitMaxRow = 1e15f;
+constexpr double kSplitMaxNorm = 1e37;
 
 // Rerank shape: rows per tile (index into the tile tables: 32, 64, 128) and
 // 16-pair column blocks per MFMA pass.  A tile overlapped by P pairs is
@@ -171,6 +186,10 @@ Plan make_plan(const Index& ix, int64_t nq, int32_t k, int32_t c, int32_t r,
   p.o_bkey = take(size_t(np) * nbroom * 4);
   rerank_shape(ix, nq, c, r, o, &p.ti, &p.npcm);
   const size_t nt = o.persistent == 2 ? size_t(ix.n_tiles[p.ti]) : 0;
+  // its lists take the room of the layer-1 scores, which nothing reads any more
+  p.split = o.precision == LIDER_F32 && o.persistent == 0 && o.tile_rows == 0 &&
+            o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && k <= kSplitMaxK &&
+            (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.x_norm_max < kSplitMaxRow;
   p.o_aflag = take(nt * 4);
   p.o_alist = take(nt * 4);
   p.o_kq = take(o.expand_bits > 0 ? size_t(nq) * std::max<int32_t>(c, 1) * H * 8 : 0);
@@ -420,7 +439,28 @@ struct CertArgs {
   float xmax = 0.f, xres = 0.f, xbmax = 0.f;
   int32_t* scnt = nullptr;  // [nq] rows listed per query
   int64_t cap = 0;          // list entries per query (all its candidates)
+  // split window scores: a score differs from the fp32 product's by at most
+  // E_q = ecoef |q| max|x| + eadd + esub (|q| + max|x|); scnt[q] counts the
+  // rows within the margin, of which the first cap are listed, or is -1 where
+  // no margin holds (values that can overflow); sthr[q] is the margin's key
+  const float* qnorm = nullptr;
+  double ecoef = 0.0, eadd = 0.0, esub = 0.0;
+  uint32_t* sthr = nullptr;
 };
+
+// Largest key (lowest score) listed for query q of the split window scores,
+// from the k-th best key T (0xffffffff: fewer than k candidates).
+__device__ inline uint32_t split_threshold(const CertArgs& ca, int64_t q, uint32_t T, bool* finite) {
+  const double qn = double(ca.qnorm[q]), xm = double(ca.xmax);
+  *finite = qn < kSplitMaxNorm && qn * xm < kSplitMaxNorm;
+  if (!*finite) return 0xffffffffu;
+  if (T == 0xffffffffu) return 0xfffffffeu;
+  const double E = (ca.ecoef * qn * xm + ca.eadd + ca.esub * (qn + xm)) * (1.0 + 0x1p-20);
+  const double thr = double(key_score(T)) - 2.0 * E;
+  float f = float(thr);
+  if (double(f) > thr) f = nextafterf(f, -INFINITY);
+  return score_key(f);
+}
 
 // Wave-wide (64 active lanes): the largest key (lowest score) still listed,
 // from the k-th best key T; T = 0xffffffff (fewer than k candidates) lists
@@ -1463,6 +1503,7 @@ constexpr int kRerankNT = 64;  // threads per rerank workgroup (one wave)
 __device__ inline int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // Operand feeds.  FMT 0: fp32 rows and queries; 1: bf16 rows and queries;
 // 2: fp8 e4m3 rows (decoded exactly to bf16) and bf16 queries; 3 / 4: fp32 /
@@ -1472,7 +1513,9 @@ typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 // to back instead of by two consecutive k-steps).  Lane slot s covers the
 // dimensions [SUBW*s, SUBW*s + SUBW) of the first load and the same range
 // plus KS/2 of the second.
-enum { kF32 = 0, kBF16 = 1, kFP8 = 2, kF32W = 3, kBF16W = 4 };
+// 5: kF32W's rows and queries, each value x split into h = bf16(x) and l =
+// bf16(x - h) for three bf16 products (the workgroup rerank only).
+enum { kF32 = 0, kBF16 = 1, kFP8 = 2, kF32W = 3, kBF16W = 4, kF32S = 5 };
 
 template <int FMT, bool VEC>
 struct Feed;
@@ -1646,6 +1689,28 @@ struct Feed<kBF16W, VEC> {  // 64 dims per k-step: 8 + 8 per lane
   }
 };
 
+// The split of a lane's eight values (the difference is exact).
+__device__ inline BF16x2 split_f32x8(const floatx4& a, const floatx4& b) {
+  BF16x2 r;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float v = e < 4 ? a[e] : b[e - 4];
+    const __bf16 h = (__bf16)v;
+    r.a[e] = h;
+    r.b[e] = (__bf16)(v - float(h));
+  }
+  return r;
+}
+
+// T holds the parts (h, l), or a row's eight fp32 values as loaded.
+template <>
+struct Feed<kF32S, true> {  // 32 dims per k-step, 8 per lane, kF32W's layout
+  static constexpr int KS = 32, SUBW = 4;
+  typedef float XE;
+  typedef float QE;
+  typedef BF16x2 T;
+};
+
 // Row source of a tile read in row-major order: one pointer per 16-row block
 // (rows past the tile clamped to its last row).
 template <class F, int RC>
@@ -1708,6 +1773,24 @@ __device__ __forceinline__ void mfma_step(const typename F::T (&x)[RC],
   for (int pc = 0; pc < NPC; ++pc) {
 #pragma unroll
     for (int rc = 0; rc < RC; ++rc) F::mfma(qv[pc], x[rc], acc[rc][pc]);
+  }
+}
+
+// h_q h_x + h_q l_x + l_q h_x of one k-step of split operands.
+template <int RC, int NPC, int NPCM>
+__device__ __forceinline__ void split_step(const BF16x2 (&x)[RC], const BF16x2 (&qv)[NPC],
+                                           floatx4 (&acc)[RC][NPCM]) {
+#pragma unroll
+  for (int pc = 0; pc < NPC; ++pc) {
+#pragma unroll
+    for (int rc = 0; rc < RC; ++rc)
+      acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[pc].a, x[rc].a, acc[rc][pc], 0, 0, 0);
+#pragma unroll
+    for (int rc = 0; rc < RC; ++rc)
+      acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[pc].a, x[rc].b, acc[rc][pc], 0, 0, 0);
+#pragma unroll
+    for (int rc = 0; rc < RC; ++rc)
+      acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[pc].b, x[rc].a, acc[rc][pc], 0, 0, 0);
   }
 }
 
@@ -2059,7 +2142,8 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const TileRows<
     qon[j] = pc < NPC;
     const int e = qon[j] ? min(16 * pc + r, np - 1) : 0;
     qsrc[j] = Q + int64_t(sh.lq[e]) * d + part * (16 / int(sizeof(QE)));
-    qdst[j] = pc * kWgQBlk + r * kWgQRow + part * 16;
+    qdst[j] = pc * kWgQBlk + r * kWgQRow +
+              (FMT == kF32S ? (part & 3) * 16 + (part >> 2) * 8 : part * 16);
   }
   floatx4 sg[2][NCH];
   auto stage_load = [&](int k, floatx4 (&dst)[NCH]) {
@@ -2070,7 +2154,22 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const TileRows<
   auto stage_store = [&](int slot, const floatx4 (&src)[NCH]) {
 #pragma unroll
     for (int j = 0; j < NCH; ++j)
-      if (qon[j]) *reinterpret_cast<floatx4*>(&sh.qs[slot][qdst[j]]) = src[j];
+      if (qon[j]) {
+        if constexpr (FMT == kF32S) {
+          // a 128-byte row holds the h parts of the four lane slots, then the
+          // l parts; part p of the step is half p / 4 of slot p % 4
+          bf16x4 h, l;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            h[e] = (__bf16)src[j][e];
+            l[e] = (__bf16)(src[j][e] - float(h[e]));
+          }
+          *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j]]) = h;
+          *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j] + 64]) = l;
+        } else {
+          *reinterpret_cast<floatx4*>(&sh.qs[slot][qdst[j]]) = src[j];
+        }
+      }
   };
   // the wave's query operands of step k from LDS slot k % 2: lane (i, s)
   // reads pair row i of each block at the lane's two 16-byte halves
@@ -2108,7 +2207,16 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const TileRows<
         if (K + RING - 1 < nsteps) xload(K + RING - 1, xs[(J + RING - 1) % RING]);
         T qv[NPC];
         qread(J & 1, qv);
-        mfma_step<F, RC, NPC, NPCM>(xs[J % RING], qv, acc);
+        if constexpr (FMT == kF32S) {
+          T xp[RC];
+#pragma unroll
+          for (int rc = 0; rc < RC; ++rc)
+            xp[rc] = split_f32x8(__builtin_bit_cast(floatx4, xs[J % RING][rc].a),
+                                 __builtin_bit_cast(floatx4, xs[J % RING][rc].b));
+          split_step<RC, NPC, NPCM>(xp, qv, acc);
+        } else {
+          mfma_step<F, RC, NPC, NPCM>(xs[J % RING], qv, acc);
+        }
         if (K + 1 < nsteps) stage_store((J + 1) & 1, sg[(J + 1) & 1]);
         __syncthreads();
       }
@@ -2680,8 +2788,9 @@ __global__ __launch_bounds__(kSelNT) void select_kernel(
   }
 }
 
-// Per query top K (K <= 64), one wave per query: repeated wave minima of
-// (key, candidate index) extract the K + 1 best; an exact key tie at the K-th
+// Per query top K (K <= 64), one wave per query (MODE 0: ids and scores, 1: the
+// fixed shortlist, 2: the certified one, 3: the rows of the split window
+// scores to rescore): repeated wave minima of (key, candidate index) extract the K + 1 best; an exact key tie at the K-th
 // place is resolved by original id over all tied candidates; the winners are
 // finally ordered by (score desc, id asc).  MODE 0 writes ids / scores, MODE 1
 // the shortlist of sorted-row indices.  drop: NaN scores (key 0xffffffff) are
@@ -3229,12 +3338,25 @@ __global__ __launch_bounds__(256) void wave_select_kernel(
       // best key (the largest winner key when all K places are taken)
       uint32_t tk = lane < got ? myk : 0u;
       for (int o = 32; o > 0; o >>= 1) tk = max(tk, uint32_t(__shfl_xor(tk, o)));
-      const uint32_t thr = cert_threshold(ca, q, got == K ? tk : 0xffffffffu, lane);
+      if (got < K) tk = 0xffffffffu;
+      uint32_t thr;
+      if (MODE == 3) {
+        bool finite;
+        thr = split_threshold(ca, q, tk, &finite);
+        if (lane == 0) ca.sthr[q] = thr;
+        if (!finite) {  // wave-uniform
+          if (lane == 0) ca.scnt[q] = -1;
+          return;
+        }
+      } else {
+        thr = cert_threshold(ca, q, tk, lane);
+      }
       int m = 0;
       auto cert = [&](int32_t i, uint32_t kk, bool ok) {
         const bool in = ok && kk <= thr;
         const uint64_t bal = __ballot(in);
-        if (in) slist[q * ca.cap + m + __popcll(bal & below)] = int32_t(row_of(i));
+        const int slot = m + __popcll(bal & below);
+        if (in && (MODE == 2 || slot < ca.cap)) slist[q * ca.cap + slot] = int32_t(row_of(i));
         m += __popcll(bal);
       };
       if (bform)  // the blocks hold every candidate with key <= thr
@@ -3811,6 +3933,139 @@ __global__ __launch_bounds__(256) void cert_wave_kernel(
   }
 }
 
+// Second pass of the split window scores (k <= kSplitMaxK), one wave per
+// query: the fp32 score of every row within the margin, then the top k by
+// (score desc, id asc).  Sixteen rows at a time form the column operand of
+// v_mfma_f32_16x16x4f32, the query (in all sixteen rows) the other, over the
+// same k-steps in the same order as the rerank's fp32 feed, so a score has the
+// bits that feed gives it.  The rows are gathered from X, 128 bytes of each per
+// step, two steps ahead; the gather bounds it (10,000 queries, k = 10, 10.3
+// rows each
+// on average: 317 MB in 80 us).
+// A list past its room, or no margin at all (scnt -1), is taken from the score
+// rows again, 64 positions at a time; without a margin every candidate counts,
+// by the membership masks where there are several arrays (drop), since its
+// score may be a NaN.
+__global__ __launch_bounds__(256) void split_rescore_kernel(
+    const float* __restrict__ X, int32_t d, const float* __restrict__ Q, int64_t nq,
+    const int32_t* __restrict__ slist, const int32_t* __restrict__ scnt,
+    const uint32_t* __restrict__ sthr, const Pair* __restrict__ pairs,
+    const float* __restrict__ sbuf, int32_t rcap, int32_t c, const int64_t* __restrict__ off,
+    const uint32_t* __restrict__ pmask, int32_t mw, const int32_t* __restrict__ perm32, int32_t k,
+    int64_t* __restrict__ ids, float* __restrict__ scores) {
+  __shared__ int32_t rows[4][64];
+  __shared__ uint32_t bkey[4][kSplitMaxK], bid[4][kSplitMaxK];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));  // uniform
+  const int i = lane & 15, s = lane >> 4;
+  const int64_t q = int64_t(blockIdx.x) * 4 + wave;
+  if (q >= nq) return;
+  const bool drop = pmask != nullptr;
+  const float* qv = Q + q * d + 4 * s;
+  const int nsteps = d / 32;
+  int nb = 0;  // entries of the best list (wave-uniform)
+  // merges the rows of lanes 0 .. m - 1 into the best list
+  auto take = [&](int32_t myrow, int m) {
+    float sc = 0.f;
+    for (int b = 0; 16 * b < m; ++b) {
+      const float* xr = X + int64_t(__shfl(myrow, min(16 * b + i, m - 1))) * d + 4 * s;
+      floatx4 acc{0.f, 0.f, 0.f, 0.f};
+      floatx4 x[3][2], y[3][2];
+      auto load = [&](int ks, floatx4 (&xo)[2], floatx4 (&yo)[2]) {
+        const int o = 32 * min(ks, nsteps - 1);
+        xo[0] = *reinterpret_cast<const floatx4*>(xr + o);
+        xo[1] = *reinterpret_cast<const floatx4*>(xr + o + 16);
+        yo[0] = *reinterpret_cast<const floatx4*>(qv + o);
+        yo[1] = *reinterpret_cast<const floatx4*>(qv + o + 16);
+      };
+      load(0, x[0], y[0]);
+      load(1, x[1], y[1]);
+      for (int ks = 0; ks < nsteps; ks += 3) {
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          if (ks + u < nsteps) {
+            load(ks + u + 2, x[(u + 2) % 3], y[(u + 2) % 3]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y[u][h][e], x[u][h][e], acc, 0, 0, 0);
+          }
+        }
+      }
+      if (s == b) sc = acc[0];  // every lane of column i holds row 16 b + i's score
+    }
+    const uint32_t ka = lane < m ? score_key(sc) : 0xffffffffu;
+    const uint32_t ia = lane < m ? uint32_t(perm32[myrow]) : 0xffffffffu;
+    const bool ok = lane < m && !(drop && ka == 0xffffffffu);
+    const uint64_t okm = __ballot(ok);
+    const uint32_t kb = lane < nb ? bkey[wave][lane] : 0xffffffffu;
+    const uint32_t ib = lane < nb ? bid[wave][lane] : 0xffffffffu;
+    int ra = 0, rb = 0;
+    for (int u = 0; u < m; ++u) {
+      if (!((okm >> u) & 1u)) continue;  // wave-uniform
+      const uint32_t ku = uint32_t(__builtin_amdgcn_readlane(int(ka), u));
+      const uint32_t iu = uint32_t(__builtin_amdgcn_readlane(int(ia), u));
+      ra += (ku < ka) || (ku == ka && iu < ia);
+      rb += (ku < kb) || (ku == kb && iu < ib);
+    }
+    for (int u = 0; u < nb; ++u) {
+      const uint32_t kv = uint32_t(__builtin_amdgcn_readlane(int(kb), u));
+      const uint32_t iv = uint32_t(__builtin_amdgcn_readlane(int(ib), u));
+      ra += (kv < ka) || (kv == ka && iv < ia);
+      rb += (kv < kb) || (kv == kb && iv < ib);
+    }
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+    if (ok && ra < k) {
+      bkey[wave][ra] = ka;
+      bid[wave][ra] = ia;
+    }
+    if (lane < nb && rb < k) {
+      bkey[wave][rb] = kb;
+      bid[wave][rb] = ib;
+    }
+    nb = min(k, nb + __popcll(okm));
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+  };
+  const int32_t n = scnt[q];
+  if (n >= 0 && n <= kSplitCap) {
+    take(lane < n ? slist[q * kSplitCap + lane] : 0, n);
+  } else {
+    const uint32_t thr = sthr[q];
+    for (int32_t t = 0; t < c; ++t) {
+      const Pair pr = pairs[q * c + t];
+      if (pr.j < 0) continue;  // wave-uniform
+      const float* sb = sbuf + (q * c + t) * int64_t(rcap);
+      const uint32_t* pm = drop ? pmask + (q * c + t) * int64_t(mw) : nullptr;
+      const int64_t base = off[pr.j] + pr.s;
+      for (int32_t p0 = 0; p0 < pr.len; p0 += 64) {
+        const int32_t p = p0 + lane;
+        bool in = p < pr.len;
+        if (in && n >= 0) in = score_key(sb[p]) <= thr;
+        if (in && n < 0 && drop) in = (pm[(pr.s + p) >> 5] >> ((pr.s + p) & 31)) & 1u;
+        const uint64_t bal = __ballot(in);
+        if (!bal) continue;  // wave-uniform
+        if (in) rows[wave][__popcll(bal & ((uint64_t(1) << lane) - 1))] = int32_t(base + p);
+        __threadfence_block();
+        __builtin_amdgcn_wave_barrier();
+        const int m = __popcll(bal);
+        take(lane < m ? rows[wave][lane] : 0, m);
+      }
+    }
+  }
+  if (lane < k) {
+    if (lane < nb) {
+      ids[q * k + lane] = int64_t(bid[wave][lane]);
+      scores[q * k + lane] = key_score(bkey[wave][lane]);
+    } else {
+      ids[q * k + lane] = -1;
+      scores[q * k + lane] = -INFINITY;
+    }
+  }
+}
+
 // ------------------------------------------------------------ debug exports
 __global__ void debug_kernel(const int32_t* __restrict__ l1, const Pair* __restrict__ pairs,
                              const Pair* __restrict__ pw, int32_t H,
@@ -3943,7 +4198,7 @@ void launch_wg_n(const Index& ix, const void* X, const void* Qv, const int32_t* 
 bool launch_score_wg(const Index& ix, bool bf16, const int32_t* cstart, const int32_t* wl,
                      const Pair* pairs, int32_t c, const float* Q, const __hip_bfloat16* Qb,
                      float* sbuf, int32_t rcap, int npcm, const uint32_t* pmask, int32_t mw,
-                     uint32_t* bkey, int32_t nbcap, hipStream_t st) {
+                     uint32_t* bkey, int32_t nbcap, bool split, hipStream_t st) {
   if (bf16 ? !(ix.d % 64 == 0 && ix.Xbt)
            : !(ix.d % 32 == 0 && ix.Xt && (reinterpret_cast<uintptr_t>(Q) & 15) == 0))
     return false;
@@ -3962,7 +4217,9 @@ bool launch_score_wg(const Index& ix, bool bf16, const int32_t* cstart, const in
       launch_wg_n<FMT, 8>(ix, X, QP, cstart, wl, pairs, c, sbuf, rcap, pmask, mw, bkey, \
                           nbcap, st);                                                   \
   }
-  if (bf16)
+  if (split)
+    launch_wg_n<kF32S, 8>(ix, ix.Xt, Q, cstart, wl, pairs, c, sbuf, rcap, pmask, mw, bkey, nbcap, st);
+  else if (bf16)
     LIDER_WG(kBF16W, (const void*)ix.Xbt, (const void*)Qb)
   else
     LIDER_WG(kF32W, (const void*)ix.Xt, (const void*)Q)
@@ -4294,6 +4551,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
   const int tr = 32 << ti;
   const int gm = o.grid_mult > 0 ? o.grid_mult : 4;
   const int npcm = p.npcm;
+  const bool win_split = p.split && (reinterpret_cast<uintptr_t>(Q) & 15) == 0;
   if (o.persistent == 2) {
     const int32_t nt = ix.n_tiles[ti];
     hipLaunchKernelGGL(zero_kernel, dim3(unsigned(std::min<int64_t>((nt + 255) / 256, 4096))),
@@ -4311,7 +4569,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
                      p.nbcap, st);
   else if (o.persistent || !launch_score_wg(ix, bf16, cstart, wl, pairs, c, Q, qb, sbuf, p.rcap,
                                             npcm, H > 1 ? pmask : (const uint32_t*)nullptr,
-                                            p.mw, bkey, p.nbcap, st))
+                                            p.mw, bkey, p.nbcap, win_split, st))
     launch_score<128>(ix, bf16, ti, cstart, wl, pairs, c, Q, qb, sbuf, p.rcap, o.persistent, gm,
                       ctr + 8, alist, npcm, H > 1 ? pmask : (const uint32_t*)nullptr, p.mw, bkey,
                       p.nbcap, st);
@@ -4319,7 +4577,28 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
   // the block selection's LDS key cache, sized to the candidates per query
   // (a fixed 32 KB cache held it to three workgroups per CU)
   const int32_t skc = int32_t(std::min<int64_t>(kKeyCache, int64_t(c) * p.rcap));
-  if (!bf16) {
+  if (win_split) {
+    CertArgs ca;
+    ca.xmax = ix.x_norm_max;
+    ca.qnorm = qnorm;
+    ca.cap = kSplitCap;
+    int32_t* list = reinterpret_cast<int32_t*>(rs);  // layer 1 is done
+    ca.scnt = list + nq * kSplitCap;
+    ca.sthr = reinterpret_cast<uint32_t*>(ca.scnt + nq);
+    // the split product's error (as for the layer-1 scores, both accumulations
+    // doubled to cover the accumulator's rounding mode) plus the fp32 product's
+    const double u = 0.00390625;
+    ca.ecoef = ((2.0 * (1.0 + u) * (1.0 + u) + 1.0) * u * u +
+                2.0 * dot_err_coef(3 * ix.d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u) +
+                2.0 * dot_err_coef(ix.d)) * 1.01;
+    ca.eadd = 4.0 * double(ix.d) * 7.888609052210118e-31;
+    ca.esub = 3.0 * std::sqrt(double(ix.d)) * 1.1754943508222875e-38;  // 2^-126
+    launch_wave_select<3>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k, list,
+                          int(H > 1), ca, bkey, p.nbcap);
+    hipLaunchKernelGGL(split_rescore_kernel, dim3(unsigned((nq + 3) / 4)), dim3(256), 0, st, ix.X,
+                       ix.d, Q, nq, list, ca.scnt, ca.sthr, pairs, sbuf, p.rcap, c, ix.off,
+                       H > 1 ? pmask : (const uint32_t*)nullptr, p.mw, ix.perm32, k, ids, scores);
+  } else if (!bf16) {
     if (k <= 64)
       launch_wave_select<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids,
                             scores, k, slist, int(H > 1), CertArgs(), bkey, p.nbcap);
