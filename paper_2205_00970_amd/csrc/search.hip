@@ -69,9 +69,15 @@ struct Plan {
 // three bf16 products of the split operands instead (WgPass below) and the rows
 // within the error bound of the k-th best are rescored by the fp32 product
 // itself, in the same order of operations, so ids and scores keep every bit.
-// The rescoring gathers about k rows per query (10,000 queries, k = 10: 0.1
-// GB per place), which outweighs the gain for long result lists.
+// The selection and the rescoring, which gathers about k rows per query, then
+// take some 100 us more per 10,000 queries, so it is for short result lists and
+// more than 48 expected pairs per tile (1M x 768, 10,000 queries, whole search,
+// fp32 windows against split ones: c = 8, r = 256, 31 pairs: 889 against 961
+// us; c = 4, r = 1,000, 40 pairs: 980 against 987; four arrays, c = 6, r = 128,
+// 60 pairs: 1373 against 1184, and 1399 against 1318 at k = 16; c = 8, r =
+// 1,000, 80 pairs: 1548 against 1224).
 constexpr int32_t kSplitMaxK = 16;
+constexpr double kSplitMinPairs = 48.0;
 constexpr int32_t kSplitCap = 62;  // rows listed per query; a longer list is found again
 // Largest row norm of an index that takes it: no part or product of the split
 // overflows while |q| |x| stays below kSplitMaxNorm (decided per query).
@@ -94,12 +100,13 @@ constexpr double kSplitMaxNorm = 1e37;
 // passes, about 26 with 32-row tiles and 64-pair passes, about 80 with 32-row
 // tiles and 128-pair passes.
 void rerank_shape(const Index& ix, int64_t nq, int32_t c, int32_t r, const lider_search_opts& o,
-                  int* ti, int* npcm) {
+                  int* ti, int* npcm, double* pairs) {
   const double lbar = std::max(1.0, double(ix.n) / double(ix.C));
   const double span = std::min(lbar, double(ix.H) * std::min(double(r), lbar));
   const double per_cluster = double(nq) * c / double(ix.C);
   const bool bf16 = o.precision == LIDER_BF16;
   const bool wg_ok = o.persistent == 0 && (bf16 ? (ix.d % 64 == 0 && ix.Xbt) : (ix.d % 32 == 0 && ix.Xt));
+  *pairs = per_cluster * std::min(1.0, (span + 128.0) / lbar);  // per 128-row tile
   if (wg_ok && (o.tile_rows == 0 || o.tile_rows == 128)) {
     *ti = 2;
     if (o.pass_pairs > 0) {
@@ -107,8 +114,7 @@ void rerank_shape(const Index& ix, int64_t nq, int32_t c, int32_t r, const lider
     } else {
       // 16 or 32 pairs keep three waves per SIMD; wider passes hold two
       // either way, so beyond 32 the widest (one pass for most tiles)
-      const double est = per_cluster * std::min(1.0, (span + 128.0) / lbar);
-      *npcm = 2.0 * est <= 16.0 ? 1 : 2.0 * est <= 32.0 ? 2 : 8;
+      *npcm = 2.0 * *pairs <= 16.0 ? 1 : 2.0 * *pairs <= 32.0 ? 2 : 8;
     }
     return;
   }
@@ -184,11 +190,12 @@ Plan make_plan(const Index& ix, int64_t nq, int32_t k, int32_t c, int32_t r,
   const int32_t nbroom = int64_t(c) * rcap > 2048 ? rcap / 32 + 1 : 0;
   p.nbcap = (S ? S : k) < 16 ? nbroom : 0;
   p.o_bkey = take(size_t(np) * nbroom * 4);
-  rerank_shape(ix, nq, c, r, o, &p.ti, &p.npcm);
+  double pairs = 0.0;
+  rerank_shape(ix, nq, c, r, o, &p.ti, &p.npcm, &pairs);
   const size_t nt = o.persistent == 2 ? size_t(ix.n_tiles[p.ti]) : 0;
   // its lists take the room of the layer-1 scores, which nothing reads any more
   p.split = o.precision == LIDER_F32 && o.persistent == 0 && o.tile_rows == 0 &&
-            o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && k <= kSplitMaxK &&
+            o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && pairs > kSplitMinPairs && k <= kSplitMaxK &&
             (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.x_norm_max < kSplitMaxRow;
   p.o_aflag = take(nt * 4);
   p.o_alist = take(nt * 4);
@@ -1776,24 +1783,6 @@ __device__ __forceinline__ void mfma_step(const typename F::T (&x)[RC],
   }
 }
 
-// h_q h_x + h_q l_x + l_q h_x of one k-step of split operands.
-template <int RC, int NPC, int NPCM>
-__device__ __forceinline__ void split_step(const BF16x2 (&x)[RC], const BF16x2 (&qv)[NPC],
-                                           floatx4 (&acc)[RC][NPCM]) {
-#pragma unroll
-  for (int pc = 0; pc < NPC; ++pc) {
-#pragma unroll
-    for (int rc = 0; rc < RC; ++rc)
-      acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[pc].a, x[rc].a, acc[rc][pc], 0, 0, 0);
-#pragma unroll
-    for (int rc = 0; rc < RC; ++rc)
-      acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[pc].a, x[rc].b, acc[rc][pc], 0, 0, 0);
-#pragma unroll
-    for (int rc = 0; rc < RC; ++rc)
-      acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[pc].b, x[rc].a, acc[rc][pc], 0, 0, 0);
-  }
-}
-
 // The k-loop of one pass over NPC column blocks of 16 pairs, software-
 // pipelined with two register sets (no copies of loaded data): the loads of
 // one step are in flight while the MFMAs of the previous step run.  The last
@@ -2117,30 +2106,49 @@ struct WgShared {
   int32_t n;
 };
 
-// One pass over NPC column blocks: acc[rc][pc] of the wave's 32 rows.
+// The wave's two 16-row blocks of an operand-ordered copy (uniform addresses;
+// a block past the tile's rows is the tile's first one, whose scores the wave
+// never stores).
+template <class F>
+struct WgRows {
+  const typename F::XE* at[2];
+};
+
+// One pass over NPC column blocks: acc[rc][pc] of the wave's 32 rows.  No load
+// of the k-loop stands under a condition: where the number of loads in flight
+// depends on the path, the compiler waits for all of them, and a step then
+// takes the whole latency of the loads it has just issued.  So the staging has
+// no idle threads (an odd block count has its last block staged twice), and a
+// load past the last step reads the last one again.  Passes of up to 32 pairs,
+// which the row stream bounds, have their last four steps, whose rows are all
+// on their way, as code of their own (precision form, 1M x 768: 305 -> 288
+// us); wider ones would spill.  1M x 768, 10,000 queries: c = 8, r = 256: 802 ->
+// 712 us; ten arrays, split: 995 -> 943 us; whole clusters: 533 -> 522 us (483
+// -> 468 on another card), bf16 291 -> 289 us (274 -> 260); uneven clusters, c
+// = 16, r = 512, 2,048 queries: 591 -> 536 us.
 template <int FMT, int NPC, int NPCM, int RING>
-__device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const TileRows<Feed<FMT, true>, 2>& xr,
+__device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Feed<FMT, true>>& xr,
                                         const typename Feed<FMT, true>::QE* __restrict__ Q, int32_t d,
                                         int np, int nsteps, floatx4 (&acc)[2][NPCM]) {
   typedef Feed<FMT, true> F;
   typedef typename F::T T;
   typedef typename F::QE QE;
+  typedef typename F::XE XE;
   constexpr int RC = 2;
   constexpr int NCH = (NPC * 128 + 255) / 256;  // 16-byte staging chunks per thread
+  constexpr int kHalf = 1024 / int(sizeof(XE));  // elements per 1 KB half of a chunk
+  static_assert(RING == 4, "the steps below are grouped by four");
   const int tid = threadIdx.x, lane = tid & 63;
   const int i = lane & 15, s = lane >> 4;
-  const int sub = F::SUBW * s;
   // staging chunk u = tid + 256 j: column block u / 128, pair row (u / 8) % 16,
   // 16-byte part u % 8 of the k-step
   const QE* qsrc[NCH];
   int qdst[NCH];
-  bool qon[NCH];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
     const int u = tid + 256 * j;
-    const int pc = u >> 7, r = (u >> 3) & 15, part = u & 7;
-    qon[j] = pc < NPC;
-    const int e = qon[j] ? min(16 * pc + r, np - 1) : 0;
+    const int pc = min(u >> 7, NPC - 1), r = (u >> 3) & 15, part = u & 7;
+    const int e = min(16 * pc + r, np - 1);
     qsrc[j] = Q + int64_t(sh.lq[e]) * d + part * (16 / int(sizeof(QE)));
     qdst[j] = pc * kWgQBlk + r * kWgQRow +
               (FMT == kF32S ? (part & 3) * 16 + (part >> 2) * 8 : part * 16);
@@ -2148,79 +2156,114 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const TileRows<
   floatx4 sg[2][NCH];
   auto stage_load = [&](int k, floatx4 (&dst)[NCH]) {
 #pragma unroll
-    for (int j = 0; j < NCH; ++j)
-      if (qon[j]) dst[j] = *reinterpret_cast<const floatx4*>(qsrc[j] + k * F::KS);
+    for (int j = 0; j < NCH; ++j) dst[j] = *reinterpret_cast<const floatx4*>(qsrc[j] + k * F::KS);
   };
   auto stage_store = [&](int slot, const floatx4 (&src)[NCH]) {
 #pragma unroll
-    for (int j = 0; j < NCH; ++j)
-      if (qon[j]) {
-        if constexpr (FMT == kF32S) {
-          // a 128-byte row holds the h parts of the four lane slots, then the
-          // l parts; part p of the step is half p / 4 of slot p % 4
-          bf16x4 h, l;
+    for (int j = 0; j < NCH; ++j) {
+      if constexpr (FMT == kF32S) {
+        // a 128-byte row holds the h parts of the four lane slots, then the
+        // l parts; part p of the step is half p / 4 of slot p % 4
+        bf16x4 h, l;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            h[e] = (__bf16)src[j][e];
-            l[e] = (__bf16)(src[j][e] - float(h[e]));
-          }
-          *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j]]) = h;
-          *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j] + 64]) = l;
-        } else {
-          *reinterpret_cast<floatx4*>(&sh.qs[slot][qdst[j]]) = src[j];
+        for (int e = 0; e < 4; ++e) {
+          h[e] = (__bf16)src[j][e];
+          l[e] = (__bf16)(src[j][e] - float(h[e]));
         }
+        *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j]]) = h;
+        *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j] + 64]) = l;
+      } else {
+        *reinterpret_cast<floatx4*>(&sh.qs[slot][qdst[j]]) = src[j];
       }
-  };
-  // the wave's query operands of step k from LDS slot k % 2: lane (i, s)
-  // reads pair row i of each block at the lane's two 16-byte halves
-  auto qread = [&](int slot, T (&qv)[NPC]) {
-#pragma unroll
-    for (int pc = 0; pc < NPC; ++pc) {
-      const unsigned char* b = &sh.qs[slot][pc * kWgQBlk + i * kWgQRow + 16 * s];
-      qv[pc] = T{__builtin_bit_cast(decltype(T::a), *reinterpret_cast<const floatx4*>(b)),
-                 __builtin_bit_cast(decltype(T::b), *reinterpret_cast<const floatx4*>(b + 64))};
     }
+  };
+  // the wave's query operands of column block pc from LDS slot k % 2: lane
+  // (i, s) reads pair row i of the block at the lane's two 16-byte halves
+  auto qread = [&](int slot, int pc) {
+    const unsigned char* b = &sh.qs[slot][pc * kWgQBlk + i * kWgQRow + 16 * s];
+    return T{__builtin_bit_cast(decltype(T::a), *reinterpret_cast<const floatx4*>(b)),
+             __builtin_bit_cast(decltype(T::b), *reinterpret_cast<const floatx4*>(b + 64))};
   };
   T xs[RING][RC];
   auto xload = [&](int k, T (&dst)[RC]) {
 #pragma unroll
-    for (int rc = 0; rc < RC; ++rc) dst[rc] = xr.load(rc, k * F::KS + sub, d, true);
+    for (int rc = 0; rc < RC; ++rc) {
+      const XE* p = xr.at[rc] + min(k, nsteps - 1) * (2 * kHalf) + lane * (kHalf / 64);
+      const floatx4 a = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p));
+      const floatx4 b = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p + kHalf));
+      dst[rc] = T{__builtin_bit_cast(decltype(T::a), a), __builtin_bit_cast(decltype(T::b), b)};
+    }
   };
-  // prologue: block 0 in LDS slot 0, block 1 staged, rows of steps
-  // 0 .. RING - 2 in flight
-  stage_load(0, sg[0]);
-  if (1 < nsteps) stage_load(1, sg[1]);
+  // two column blocks' operands at a time, so that wide passes keep their
+  // registers for the accumulators and the row ring
+  auto products = [&](const T (&x)[RC], int slot) {
+    T xp[RC];
 #pragma unroll
-  for (int u = 0; u + 1 < RING; ++u)
-    if (u < nsteps) xload(u, xs[u]);
-  stage_store(0, sg[0]);
-  __syncthreads();
-  // unrolled by U (a multiple of RING and of 2), so every register set index
-  // below is a compile-time constant
-  constexpr int U = RING % 2 == 0 ? RING : 2 * RING;
-  for (int k = 0; k < nsteps; k += U) {
+    for (int rc = 0; rc < RC; ++rc) {
+      if constexpr (FMT == kF32S)
+        xp[rc] = split_f32x8(__builtin_bit_cast(floatx4, x[rc].a), __builtin_bit_cast(floatx4, x[rc].b));
+      else
+        xp[rc] = x[rc];
+    }
 #pragma unroll
-    for (int J = 0; J < U; ++J) {
-      const int K = k + J;
-      if (K < nsteps) {
-        if (K + 2 < nsteps) stage_load(K + 2, sg[J & 1]);
-        if (K + RING - 1 < nsteps) xload(K + RING - 1, xs[(J + RING - 1) % RING]);
-        T qv[NPC];
-        qread(J & 1, qv);
-        if constexpr (FMT == kF32S) {
-          T xp[RC];
+    for (int p0 = 0; p0 < NPC; p0 += 2) {
+      constexpr int kG = NPC < 2 ? 1 : 2;
+      T qv[kG];
+#pragma unroll
+      for (int g = 0; g < kG; ++g)
+        if (p0 + g < NPC) qv[g] = qread(slot, p0 + g);
+#pragma unroll
+      for (int g = 0; g < kG; ++g) {
+        if (p0 + g >= NPC) continue;
+        const int pc = p0 + g;
+        if constexpr (FMT == kF32S) {  // h_q h_x + h_q l_x + l_q h_x
 #pragma unroll
           for (int rc = 0; rc < RC; ++rc)
-            xp[rc] = split_f32x8(__builtin_bit_cast(floatx4, xs[J % RING][rc].a),
-                                 __builtin_bit_cast(floatx4, xs[J % RING][rc].b));
-          split_step<RC, NPC, NPCM>(xp, qv, acc);
+            acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[g].a, xp[rc].a, acc[rc][pc], 0, 0, 0);
+#pragma unroll
+          for (int rc = 0; rc < RC; ++rc)
+            acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[g].a, xp[rc].b, acc[rc][pc], 0, 0, 0);
+#pragma unroll
+          for (int rc = 0; rc < RC; ++rc)
+            acc[rc][pc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[g].b, xp[rc].a, acc[rc][pc], 0, 0, 0);
         } else {
-          mfma_step<F, RC, NPC, NPCM>(xs[J % RING], qv, acc);
+#pragma unroll
+          for (int rc = 0; rc < RC; ++rc) F::mfma(qv[g], xp[rc], acc[rc][pc]);
         }
-        if (K + 1 < nsteps) stage_store((J + 1) & 1, sg[(J + 1) & 1]);
-        __syncthreads();
       }
     }
+  };
+  // prologue: block 0 in LDS slot 0, block 1 staged, rows of
+  // steps 0 .. RING - 2 in flight
+  stage_load(0, sg[0]);
+  stage_load(min(1, nsteps - 1), sg[1]);
+#pragma unroll
+  for (int u = 0; u + 1 < RING; ++u) xload(u, xs[u]);
+  __builtin_amdgcn_sched_barrier(0);
+  stage_store(0, sg[0]);
+  __syncthreads();
+  // step K at place J of its group; rows: the rows of step K + 3 are loaded
+  auto step = [&](int J, int K, bool rows) {
+    stage_load(min(K + 2, nsteps - 1), sg[J & 1]);
+    if (rows) xload(K + 3, xs[(J + 3) & 3]);
+    __builtin_amdgcn_sched_barrier(0);
+    products(xs[J], J & 1);
+    stage_store((J + 1) & 1, sg[(J + 1) & 1]);
+    __syncthreads();
+  };
+  constexpr bool kPeel = NPCM <= 2;
+  int k = 0;
+  for (; k + 4 < nsteps + (kPeel ? 0 : 1); k += 4) {
+#pragma unroll
+    for (int J = 0; J < 4; ++J) step(J, k + J, true);
+  }
+  if (kPeel && k + 4 == nsteps) {
+#pragma unroll
+    for (int J = 0; J < 4; ++J) step(J, k + J, J == 0);
+  } else {
+#pragma unroll
+    for (int J = 0; J < 3; ++J)
+      if (k + J < nsteps) step(J, k + J, false);
   }
 }
 
@@ -2237,7 +2280,8 @@ __global__ __launch_bounds__(256, 2) void rerank_wg_kernel(
   constexpr int PP = 16 * NPCM;
   constexpr int CAP = WgShared<FMT, NPCM>::CAP;
   __shared__ WgShared<FMT, NPCM> sh;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
   const int i = lane & 15, s = lane >> 4;
   const uint64_t below = (uint64_t(1) << lane) - 1;
   const int32_t tile = xcd_chunk_tile(ntiles, tile_chunk(128));
@@ -2248,12 +2292,15 @@ __global__ __launch_bounds__(256, 2) void rerank_wg_kernel(
   const int32_t j = td.x, row0 = td.y, rows_here = td.w;
   const int32_t plo = cstart[j], phi = cstart[j + 1];
   const int nsteps = d / F::KS;
-  TileRows<F, 2> xr;
+  WgRows<F> xr;
   {
-    constexpr int kChunk = 2 * TileRows<F, 2>::kHalf;
-    xr.base = X + (int64_t(tblk[tile]) + 2 * wave) * nsteps * kChunk + lane * (16 / int(sizeof(XE)));
-    xr.bstride = nsteps * kChunk;
-    xr.rows = max(0, min(32, rows_here - 32 * wave));
+    constexpr int kChunk = 2048 / int(sizeof(XE));  // elements per (block, k-step)
+    const int32_t nblk = (rows_here + 15) / 16;
+#pragma unroll
+    for (int rc = 0; rc < 2; ++rc) {
+      const int32_t b = 2 * wave + rc;
+      xr.at[rc] = X + (int64_t(tblk[tile]) + (b < nblk ? b : 0)) * nsteps * kChunk;
+    }
   }
   if (tid == 0) sh.n = 0;
   __syncthreads();
@@ -3940,8 +3987,7 @@ __global__ __launch_bounds__(256) void cert_wave_kernel(
 // same k-steps in the same order as the rerank's fp32 feed, so a score has the
 // bits that feed gives it.  The rows are gathered from X, 128 bytes of each per
 // step, two steps ahead; the gather bounds it (10,000 queries, k = 10, 10.3
-// rows each
-// on average: 317 MB in 80 us).
+// rows each on average: 317 MB in 80 us).
 // A list past its room, or no margin at all (scnt -1), is taken from the score
 // rows again, 64 positions at a time; without a margin every candidate counts,
 // by the membership masks where there are several arrays (drop), since its
