@@ -178,14 +178,16 @@ __device__ inline void assign_decide(const AssignOut& o, int64_t row, const Best
 // and 256 points per workgroup read the centroids from L2 n / 256 times and
 // the points C / 256 times; the matrix cores bound it (points served from L2:
 // 6% faster).  120,000 x 768 points, 1,000 centroids: 3,374 us by the fp32
-// product of 16 points per wave straight from L2, 740 us now (750 TFLOP/s of
-// bf16 products, 77% of the rate of a plain 8192^3 library product once the
-// last round of 469 workgroups on 256 CUs is allowed for).
+// product of 16 points per wave straight from L2, 740 us by this one with its
+// loads under conditions, 650 us now (850 TFLOP/s of bf16 products; a plain
+// 8192^3 library product reaches 1,145 on the same card).
 // The values of a tile are reduced over the wave's columns (registers, then
 // DPP rotations over the 16 lanes of a point) and merged into the point's
 // best in LDS, so no value is stored.  Decided here without `part`, else part
 // receives each group's best (value, centroid, second value, |x|^2).
-template <bool VEC>
+// MODE 2: rows of whole 32-dimension steps at 16-byte addresses, 1: d a
+// multiple of 4 there, 0: any.
+template <int MODE>
 __global__ __launch_bounds__(512, 2) void assign_kernel(
     const float* __restrict__ X, int64_t n, int32_t d, const bf16x8* __restrict__ cs,
     const float* __restrict__ cnorm, int32_t ntiles, AssignOut o, float4* __restrict__ part) {
@@ -214,13 +216,19 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int32_t at = xo[a] + 4 * h, kd = 32 * kc + 8 * s + 4 * h;
-        if (VEC) {  // d % 4 == 0: a whole float4 lies inside the point or past it
-          xa[a][h] = kd < d ? *reinterpret_cast<const float4*>(xk + at) : float4{0.f, 0.f, 0.f, 0.f};
+        if (MODE == 2) {  // d % 32 == 0
+          xa[a][h] = *reinterpret_cast<const float4*>(xk + at);
+        } else if (MODE == 1) {  // d % 4 == 0: a whole float4 lies inside the point or past it
+          const float4 v = *reinterpret_cast<const float4*>(xk + at - max(kd - (d - 4), 0));
+          xa[a][h] = kd < d ? v : float4{0.f, 0.f, 0.f, 0.f};
         } else {
-          xa[a][h].x = kd < d ? xk[at] : 0.f;
-          xa[a][h].y = kd + 1 < d ? xk[at + 1] : 0.f;
-          xa[a][h].z = kd + 2 < d ? xk[at + 2] : 0.f;
-          xa[a][h].w = kd + 3 < d ? xk[at + 3] : 0.f;
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = xk[at + e - max(kd + e - (d - 1), 0)];
+          xa[a][h].x = kd < d ? v[0] : 0.f;
+          xa[a][h].y = kd + 1 < d ? v[1] : 0.f;
+          xa[a][h].z = kd + 2 < d ? v[2] : 0.f;
+          xa[a][h].w = kd + 3 < d ? v[3] : 0.f;
         }
       }
   };
@@ -261,11 +269,12 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
         }
       }
       const bool last = kc + 1 == nk;
-      const bool more = !last || t + 1 < t1;
-      if (more) {  // the next step's operands, in flight during this one
-        load_cents(last ? t + 1 : t, last ? 0 : kc + 1);
-        load_points(last ? 0 : kc + 1);
-      }
+      // the next step's operands, in flight during this one (after the last
+      // step some again: a load under a condition would make the compiler wait
+      // for all loads at the next use)
+      load_cents(last ? min(t + 1, t1 - 1) : t, last ? 0 : kc + 1);
+      load_points(last ? 0 : kc + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 8; ++b) {
         const bf16x8 bh = sb[slot][(8 * wc + b) * 128 + lane];
@@ -280,7 +289,7 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
         for (int a = 0; a < 4; ++a)
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[a], bh, acc[a][b], 0, 0, 0);
       }
-      if (more) store_cents(slot ^ 1);
+      store_cents(slot ^ 1);
       __syncthreads();
       slot ^= 1;
     }
@@ -450,14 +459,14 @@ static void launch_product(const float* X, int64_t n, int32_t d, const float* ce
                      reinterpret_cast<int32_t*>(a.maxbits), int64_t(2));
   hipLaunchKernelGGL(cent_split_kernel, dim3(unsigned(ntiles) * (kAsgTile / 4)), dim3(256), 0, st,
                      cent, C, d, a.cs, a.cnorm, a.maxbits);
-  const bool vec = (d % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
+  const bool al = (reinterpret_cast<uintptr_t>(X) & 15) == 0;
   const dim3 grid(unsigned((n + kAsgTile - 1) / kAsgTile), unsigned(G));
-  if (vec)
-    hipLaunchKernelGGL(assign_kernel<true>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles,
-                       o, part);
+  if (al && d % 32 == 0)
+    hipLaunchKernelGGL(assign_kernel<2>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles, o, part);
+  else if (al && d % 4 == 0)
+    hipLaunchKernelGGL(assign_kernel<1>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles, o, part);
   else
-    hipLaunchKernelGGL(assign_kernel<false>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles,
-                       o, part);
+    hipLaunchKernelGGL(assign_kernel<0>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles, o, part);
 }
 
 // The product alone: the groups' bests in part ([G x n]); returns G, and in
