@@ -12,6 +12,8 @@
 // within that band of a bucket edge (about 1e-10 relative at d = 768, so almost
 // never) is listed and decided by hash_decide_wave in the same kernel, down to
 // the sequential FP64 dot product in dimension order where needed.
+#include <type_traits>
+
 #include "lider_internal.hpp"
 
 namespace lider {
@@ -74,31 +76,35 @@ __device__ void hash_decide_wave(const float* __restrict__ xr, const float* __re
 // wave owns row / hash (l % 16) and the dimension slot s = l / 16: per step it
 // loads 4 consecutive dims [k0 + 4s, k0 + 4s + 4) of its row and of its hash
 // vectors and feeds them to 4 MFMAs (the k index of an MFMA only needs to map
-// to the same dimension on both operands).  The next step's operands are
-// loaded before the current step's MFMAs are issued.  Partial projections are
-// added in wave order through LDS; the projections inside the band are listed
+// to the same dimension on both operands).  FULL (d a multiple of 16, 16-byte
+// aligned rows): the operands of the next three steps are in flight while a
+// step's MFMAs run, with no load under a condition (which would make the
+// compiler wait for all of them each step); else those of the next one.  The
+// kernel is bound by the latency of these chains (10,000 queries x 768: 16
+// hashes 22 -> 20 us, 20 signs 28 -> 22 us, 160 hashes 87 -> 76 us against one
+// step ahead with conditional loads).  Partial projections are added in wave order through LDS; the projections inside the band are listed
 // in LDS and decided by hash_decide_wave after the block's other outputs.
 // xb (nullable): the rows rounded to bf16 (round to nearest even), written by
 // the blocks of grid row 0 from the values they load anyway.  z: counters
 // the caller's later kernels need cleared, cleared by the blocks of grid row
 // 0 (status must not be among them unless clamp is set: this kernel only
 // writes status when it is not).
-template <bool VEC>
-__global__ __launch_bounds__(256) void hash_kernel(
+template <bool VEC, bool FULL, int NW>
+__global__ __launch_bounds__(64 * NW) void hash_kernel(
     const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ A,
     const float* __restrict__ bvec, const float* __restrict__ anorm, int32_t nh, double w,
     int32_t* __restrict__ out, int32_t* __restrict__ status, int clamp,
     float* __restrict__ rownorm, int kind, __hip_bfloat16* __restrict__ xb, HashZero z) {
   if (blockIdx.y == 0 && z.nz > 0) {
-    for (int32_t t = int32_t(blockIdx.x) * 256 + threadIdx.x; t < z.nz;
-         t += int32_t(gridDim.x) * 256) {
+    for (int32_t t = int32_t(blockIdx.x) * (64 * NW) + threadIdx.x; t < z.nz;
+         t += int32_t(gridDim.x) * (64 * NW)) {
       if (z.a && t < z.na) z.a[t] = 0;
       if (z.b && t < z.nb) z.b[t] = 0;
       if (z.c && t < z.nb) z.c[t] = 0;
     }
   }
-  __shared__ double part[4][32][16];  // [wave][hash][row]
-  __shared__ float pss[4][16];
+  __shared__ double part[NW][32][16];  // [wave][hash][row]
+  __shared__ float pss[NW][16];
   __shared__ int32_t qlist[16 * 32];  // (row, hash) entries inside the band
   __shared__ int32_t qn;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -118,7 +124,7 @@ __global__ __launch_bounds__(256) void hash_kernel(
   doublex4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
   float ss = 0.f;
   const int nk = (d + 15) / 16;
-  const int k0s = wave * nk / 4, k1s = (wave + 1) * nk / 4;
+  const int k0s = wave * nk / NW, k1s = (wave + 1) * nk / NW;
   float xe[4], ae[4], be[4] = {0.f, 0.f, 0.f, 0.f};
   auto load = [&](int ks, float* xo, float* ao, float* bo) {
     const int kk = ks * 16 + 4 * s;
@@ -141,34 +147,93 @@ __global__ __launch_bounds__(256) void hash_kernel(
       }
     }
   };
-  if (k0s < k1s) load(k0s, xe, ae, be);
-  for (int ks = k0s; ks < k1s; ++ks) {
-    float xn[4], an[4], bn[4] = {0.f, 0.f, 0.f, 0.f};
-    load(ks + 1 < k1s ? ks + 1 : ks, xn, an, bn);
-    if (xbr) {
-      const int kk = ks * 16 + 4 * s;
-      if (VEC && kk + 3 < d) {
-        __hip_bfloat16 v4[4];
+  // one step's products (xo: this lane's four values of its row)
+  auto feed = [&](const float (&xo)[4], const float (&ao)[4], const float (&bo)[4], bool second) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v4[e] = __float2bfloat16(xe[e]);
-        *reinterpret_cast<uint2*>(xbr + kk) = *reinterpret_cast<const uint2*>(v4);
-      } else {
+    for (int e = 0; e < 4; ++e) {
+      ss += xo[e] * xo[e];
+      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(double(xo[e]), double(ao[e]), acc0, 0, 0, 0);
+      if (second) acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(double(xo[e]), double(bo[e]), acc1, 0, 0, 0);
+    }
+  };
+  if constexpr (FULL) {
+    // a row past the last writes its bf16 values where row n - 1 does
+    __hip_bfloat16* xw = xb ? xb + myrow * d : nullptr;
+    auto run = [&](auto second, auto copy) {
+      constexpr bool SECOND = decltype(second)::value, COPY = decltype(copy)::value;
+      constexpr int RING = 4;
+      float4 xr4[RING], ar4[RING], br4[RING];
+      auto fetch = [&](int ks, int u) {
+        const int kk = min(ks, k1s - 1) * 16 + 4 * s;
+        xr4[u] = *reinterpret_cast<const float4*>(xr + kk);
+        ar4[u] = *reinterpret_cast<const float4*>(a0 + kk);
+        if (SECOND) br4[u] = *reinterpret_cast<const float4*>(a1 + kk);
+      };
+      auto step = [&](int ks, int u) {
+        const float xo[4] = {xr4[u].x, xr4[u].y, xr4[u].z, xr4[u].w};
+        const float ao[4] = {ar4[u].x, ar4[u].y, ar4[u].z, ar4[u].w};
+        float bo[4] = {0.f, 0.f, 0.f, 0.f};
+        if (SECOND) {
+          bo[0] = br4[u].x;
+          bo[1] = br4[u].y;
+          bo[2] = br4[u].z;
+          bo[3] = br4[u].w;
+        }
+        if (COPY) {
+          __hip_bfloat16 v4[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (kk + e < d) xbr[kk + e] = __float2bfloat16(xe[e]);
+          for (int e = 0; e < 4; ++e) v4[e] = __float2bfloat16(xo[e]);
+          *reinterpret_cast<uint2*>(xw + ks * 16 + 4 * s) = *reinterpret_cast<const uint2*>(v4);
+        }
+        feed(xo, ao, bo, SECOND);
+      };
+#pragma unroll
+      for (int u = 0; u + 1 < RING; ++u) fetch(k0s + u, u);
+      int ks = k0s;
+      for (; ks + RING <= k1s; ks += RING) {
+#pragma unroll
+        for (int u = 0; u < RING; ++u) {
+          fetch(ks + u + RING - 1, (u + RING - 1) % RING);
+          __builtin_amdgcn_sched_barrier(0);
+          step(ks + u, u);
+        }
       }
-    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      ss += xe[e] * xe[e];
-      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(double(xe[e]), double(ae[e]), acc0, 0, 0, 0);
-      if (two) acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(double(xe[e]), double(be[e]), acc1, 0, 0, 0);
+      for (int u = 0; u + 1 < RING; ++u)
+        if (ks + u < k1s) step(ks + u, u);
+    };
+    if (k0s < k1s) {
+      const bool copy = xb && blockIdx.y == 0;
+      if (two && copy) run(std::true_type(), std::true_type());
+      else if (two) run(std::true_type(), std::false_type());
+      else if (copy) run(std::false_type(), std::true_type());
+      else run(std::false_type(), std::false_type());
     }
+  } else {
+    if (k0s < k1s) load(k0s, xe, ae, be);
+    for (int ks = k0s; ks < k1s; ++ks) {
+      float xn[4], an[4], bn[4] = {0.f, 0.f, 0.f, 0.f};
+      load(ks + 1 < k1s ? ks + 1 : ks, xn, an, bn);
+      if (xbr) {
+        const int kk = ks * 16 + 4 * s;
+        if (VEC && kk + 3 < d) {
+          __hip_bfloat16 v4[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      xe[e] = xn[e];
-      ae[e] = an[e];
-      be[e] = bn[e];
+          for (int e = 0; e < 4; ++e) v4[e] = __float2bfloat16(xe[e]);
+          *reinterpret_cast<uint2*>(xbr + kk) = *reinterpret_cast<const uint2*>(v4);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (kk + e < d) xbr[kk + e] = __float2bfloat16(xe[e]);
+        }
+      }
+      feed(xe, ae, be, two);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        xe[e] = xn[e];
+        ae[e] = an[e];
+        be[e] = bn[e];
+      }
     }
   }
   // |x|^2 of row i over this wave's dims: sum the four dimension slots
@@ -185,12 +250,17 @@ __global__ __launch_bounds__(256) void hash_kernel(
   __syncthreads();
   const double u = 1.1102230246251565e-16;  // 2^-53
   const double gam = double(d + 2) * 5.9604644775390625e-08;
-  for (int o = threadIdx.x; o < 16 * nhc; o += 256) {
+  for (int o = threadIdx.x; o < 16 * nhc; o += 64 * NW) {
     const int ri = o / nhc, hl = o - ri * nhc, hash = hb + hl;
     const int64_t row = row0 + ri;
     if (row >= n) continue;
-    const float ssr = ((pss[0][ri] + pss[1][ri]) + pss[2][ri]) + pss[3][ri];
-    const double sv = ((part[0][hl][ri] + part[1][hl][ri]) + part[2][hl][ri]) + part[3][hl][ri];
+    float ssr = pss[0][ri];
+    double sv = part[0][hl][ri];
+#pragma unroll
+    for (int v = 1; v < NW; ++v) {
+      ssr += pss[v][ri];
+      sv += part[v][hl][ri];
+    }
     const double xn = sqrt(double(ssr) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07);
     if (rownorm && hash == 0) rownorm[row] = float(xn * (1.0 + 9.5367431640625e-07));
     const int64_t oi = row * nh + hash;
@@ -225,7 +295,7 @@ __global__ __launch_bounds__(256) void hash_kernel(
   }
   __syncthreads();
   const int nq = qn;
-  for (int e = wave; e < nq; e += 4) {
+  for (int e = wave; e < nq; e += NW) {
     const int o = qlist[e];
     const int ri = o / nhc, hash = hb + (o - ri * nhc);
     const int64_t row = row0 + ri;
@@ -270,12 +340,21 @@ int run_hash_ex(const float* X, int64_t n, int32_t d, const float* A, const floa
                    ((reinterpret_cast<uintptr_t>(A) & 15) == 0) &&
                    ((reinterpret_cast<uintptr_t>(xb) & 7) == 0);
   const dim3 grid(unsigned((n + 15) / 16), unsigned((nh + 31) / 32));
-  if (vec)
-    hipLaunchKernelGGL(hash_kernel<true>, grid, dim3(256), 0, st, X, n, d, A, b, anorm, nh, w,
-                       out, status, clamp, rownorm, kind, xb, z);
+  // few workgroups: sixteen waves each, a quarter of the chain per wave (one
+  // query, 768 dimensions, 16 hashes: 13 -> 7 us)
+  const bool few = int64_t(grid.x) * grid.y <= 256 && d >= 256;
+  if (vec && d % 16 == 0 && few)
+    hipLaunchKernelGGL((hash_kernel<true, true, 16>), grid, dim3(1024), 0, st, X, n, d, A, b, anorm,
+                       nh, w, out, status, clamp, rownorm, kind, xb, z);
+  else if (vec && d % 16 == 0)
+    hipLaunchKernelGGL((hash_kernel<true, true, 4>), grid, dim3(256), 0, st, X, n, d, A, b, anorm,
+                       nh, w, out, status, clamp, rownorm, kind, xb, z);
+  else if (vec)
+    hipLaunchKernelGGL((hash_kernel<true, false, 4>), grid, dim3(256), 0, st, X, n, d, A, b, anorm,
+                       nh, w, out, status, clamp, rownorm, kind, xb, z);
   else
-    hipLaunchKernelGGL(hash_kernel<false>, grid, dim3(256), 0, st, X, n, d, A, b, anorm, nh, w,
-                       out, status, clamp, rownorm, kind, xb, z);
+    hipLaunchKernelGGL((hash_kernel<false, false, 4>), grid, dim3(256), 0, st, X, n, d, A, b, anorm,
+                       nh, w, out, status, clamp, rownorm, kind, xb, z);
   return check_hip(hipGetLastError(), "hash kernel");
 }
 
