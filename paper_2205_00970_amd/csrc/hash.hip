@@ -82,8 +82,9 @@ __device__ void hash_decide_wave(const float* __restrict__ xr, const float* __re
 // compiler wait for all of them each step); else those of the next one.  The
 // kernel is bound by the latency of these chains (10,000 queries x 768: 16
 // hashes 22 -> 20 us, 20 signs 28 -> 22 us, 160 hashes 87 -> 76 us against one
-// step ahead with conditional loads).  Partial projections are added in wave order through LDS; the projections inside the band are listed
-// in LDS and decided by hash_decide_wave after the block's other outputs.
+// step ahead with conditional loads).  Partial projections are added in wave
+// order through LDS; the projections inside the band are listed in LDS and
+// decided by hash_decide_wave after the block's other outputs.
 // xb (nullable): the rows rounded to bf16 (round to nearest even), written by
 // the blocks of grid row 0 from the values they load anyway.  z: counters
 // the caller's later kernels need cleared, cleared by the blocks of grid row

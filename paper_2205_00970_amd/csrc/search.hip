@@ -52,6 +52,7 @@ struct Plan {
   int ti, npcm;  // rerank tile table and 16-pair blocks per pass
   bool cert;     // precision form with the certified shortlist
   bool split;    // windows scored by the split product, short lists rescored
+  bool small;    // windows scored pair by pair, without a work list
   size_t o_scnt;
   // l1_dense_rows: layer-1 scores of every centroid (dense product), else of
   // the r1-windows (window kernel).  Several hashkey arrays: lcap = layer-1
@@ -83,6 +84,13 @@ constexpr int32_t kSplitCap = 62;  // rows listed per query; a longer list is fo
 // overflows while |q| |x| stays below kSplitMaxNorm (decided per query).
 constexpr float kSplitMaxRow = 1e15f;
 constexpr double kSplitMaxNorm = 1e37;
+
+// Batches up to this many queries take the small batches' layer-1 product
+// (1,000 centroids x 768, product and routing together, 256 queries: 18.6 us
+// against 24.8 with the large tiles, 32 against 49 split; the small tiles'
+// time grows by 0.025 and 0.045 us a query, the large ones' not up to some 600)
+// and may take their routing and window scores.
+constexpr int64_t kSmallBatch = 512;
 
 // Rerank shape: rows per tile (index into the tile tables: 32, 64, 128) and
 // 16-pair column blocks per MFMA pass.  A tile overlapped by P pairs is
@@ -197,6 +205,18 @@ Plan make_plan(const Index& ix, int64_t nq, int32_t k, int32_t c, int32_t r,
   p.split = o.precision == LIDER_F32 && o.persistent == 0 && o.tile_rows == 0 &&
             o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && pairs > kSplitMinPairs && k <= kSplitMaxK &&
             (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.x_norm_max < kSplitMaxRow;
+  // pair by pair: few queries whose windows hardly share a cluster (a quarter
+  // as many pairs as clusters: 12% of them do), or few enough rows for the
+  // caches to serve the shared ones
+  const double wrows = double(nq) * c * double(std::min<int64_t>(r, ix.max_cluster) + 16);
+  const bool tiled = o.precision == LIDER_BF16 ? ix.d % 64 == 0 && ix.Xbt : ix.d % 32 == 0 && ix.Xt;
+  p.small = H == 1 && nq <= kSmallBatch && o.persistent == 0 && o.tile_rows == 0 && o.pass_pairs == 0 &&
+            tiled && np <= 32768 &&
+            (np * 4 <= ix.C || wrows * ix.d * (o.precision == LIDER_BF16 ? 2.0 : 4.0) <= double(64 << 20));
+  if (p.small) {  // no block keys either: their readers are for large batches
+    p.split = false;
+    p.nbcap = 0;
+  }
   p.o_aflag = take(nt * 4);
   p.o_alist = take(nt * 4);
   p.o_kq = take(o.expand_bits > 0 ? size_t(nq) * std::max<int32_t>(c, 1) * H * 8 : 0);
@@ -628,6 +648,9 @@ __global__ __launch_bounds__(256) void l1_union_kernel(
   }
 }
 
+// A wave-uniform value, moved to a scalar register.
+__device__ inline int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Minimum over the 64 lanes of a wave (all lanes active), on DPP: inclusive
 // prefix minima within each row of 16 (row_shr 1, 2, 4, 8; a lane whose
 // source lies before its row keeps its own value), then row_bcast:15 and
@@ -751,22 +774,46 @@ __device__ __attribute__((noinline)) void route_fp64_wave(const float* __restric
 // R: approximate scores kept in registers per lane (len1 <= 64 R), else
 // re-read.
 
+struct RouteArgs {
+  const float* Q;
+  int32_t d;
+  int64_t nq;
+  const float* cent_l1;
+  const int32_t* l1_order32;
+  const int32_t* l1;  // query q's window: l1[wst q + 1], l1[wst q + 2]
+  int32_t wst;
+  const int32_t* lst;
+  int32_t lcap;
+  const float* rs;
+  int32_t rstride;
+  int dense;
+  const float* qnorm;
+  const float* cent_norm_max;
+  double ecoef, eadd, esub;
+  int32_t c;
+  int32_t *rcand, *rcnt;
+  double* rs64;
+  int32_t* routed;
+  int whole;
+};
+
+// The filter of query q by one wave; cpos: kCandCap entries of LDS.
 template <int R>
-__global__ __launch_bounds__(256) void route_filter_kernel(
-    int32_t d, int64_t nq, const int32_t* __restrict__ l1_order32,
-    const int32_t* __restrict__ l1, int32_t wst, const int32_t* __restrict__ lst, int32_t lcap,
-    const float* __restrict__ rs, int32_t rstride, int dense, const float* __restrict__ qnorm,
-    const float* __restrict__ cent_norm_max, double ecoef, double eadd, double esub, int32_t c,
-    int32_t* __restrict__ rcand, int32_t* __restrict__ rcnt, int32_t* __restrict__ routed,
-    int whole) {
-  __shared__ int32_t cpos[4][kCandCap];
+__device__ __forceinline__ void route_filter_query(const RouteArgs& a, int64_t q, int32_t* cpos) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));  // uniform
   const uint64_t below = (uint64_t(1) << lane) - 1;
-  // one query per wave, no loop (per-query index arithmetic is not hoisted
-  // into registers held across queries)
-  const int64_t q = int64_t(blockIdx.x) * 4 + wave;
-  if (q >= nq) return;
+  const int32_t* __restrict__ l1_order32 = a.l1_order32;
+  const int32_t* __restrict__ l1 = a.l1;
+  const int32_t* __restrict__ lst = a.lst;
+  const float* __restrict__ rs = a.rs;
+  const float* __restrict__ qnorm = a.qnorm;
+  const float* __restrict__ cent_norm_max = a.cent_norm_max;
+  int32_t* __restrict__ rcand = a.rcand;
+  int32_t* __restrict__ rcnt = a.rcnt;
+  int32_t* __restrict__ routed = a.routed;
+  const int32_t wst = a.wst, lcap = a.lcap, rstride = a.rstride, c = a.c;
+  const int dense = a.dense, whole = a.whole;
+  const double ecoef = a.ecoef, eadd = a.eadd, esub = a.esub;
   const float* rsq = rs + q * rstride;
   // whole: every query's window is the whole dense row [0, rstride), so the
   // score loads are issued before the window is read
@@ -839,23 +886,33 @@ __global__ __launch_bounds__(256) void route_filter_kernel(
     const bool in = p < len1 && double(sv) >= thr;
     const uint64_t m = __ballot(in);
     const int slot = n + __popcll(m & below);
-    if (in && slot < kCandCap) cpos[wave][slot] = p;
+    if (in && slot < kCandCap) cpos[slot] = p;
     n += __popcll(m);
   }
   __threadfence_block();
   __builtin_amdgcn_wave_barrier();
   if (n == c) {  // the candidates are the routed set (listed in window order)
-    for (int t = lane; t < c; t += 64) routed[q * c + t] = l1_order32[pos_of(cpos[wave][t])];
+    for (int t = lane; t < c; t += 64) routed[q * c + t] = l1_order32[pos_of(cpos[t])];
     if (lane == 0) rcnt[q] = 0;
   } else {
     int32_t* cq = rcand + q * kCandCap;
     const int nl = min(n, kCandCap);
-    for (int t = lane; t < nl; t += 64) cq[t] = pos_of(cpos[wave][t]);
+    for (int t = lane; t < nl; t += 64) cq[t] = pos_of(cpos[t]);
     // fewer than c candidates only with non-finite scores (a query holding a
     // NaN or an infinity): the whole window is then decided sequentially,
     // which routes c valid clusters (or -1) whatever the scores
     if (lane == 0) rcnt[q] = (n > kCandCap || n < c) ? kCandCap + 1 : n;
   }
+}
+
+template <int R>
+__global__ __launch_bounds__(256) void route_filter_kernel(RouteArgs a) {
+  __shared__ int32_t cpos[4][kCandCap];
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));  // uniform
+  // one query per wave, no loop (per-query index arithmetic is not hoisted
+  // into registers held across queries)
+  const int64_t q = int64_t(blockIdx.x) * 4 + wave;
+  if (q < a.nq) route_filter_query<R>(a, q, cpos[wave]);
 }
 
 // route_rescore_kernel, one wave per query with rcnt[q] > 0.  Each
@@ -873,41 +930,49 @@ constexpr int kRescoreSteps = 16;  // float4 steps per lane of the fast path: d 
 // once instead of waiting for three busy neighbours
 constexpr int kRescoreWaves = 1;
 
-__global__ __launch_bounds__(64 * kRescoreWaves) void route_rescore_kernel(
-    const float* __restrict__ Q, int32_t d, int64_t nq, const float* __restrict__ cent_l1,
-    const int32_t* __restrict__ l1_order32, const int32_t* __restrict__ l1, int32_t wst,
-    const int32_t* __restrict__ lst, int32_t lcap, int32_t c, const int32_t* __restrict__ rcand,
-    const int32_t* __restrict__ rcnt, double* __restrict__ rs64, int32_t* __restrict__ routed) {
-  __shared__ float sq[kRescoreWaves][64 * kRescoreSteps] __attribute__((aligned(16)));
-  __shared__ double clo[kRescoreWaves][kCandCap], chi[kRescoreWaves][kCandCap];
-  __shared__ int32_t cid[kRescoreWaves][kCandCap];
-  __shared__ uint8_t cpick[kRescoreWaves][kCandCap];
-  __shared__ int32_t chosen[kRescoreWaves][LIDER_MAX_C];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+struct RescoreShared {
+  __attribute__((aligned(16))) float sq[64 * kRescoreSteps];
+  double clo[kCandCap], chi[kCandCap];
+  int32_t cid[kCandCap];
+  uint8_t cpick[kCandCap];
+  int32_t chosen[LIDER_MAX_C];
+};
+
+// The decision of query q from its n > 0 candidates (kCandCap + 1: the whole
+// window) by one wave.
+__device__ __forceinline__ void route_rescore_query(const RouteArgs& a, int64_t q, int32_t n,
+                                                    RescoreShared& sh) {
+  const int lane = threadIdx.x & 63;
   const int g = lane >> 4, j = lane & 15;
   const double u = 1.1102230246251565e-16;  // 2^-53
+  const float* __restrict__ Q = a.Q;
+  const float* __restrict__ cent_l1 = a.cent_l1;
+  const int32_t* __restrict__ l1_order32 = a.l1_order32;
+  const int32_t* __restrict__ l1 = a.l1;
+  const int32_t* __restrict__ lst = a.lst;
+  const int32_t* rcand = a.rcand;
+  double* rs64 = a.rs64;
+  int32_t* __restrict__ routed = a.routed;
+  const int32_t d = a.d, wst = a.wst, lcap = a.lcap, c = a.c;
   const bool fast = (d & 3) == 0 && d <= 64 * kRescoreSteps &&
                     ((reinterpret_cast<uintptr_t>(Q) | reinterpret_cast<uintptr_t>(cent_l1)) & 15) == 0;
-  for (int64_t q = int64_t(blockIdx.x) * kRescoreWaves + wave; q < nq;
-       q += int64_t(gridDim.x) * kRescoreWaves) {
-    const int32_t n = rcnt[q];
-    if (n == 0) continue;  // decided by the filter (wave-uniform)
+  {
     const float* qv = Q + q * d;
     const int32_t* cq = rcand + q * kCandCap;
     if (n > kCandCap) {
       const int32_t s1 = l1[wst * q + 1], len1 = l1[wst * q + 2];
       route_fp64_wave(qv, d, cent_l1, l1_order32, s1, len1, lst ? lst + q * lcap : nullptr, c,
-                      rs64 + q * lcap, chosen[wave]);
-      for (int t = lane; t < c; t += 64) routed[q * c + t] = chosen[wave][t];
+                      rs64 + q * lcap, sh.chosen);
+      for (int t = lane; t < c; t += 64) routed[q * c + t] = sh.chosen[t];
       __threadfence_block();
       __builtin_amdgcn_wave_barrier();
-      continue;
+      return;
     }
     // lane j of group g: dims 4 j + 64 i (fast path, query staged in LDS) or
     // j + 16 i
     if (fast) {  // zero beyond d: those products must be exact zeros
       for (int k = 4 * lane; k < 64 * kRescoreSteps; k += 256)
-        *reinterpret_cast<float4*>(&sq[wave][k]) =
+        *reinterpret_cast<float4*>(&sh.sq[k]) =
             k < d ? *reinterpret_cast<const float4*>(qv + k) : float4{0.f, 0.f, 0.f, 0.f};
       __threadfence_block();
       __builtin_amdgcn_wave_barrier();
@@ -929,7 +994,7 @@ __global__ __launch_bounds__(64 * kRescoreWaves) void route_rescore_kernel(
         }
 #pragma unroll
         for (int i = 0; i < kRescoreSteps; ++i) {
-          const float4 x = *reinterpret_cast<const float4*>(&sq[wave][4 * j + 64 * i]);
+          const float4 x = *reinterpret_cast<const float4*>(&sh.sq[4 * j + 64 * i]);
           const double p0 = double(x.x) * double(m[i].x), p1 = double(x.y) * double(m[i].y);
           const double p2 = double(x.z) * double(m[i].z), p3 = double(x.w) * double(m[i].w);
           ps += p0;
@@ -954,10 +1019,10 @@ __global__ __launch_bounds__(64 * kRescoreWaves) void route_rescore_kernel(
       }
       if (j == 0 && t < n) {
         const double band = 8.0 * double(d) * u * pa;
-        clo[wave][t] = ps - band;
-        chi[wave][t] = ps + band;
-        cid[wave][t] = l1_order32[cq[t]];
-        cpick[wave][t] = 0;
+        sh.clo[t] = ps - band;
+        sh.chi[t] = ps + band;
+        sh.cid[t] = l1_order32[cq[t]];
+        sh.cpick[t] = 0;
       }
     }
     __threadfence_block();
@@ -966,43 +1031,52 @@ __global__ __launch_bounds__(64 * kRescoreWaves) void route_rescore_kernel(
     // a candidate's place is the number of candidates ahead of it in that order
     // (a NaN midpoint counts as -inf, so the order stays total)
     const auto mid = [&](int t) {
-      const double v = 0.5 * (clo[wave][t] + chi[wave][t]);
+      const double v = 0.5 * (sh.clo[t] + sh.chi[t]);
       return v == v ? v : -INFINITY;
     };
     for (int t = lane; t < n; t += 64) {
       const double v = mid(t);
-      const int32_t id = cid[wave][t];
+      const int32_t id = sh.cid[t];
       int32_t place = 0;
 #pragma unroll 4
       for (int s = 0; s < n; ++s) {
         const double vs = mid(s);
-        place += (vs > v || (vs == v && cid[wave][s] < id)) ? 1 : 0;
+        place += (vs > v || (vs == v && sh.cid[s] < id)) ? 1 : 0;
       }
-      cpick[wave][t] = place < c;
-      if (place < c) chosen[wave][place] = id;
+      sh.cpick[t] = place < c;
+      if (place < c) sh.chosen[place] = id;
     }
     __threadfence_block();
     __builtin_amdgcn_wave_barrier();
     // decided when every chosen band lies above every other band
     double lo = INFINITY, hi = -INFINITY;
     for (int t = lane; t < n; t += 64) {
-      if (cpick[wave][t])
-        lo = fmin(lo, clo[wave][t]);
+      if (sh.cpick[t])
+        lo = fmin(lo, sh.clo[t]);
       else
-        hi = fmax(hi, chi[wave][t]);
+        hi = fmax(hi, sh.chi[t]);
     }
     for (int o = 32; o > 0; o >>= 1) {
       lo = fmin(lo, __shfl_xor(lo, o));
       hi = fmax(hi, __shfl_xor(hi, o));
     }
     if (!(lo > hi))
-      route_fp64_wave(qv, d, cent_l1, l1_order32, 0, n, cq, c, rs64 + q * lcap, chosen[wave]);
-    for (int t = lane; t < c; t += 64) routed[q * c + t] = chosen[wave][t];
+      route_fp64_wave(qv, d, cent_l1, l1_order32, 0, n, cq, c, rs64 + q * lcap, sh.chosen);
+    for (int t = lane; t < c; t += 64) routed[q * c + t] = sh.chosen[t];
     __threadfence_block();
     __builtin_amdgcn_wave_barrier();
   }
 }
 
+__global__ __launch_bounds__(64 * kRescoreWaves) void route_rescore_kernel(RouteArgs a) {
+  __shared__ RescoreShared sh[kRescoreWaves];
+  const int wave = threadIdx.x >> 6;
+  for (int64_t q = int64_t(blockIdx.x) * kRescoreWaves + wave; q < a.nq;
+       q += int64_t(gridDim.x) * kRescoreWaves) {
+    const int32_t n = a.rcnt[q];
+    if (n > 0) route_rescore_query(a, q, n, sh[wave]);  // 0: decided by the filter (wave-uniform)
+  }
+}
 
 // ------------------------------------------------------------ layer 2 pairs
 // The per-cluster pair counts and scatter cursors are kept in kCntCopies
@@ -1063,6 +1137,46 @@ __global__ void pairs_kernel(const Model* __restrict__ models, const double* __r
   if (h == 0) {
     if (j >= 0 && ph.len > 0) atomicAdd(&ccount[cnt_copy(t) * C + j], 1);
     pairs[t] = ph;
+  }
+}
+
+// Small batches: the filter, the decision where it needs one, and the windows
+// of the query's pairs (one array), one wave per query in one launch.  With
+// few queries each of these is a launch's latency and little else (one query,
+// 1,000 centroids: 4 + 1.3 + 3.1 us as three launches and 4.8 for the work
+// list, 6.4 us as one without it).  The
+// rescoring's registers allow three waves per SIMD, so large batches keep the
+// separate kernels.
+template <int R>
+__global__ __launch_bounds__(64) void route_pairs_kernel(RouteArgs a, const Model* __restrict__ models,
+                                                         const double* __restrict__ leaves,
+                                                         const int32_t* __restrict__ qdig, int32_t m,
+                                                         int32_t r, Pair* __restrict__ pairs,
+                                                         uint64_t* __restrict__ kq) {
+  __shared__ int32_t cpos[kCandCap];
+  __shared__ RescoreShared sh;
+  const int lane = threadIdx.x;
+  const int64_t q = blockIdx.x;
+  route_filter_query<R>(a, q, cpos);
+  __threadfence_block();
+  __builtin_amdgcn_wave_barrier();
+  const int32_t n = uni(a.rcnt[q]);
+  if (n > 0) route_rescore_query(a, q, n, sh);
+  __threadfence_block();
+  __builtin_amdgcn_wave_barrier();
+  for (int32_t t = lane; t < a.c; t += 64) {
+    const int32_t j = a.routed[q * a.c + t];
+    Pair pr{-1, 0, 0, 0};
+    if (j >= 0) {
+      const int64_t L = models[j].L;
+      uint64_t K = 0;
+      const int64_t pos = locate(models + j, leaves, qdig + q * 2 * m + m, m, &K);
+      int64_t s, len;
+      window_of(pos, r, L, &s, &len);  // the expansion (if any) replaces s later
+      if (kq) kq[q * a.c + t] = K;
+      pr = Pair{j, int32_t(s), int32_t(len), int32_t(pos)};
+    }
+    pairs[q * a.c + t] = pr;
   }
 }
 
@@ -1505,9 +1619,6 @@ __device__ inline int32_t fetch_tile(int persistent, int32_t ntiles, int32_t* __
 // accumulator summed over the k-steps in order, so results do not depend on
 // the tile size, the schedule or which other pairs share a pass.
 constexpr int kRerankNT = 64;  // threads per rerank workgroup (one wave)
-
-// A wave-uniform value, moved to a scalar register.
-__device__ inline int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -2443,6 +2554,68 @@ __global__ __launch_bounds__(256, 2) void rerank_wg_kernel(
   }
 }
 
+// Window scores of a small batch, pair by pair: no work list, no schedule over
+// the index's tiles (one query: 8,704 workgroups of which nine had rows).  A
+// wave takes 16 rows of pair blockIdx.y's window (its row blocks of the
+// operand-ordered copy; blockIdx.x counts four of them from the window's first
+// one), the query in all sixteen pair rows of the MFMA, so a score is the same
+// chain as in the other reranks.  Rows and query values of kPairRing - 1 steps
+// are in flight; the grid is small, so latency bounds it: one query, 1,000 rows
+// x 768: 12 -> 6.4 us; 100 queries, 1,000 bf16 rows each, 148 MB: 39 -> 28.7 us
+// (5.2 TB/s).
+constexpr int kPairRing = 6;
+
+template <int FMT>
+__global__ __launch_bounds__(256) void pair_score_kernel(
+    const void* __restrict__ Xv, int32_t d, const Pair* __restrict__ pairs, int32_t c,
+    const void* __restrict__ Qv, const int32_t* __restrict__ tile_base,
+    const int32_t* __restrict__ tblk, float* __restrict__ sbuf, int32_t rcap) {
+  typedef Feed<FMT, true> F;
+  typedef typename F::T T;
+  typedef typename F::XE XE;
+  typedef typename F::QE QE;
+  constexpr int kHalf = 1024 / int(sizeof(XE));  // elements per 1 KB half of a chunk
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));  // uniform
+  const int i = lane & 15, s = lane >> 4;
+  const int64_t t = blockIdx.y;
+  const Pair pr = pairs[t];
+  const int32_t j = uni(pr.j), a = uni(pr.s), en = a + uni(pr.len);
+  const int32_t b = (a >> 4) + int32_t(blockIdx.x) * 4 + wave;  // row block of the cluster
+  if (j < 0 || 16 * b >= en) return;
+  const int32_t nsteps = d / F::KS;
+  // tblk holds the first block of every 128-row tile; a cluster's are consecutive
+  const XE* x0 = static_cast<const XE*>(Xv) + (int64_t(uni(tblk[tile_base[j]])) + b) * nsteps * (2 * kHalf);
+  const QE* q0 = static_cast<const QE*>(Qv) + (t / c) * d + F::SUBW * s;
+  T x[kPairRing], y[kPairRing];
+  auto load = [&](int k, int u) {
+    const int kk = min(k, nsteps - 1);
+    const XE* p = x0 + kk * (2 * kHalf) + lane * (kHalf / 64);
+    const floatx4 h0 = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p));
+    const floatx4 h1 = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p + kHalf));
+    x[u] = T{__builtin_bit_cast(decltype(T::a), h0), __builtin_bit_cast(decltype(T::b), h1)};
+    y[u] = F::load(q0, kk * F::KS, d);
+  };
+  floatx4 acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u + 1 < kPairRing; ++u) load(u, u);
+  int k = 0;
+  for (; k + kPairRing <= nsteps; k += kPairRing) {
+#pragma unroll
+    for (int u = 0; u < kPairRing; ++u) {
+      load(k + u + kPairRing - 1, (u + kPairRing - 1) % kPairRing);
+      __builtin_amdgcn_sched_barrier(0);
+      F::mfma(y[u], x[u], acc);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u + 1 < kPairRing; ++u)
+    if (k + u < nsteps) F::mfma(y[u], x[u], acc);
+  // every lane of column i holds row i's score
+  const int32_t row = 16 * b + i;
+  if (s == 0 && row >= a && row < en) sbuf[t * rcap + (row - a)] = acc[0];
+}
+
 // Layer-1 scores when every query's centroid window is the whole layer 1
 // (r1 = C): the dense product rs[q][p] = <Q[q], cent_l1[p]>, a GEMM on MFMA.
 // One (32 MB) x 128 output tile per workgroup; workgroups are dealt to the 8
@@ -2716,6 +2889,74 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
         const int64_t q = m0 + wr + 16 * a + 4 * s + e;
         if (q < nq) rs[q * C + p] = acc[a][b][e];
       }
+  }
+}
+
+// Layer-1 product of a small batch (d a multiple of 32): a workgroup owns 16
+// queries x 16 centroids, its 4 waves a quarter of the dimension range each,
+// eight steps' operands in flight straight from L2; the partial tiles are
+// added through LDS.  The 128 x 128 tiles of l1_gemm_lds_kernel give one query
+// eight workgroups with a chain of 12 or 24 chunks each (14 us); this takes 3
+// us, 5.4 with 100 queries.  SPLIT as there, from the fp32 operands.  The first l1_blocks
+// workgroups run the layer-1 locate.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void l1_small_kernel(const void* __restrict__ Qv, int64_t nq,
+                                                       const void* __restrict__ Cv, int32_t C,
+                                                       int32_t d, float* __restrict__ rs, L1Args la,
+                                                       unsigned l1_blocks) {
+  typedef typename std::conditional<SPLIT, float, __hip_bfloat16>::type E;
+  __shared__ floatx4 part[4][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x < l1_blocks) {
+    l1_item(la, int64_t(blockIdx.x) * 256 + tid);
+    return;
+  }
+  const int64_t t = blockIdx.x - l1_blocks;
+  const int32_t ntc = (C + 15) / 16;
+  const int i = lane & 15, s = lane >> 4;
+  const int64_t q0 = t / ntc * 16;
+  const int32_t c0 = int32_t(t % ntc) * 16;
+  const E* qr = static_cast<const E*>(Qv) + min(q0 + i, nq - 1) * d + 8 * s;
+  const E* cr = static_cast<const E*>(Cv) + int64_t(min(c0 + i, C - 1)) * d + 8 * s;
+  const int32_t nk = d / 32, k0 = wave * nk / 4, k1 = (wave + 1) * nk / 4;
+  floatx4 acc{0.f, 0.f, 0.f, 0.f};
+  constexpr int U = SPLIT ? 4 : 8;
+  for (int32_t kb = k0; kb < k1; kb += U) {
+    floatx4 x[U][2], y[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t o = 32 * min(kb + u, k1 - 1);
+      x[u][0] = *reinterpret_cast<const floatx4*>(qr + o);
+      y[u][0] = *reinterpret_cast<const floatx4*>(cr + o);
+      if (SPLIT) {
+        x[u][1] = *reinterpret_cast<const floatx4*>(qr + o + 4);
+        y[u][1] = *reinterpret_cast<const floatx4*>(cr + o + 4);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (kb + u >= k1) break;
+      if constexpr (SPLIT) {
+        const BF16x2 p = split_f32x8(x[u][0], x[u][1]), q = split_f32x8(y[u][0], y[u][1]);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p.a, q.a, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p.a, q.b, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p.b, q.a, acc, 0, 0, 0);
+      } else {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[u][0]),
+                                                      __builtin_bit_cast(bf16x8, y[u][0]), acc, 0, 0, 0);
+      }
+    }
+  }
+  part[wave][lane] = acc;
+  __syncthreads();
+  if (wave != 0) return;
+  acc = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+  // D layout: acc[e] = query 4 s + e, centroid i
+  if (c0 + i < C) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (q0 + 4 * s + e < nq) rs[(q0 + 4 * s + e) * C + c0 + i] = acc[e];
   }
 }
 
@@ -4273,6 +4514,20 @@ bool launch_score_wg(const Index& ix, bool bf16, const int32_t* cstart, const in
   return true;
 }
 
+// Pair by pair (Plan::small); a window of rcap rows touches at most rcap / 16 +
+// 1 row blocks.
+void launch_pair_scores(const Index& ix, bool bf16, int64_t np, const Pair* pairs, int32_t c,
+                        const float* Q, const __hip_bfloat16* Qb, float* sbuf, int32_t rcap,
+                        hipStream_t st) {
+  const dim3 grid(unsigned((rcap / 16 + 1 + 3) / 4), unsigned(np));
+  if (bf16)
+    hipLaunchKernelGGL(pair_score_kernel<kBF16W>, grid, dim3(256), 0, st, (const void*)ix.Xbt, ix.d,
+                       pairs, c, (const void*)Qb, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
+  else
+    hipLaunchKernelGGL(pair_score_kernel<kF32W>, grid, dim3(256), 0, st, (const void*)ix.Xt, ix.d,
+                       pairs, c, (const void*)Q, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
+}
+
 // npcm: 16-pair column blocks per pass (1, 2, 4 or 8; the per-wave rerank
 // takes at most 2 with 128-row tiles, at most 4 with 64-row tiles).
 template <int RT>
@@ -4374,6 +4629,17 @@ void launch_l1_gemm_mb(const Index& ix, bool fp8, int64_t nq, const float* Q,
 // aligned): the split product of the fp32 queries and centroids instead.
 void launch_l1_gemm_bf16(const Index& ix, int64_t nq, const __hip_bfloat16* Qb, float* rs,
                          hipStream_t st, const L1Args* la = nullptr, const float* Qf = nullptr) {
+  if (ix.d % kLdsK == 0 && nq <= kSmallBatch) {
+    const unsigned l1b = la ? unsigned((la->nq * la->H + 255) / 256) : 0u;
+    const dim3 grid(l1b + unsigned((nq + 15) / 16 * ((ix.C + 15) / 16)));
+    if (Qf)
+      hipLaunchKernelGGL(l1_small_kernel<true>, grid, dim3(256), 0, st, (const void*)Qf, nq,
+                         (const void*)ix.cent_l1, ix.C, ix.d, rs, la ? *la : L1Args{}, l1b);
+    else
+      hipLaunchKernelGGL(l1_small_kernel<false>, grid, dim3(256), 0, st, (const void*)Qb, nq,
+                         (const void*)ix.cent_l1_b, ix.C, ix.d, rs, la ? *la : L1Args{}, l1b);
+    return;
+  }
   if (ix.d % kLdsK == 0) {
     const int64_t nblk = (nq + 127) / 128 * ((ix.C + 127) / 128);
     const unsigned l1b = la ? unsigned((la->nq * la->H + 255) / 256 + 7) / 8 * 8 : 0u;
@@ -4424,7 +4690,10 @@ size_t search_workspace(const Index& ix, int64_t nq, int32_t k, int32_t c, int32
 int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c, int32_t r,
                int64_t* ids, float* scores, void* ws, size_t ws_bytes, hipStream_t st,
                const lider_search_opts& o, const lider_search_debug* dbg, hipEvent_t* ev) {
-  const Plan p = make_plan(ix, nq, k, c, r, o);
+  Plan p = make_plan(ix, nq, k, c, r, o);
+  // queries that 16-byte loads cannot read take the kernels that do without
+  const bool q16 = (reinterpret_cast<uintptr_t>(Q) & 15) == 0;
+  p.small = p.small && (q16 || o.precision == LIDER_BF16);
   if (ws_bytes < p.total)
     return set_error(LIDER_EINVAL, "workspace too small: need " + std::to_string(p.total) +
                                        " bytes, got " + std::to_string(ws_bytes));
@@ -4552,31 +4821,40 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
   {
     // every window is the whole dense row when r1 >= C with a single window per query
     const int whole = dense && !lstp && p.r1 >= C && o.expand_bits == 0;
-    const unsigned fgrid = unsigned((nq + 3) / 4);  // one wave per query (nq < 2^31)
-    if (p.lcap <= 16 * 64)
-      hipLaunchKernelGGL(route_filter_kernel<16>, dim3(fgrid), dim3(256), 0, st, ix.d, nq,
-                         ix.l1_order32, l1w, wst, lstp, p.lcap, rs, rstride, dense, qnorm,
-                         ix.cent_norm_max, ecoef, eadd, esub, c, rcand, rcnt, routed, whole);
-    else
-      hipLaunchKernelGGL(route_filter_kernel<0>, dim3(fgrid), dim3(256), 0, st, ix.d, nq,
-                         ix.l1_order32, l1w, wst, lstp, p.lcap, rs, rstride, dense, qnorm,
-                         ix.cent_norm_max, ecoef, eadd, esub, c, rcand, rcnt, routed, whole);
-    const unsigned rgrid =
-        unsigned(std::min<int64_t>((nq + kRescoreWaves - 1) / kRescoreWaves, 65535));
-    hipLaunchKernelGGL(route_rescore_kernel, dim3(rgrid), dim3(64 * kRescoreWaves), 0, st, Q, ix.d, nq,
-                       ix.cent_l1, ix.l1_order32, l1w, wst, lstp, p.lcap, c, rcand, rcnt, rs64,
-                       routed);
+    const RouteArgs ra{Q, ix.d, nq, ix.cent_l1, ix.l1_order32, l1w, wst, lstp, p.lcap, rs, rstride, dense,
+                       qnorm, ix.cent_norm_max, ecoef, eadd, esub, c, rcand, rcnt, rs64, routed, whole};
+    if (p.small) {
+      uint64_t* kqp = o.expand_bits > 0 ? kq : nullptr;
+      if (p.lcap <= 16 * 64)
+        hipLaunchKernelGGL(route_pairs_kernel<16>, dim3(unsigned(nq)), dim3(64), 0, st, ra, ix.models,
+                           ix.leaves, qdig, m, r, pairs, kqp);
+      else
+        hipLaunchKernelGGL(route_pairs_kernel<0>, dim3(unsigned(nq)), dim3(64), 0, st, ra, ix.models,
+                           ix.leaves, qdig, m, r, pairs, kqp);
+    } else {
+      const unsigned fgrid = unsigned((nq + 3) / 4);  // one wave per query (nq < 2^31)
+      if (p.lcap <= 16 * 64)
+        hipLaunchKernelGGL(route_filter_kernel<16>, dim3(fgrid), dim3(256), 0, st, ra);
+      else
+        hipLaunchKernelGGL(route_filter_kernel<0>, dim3(fgrid), dim3(256), 0, st, ra);
+      const unsigned rgrid =
+          unsigned(std::min<int64_t>((nq + kRescoreWaves - 1) / kRescoreWaves, 65535));
+      hipLaunchKernelGGL(route_rescore_kernel, dim3(rgrid), dim3(64 * kRescoreWaves), 0, st, ra);
+    }
   }
   mark(2);
   Pair* pwp = H > 1 ? pw : nullptr;
-  hipLaunchKernelGGL(pairs_kernel, dim3(unsigned((np * H + 255) / 256)), dim3(256), 0, st, ix.models,
-                     ix.leaves, qdig, m, H, C, np, c, r, routed, pairs, pwp, ccount,
-                     o.expand_bits > 0 ? kq : (uint64_t*)nullptr);
+  if (!p.small)
+    hipLaunchKernelGGL(pairs_kernel, dim3(unsigned((np * H + 255) / 256)), dim3(256), 0, st, ix.models,
+                       ix.leaves, qdig, m, H, C, np, c, r, routed, pairs, pwp, ccount,
+                       o.expand_bits > 0 ? kq : (uint64_t*)nullptr);
   if (o.expand_bits > 0)
     hipLaunchKernelGGL(expand_kernel, dim3(unsigned((np * H + 3) / 4)), dim3(256), 0, st,
                        ix.keys, ix.off, int64_t(0), H > 1 ? pw : pairs, np * H, kq,
                        o.expand_bits, (int32_t*)nullptr, H, ix.n);
-  if (C <= kFusedScanMax) {
+  if (p.small) {
+    // no work list
+  } else if (C <= kFusedScanMax) {
     hipLaunchKernelGGL(scan_scatter_kernel, dim3(unsigned(std::max<int64_t>(1, (np + 255) / 256))),
                        dim3(256), 0, st, ccount, C, pairs, np, cstart, cfill, wl);
   } else {
@@ -4597,7 +4875,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
   const int tr = 32 << ti;
   const int gm = o.grid_mult > 0 ? o.grid_mult : 4;
   const int npcm = p.npcm;
-  const bool win_split = p.split && (reinterpret_cast<uintptr_t>(Q) & 15) == 0;
+  const bool win_split = p.split && q16;
   if (o.persistent == 2) {
     const int32_t nt = ix.n_tiles[ti];
     hipLaunchKernelGGL(zero_kernel, dim3(unsigned(std::min<int64_t>((nt + 255) / 256, 4096))),
@@ -4605,7 +4883,9 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     hipLaunchKernelGGL(mark_tiles_kernel, dim3(unsigned((np + 255) / 256)), dim3(256), 0, st,
                        pairs, np, tr, ix.tile_base[ti], aflag, alist, ctr + 16);
   }
-  if (tr == 32)
+  if (p.small)
+    launch_pair_scores(ix, bf16, np, pairs, c, Q, qb, sbuf, p.rcap, st);
+  else if (tr == 32)
     launch_score<32>(ix, bf16, ti, cstart, wl, pairs, c, Q, qb, sbuf, p.rcap, o.persistent, gm,
                      ctr + 8, alist, npcm, H > 1 ? pmask : (const uint32_t*)nullptr, p.mw, bkey,
                      p.nbcap, st);
