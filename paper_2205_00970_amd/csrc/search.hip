@@ -3915,6 +3915,272 @@ __global__ __launch_bounds__(256) void wave_select_wide_kernel(
   }
 }
 
+// Per query top K for 64 < K <= 128 by a workgroup of 256 threads with the
+// candidates' keys in registers (n <= 256 R).  The (K+1)-th smallest of the 256
+// threads' own minima is a threshold that at least K + 1 candidates reach and
+// that about -256 ln(1 - (K+1) / 256) pass (130 for K = 100), so one look at the
+// keys, one bisection over 256 values and one ranking of the listed replace
+// the four histogram passes of the radix select: uneven clusters, 16 windows of
+// 512 rows, 2,048 queries, K = 100: 185 us by that, 55 us now (10,000 queries
+// 1,069 and 217 us).  More than
+// kBlockList listed (equal keys) go to the radix select.  MODE 0 and 2 as in
+// wave_select_kernel.
+constexpr int kBlockList = 512;
+
+template <int MODE, int R>
+__global__ __launch_bounds__(256) void block_select_wide_kernel(
+    const Pair* __restrict__ pairs, const float* __restrict__ sbuf, int32_t rcap, int32_t c,
+    int64_t nq, int32_t K, const int64_t* __restrict__ off, const int32_t* __restrict__ perm32,
+    int64_t* __restrict__ ids, float* __restrict__ scores, int32_t kout,
+    int32_t* __restrict__ slist, int drop, CertArgs ca) {
+  __shared__ SelShared sh;
+  __shared__ int32_t start[LIDER_MAX_C + 1];
+  __shared__ int64_t pbase[LIDER_MAX_C];  // sorted row of each slot's first candidate
+  __shared__ uint32_t tmin[256];
+  __shared__ uint64_t list[kBlockList];
+  __shared__ uint64_t ext[kWideK + 1];  // (key << 32 | index) by rank, or (key << 32 | id)
+  __shared__ int32_t widx[kWideK];
+  __shared__ uint64_t red[4];
+  __shared__ uint32_t s_tau, s_thr;
+  __shared__ int32_t s_m, s_valid;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t q = blockIdx.x;
+  const float* sbq = sbuf + q * int64_t(c) * rcap;
+  if (wave == 0) {
+    int32_t n0 = 0;
+    for (int t0 = 0; t0 < c; t0 += 64) {
+      const int t = t0 + lane;
+      int32_t len = 0;
+      int64_t base = 0;
+      if (t < c) {
+        const Pair pr = pairs[q * c + t];
+        if (pr.j >= 0) {
+          len = pr.len;
+          base = off[pr.j] + pr.s;
+        }
+      }
+      int32_t incl = len;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      if (t < c) {
+        start[t] = n0 + incl - len;
+        pbase[t] = base;
+      }
+      n0 += __shfl(incl, 63);
+    }
+    if (lane == 0) {
+      start[c] = n0;
+      s_m = s_valid = 0;
+    }
+  }
+  __syncthreads();
+  const int32_t n = start[c];
+  auto slot_of = [&](int32_t i) {
+    int lo = 0, hi = c;  // the largest slot t with start[t] <= i
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (start[mid] <= i)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    return lo;
+  };
+  auto row_of = [&](int32_t i) {
+    const int t = slot_of(i);
+    return pbase[t] + (i - start[t]);
+  };
+  // candidate i = tid + 256 j in register j, all loads issued before any key
+  // is formed (the slot of i only moves forward as i grows)
+  float fv[R];
+  if (n > 0) {
+    int t = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (256 * j >= n) continue;  // workgroup-uniform
+      const int32_t i = min(tid + 256 * j, n - 1);
+      while (t + 1 < c && start[t + 1] <= i) ++t;
+      fv[j] = sbq[int64_t(t) * rcap + (i - start[t])];
+    }
+  }
+  uint32_t kr[R];
+  uint32_t kmin = 0xffffffffu;
+  int nv = 0;  // this thread's candidates
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const bool in = tid + 256 * j < n;
+    kr[j] = in ? score_key(fv[j]) : 0xffffffffu;
+    if (in && !(drop && kr[j] == 0xffffffffu)) {
+      kmin = min(kmin, kr[j]);
+      ++nv;
+    }
+  }
+  auto cand = [&](int j) { return tid + 256 * j < n && !(drop && kr[j] == 0xffffffffu); };
+  tmin[tid] = kmin;
+  for (int o = 32; o > 0; o >>= 1) nv += __shfl_xor(nv, o);
+  if (lane == 0) atomicAdd(&s_valid, nv);
+  __syncthreads();
+  const int want = min(s_valid, K + 1);
+  if (wave == 0) {
+    // the want-th smallest thread minimum (all keys if fewer threads have one)
+    uint32_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = tmin[lane + 64 * u];
+    uint32_t lo = 0u, hi = 0xffffffffu;
+    while (lo < hi) {
+      const uint32_t mid = lo + ((hi - lo) >> 1);
+      int cnt = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cnt += __popcll(__ballot(v[u] <= mid));
+      if (cnt >= want)
+        hi = mid;
+      else
+        lo = mid + 1;
+    }
+    if (lane == 0) s_tau = lo;
+  }
+  __syncthreads();
+  const uint32_t tau = s_tau;
+  int mine = 0;
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+    if (256 * j < n) mine += cand(j) && kr[j] <= tau;
+  if (mine) {
+    int at = atomicAdd(&s_m, mine);
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (256 * j < n && cand(j) && kr[j] <= tau) {
+        if (at < kBlockList) list[at] = (uint64_t(kr[j]) << 32) | uint32_t(tid + 256 * j);
+        ++at;
+      }
+  }
+  __syncthreads();
+  const int m = s_m;
+  int got;
+  if (m <= kBlockList) {
+    // each listed entry's rank among the listed, by (key, index)
+    uint64_t me[kBlockList / 256];
+    int rk[kBlockList / 256];
+#pragma unroll
+    for (int v = 0; v < kBlockList / 256; ++v) {
+      me[v] = tid + 256 * v < m ? list[tid + 256 * v] : ~uint64_t(0);
+      rk[v] = 0;
+    }
+#pragma unroll 8
+    for (int u = 0; u < m; ++u) {
+      const uint64_t x = list[u];
+#pragma unroll
+      for (int v = 0; v < kBlockList / 256; ++v) rk[v] += x < me[v];
+    }
+#pragma unroll
+    for (int v = 0; v < kBlockList / 256; ++v)
+      if (tid + 256 * v < m && rk[v] < want) ext[rk[v]] = me[v];
+    __syncthreads();
+    got = min(want, K);
+    const bool tie = want == K + 1 && uint32_t(ext[K - 1] >> 32) == uint32_t(ext[K] >> 32);
+    uint64_t e = 0;
+    if (tid < got) e = ext[tid];
+    __syncthreads();
+    if (tid < got) {
+      const int32_t i = int32_t(e & 0xffffffffu);
+      widx[tid] = i;
+      ext[tid] = (e & 0xffffffff00000000ull) | uint32_t(perm32[row_of(i)]);
+    }
+    __syncthreads();
+    if (tie) {
+      // exact tie at the boundary: the tied places go to the smallest ids
+      const uint32_t TT = uint32_t(ext[K - 1] >> 32);
+      int need = 0;
+      for (int t = 0; t < K; ++t) need += uint32_t(ext[t] >> 32) == TT;
+      uint64_t last = 0;
+      for (int r = 0; r < need; ++r) {
+        uint64_t best = ~uint64_t(0);  // (id, index)
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          if (256 * j >= n || !(cand(j) && kr[j] == TT)) continue;
+          const uint32_t i = uint32_t(tid + 256 * j);
+          const uint64_t v = (uint64_t(uint32_t(perm32[row_of(int32_t(i))])) << 32) | i;
+          if ((r == 0 || v > last) && v < best) best = v;
+        }
+        best = wave_min_u64(best);
+        if (lane == 0) red[wave] = best;
+        __syncthreads();
+        best = min(min(red[0], red[1]), min(red[2], red[3]));
+        __syncthreads();
+        if (tid == 0) {
+          ext[K - need + r] = (uint64_t(TT) << 32) | (best >> 32);
+          widx[K - need + r] = int32_t(best & 0xffffffffu);
+        }
+        last = best;
+      }
+      __syncthreads();
+    }
+  } else {
+    __shared__ uint64_t srt[kWideK];
+    __shared__ int32_t sidx[kWideK];
+    auto key_of = [&](int i) {
+      const int t = slot_of(i);
+      return score_key(sbq[int64_t(t) * rcap + (i - start[t])]);
+    };
+    auto id_of = [&](int i) { return uint32_t(perm32[row_of(i)]); };
+    block_select<256>(n, K, pow2_at_least(K), key_of, id_of, srt, sidx, sh);
+    got = min(s_valid, K);  // dropped rows sort last
+    if (tid < got) {
+      ext[tid] = srt[tid];
+      widx[tid] = sidx[tid];
+    }
+    __syncthreads();
+  }
+  // the winners ordered by (key, id)
+  uint64_t me = ~uint64_t(0);
+  int rank = 0;
+  if (tid < kWideK) {
+    if (tid < got) me = ext[tid];
+#pragma unroll 8
+    for (int u = 0; u < got; ++u) rank += ext[u] < me;
+  }
+  if (MODE == 0) {
+    if (tid < got) {
+      ids[q * kout + rank] = int64_t(me & 0xffffffffu);
+      scores[q * kout + rank] = key_score(uint32_t(me >> 32));
+    }
+    for (int t = got + tid; t < kout; t += 256) {
+      ids[q * kout + t] = -1;
+      scores[q * kout + t] = -INFINITY;
+    }
+  } else {
+    // certified shortlist: every candidate within the margin of the k-th
+    // best key (the largest winner key when all K places are taken)
+    if (wave == 0) {
+      uint32_t tk = 0u;
+      for (int t = lane; t < got; t += 64) tk = max(tk, uint32_t(ext[t] >> 32));
+      for (int o = 32; o > 0; o >>= 1) tk = max(tk, uint32_t(__shfl_xor(tk, o)));
+      const uint32_t thr = cert_threshold(ca, q, got == K ? tk : 0xffffffffu, lane);
+      if (lane == 0) {
+        s_thr = thr;
+        s_m = 0;
+      }
+    }
+    __syncthreads();
+    const uint32_t thr = s_thr;
+    mine = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (256 * j < n) mine += cand(j) && kr[j] <= thr;
+    if (mine) {
+      int at = atomicAdd(&s_m, mine);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (256 * j < n && cand(j) && kr[j] <= thr)
+          slist[q * ca.cap + at++] = int32_t(row_of(tid + 256 * j));
+    }
+    __syncthreads();
+    if (tid == 0) ca.scnt[q] = s_m;
+  }
+}
+
 // Precision form, second pass: exact fp32 inner products of the shortlisted
 // rows (from the fp32 copy), then the top k.  One workgroup per query; one
 // wave per row at a time, lanes over dimensions.
@@ -4049,11 +4315,15 @@ __global__ __launch_bounds__(256) void wave_shortlist_kernel(
 // workgroup per query; the list is taken in chunks of kCertChunk rows, each
 // merged with the best k so far.  16 lanes per row (float4 slots when d % 4
 // == 0 and the rows are 16-byte aligned, else scalar), reduced over the 16
-// lanes by a fixed xor tree.
+// lanes by a fixed xor tree.  A chunk that fits the workgroup with the best so
+// far is ranked all against all, a longer one goes through the radix select.
+// 1,024 threads for up to 1,024 queries, whose lists bound the time (100 queries,
+// k = 100, 120 rows each: 59 us with 256 threads, one step of the loads in
+// flight and the radix select, 17 us now).
 constexpr int kCertChunk = 1024;
 
-template <int KPMAX>
-__global__ __launch_bounds__(kSelNT) void cert_rerank_kernel(
+template <int KPMAX, int NT>
+__global__ __launch_bounds__(NT) void cert_rerank_kernel(
     const float* __restrict__ X, int32_t d, const float* __restrict__ Q, int64_t nq,
     const int32_t* __restrict__ slist, int64_t cap, const int32_t* __restrict__ scnt,
     const int32_t* __restrict__ perm32, int32_t k, int vec, int64_t* __restrict__ ids,
@@ -4064,6 +4334,7 @@ __global__ __launch_bounds__(kSelNT) void cert_rerank_kernel(
   __shared__ uint64_t best[KPMAX];
   __shared__ float sc[kCertChunk];
   __shared__ int32_t rows[kCertChunk];
+  __shared__ uint64_t all[NT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, c16 = lane & 15;
   const int KP = pow2_at_least(k);
@@ -4073,39 +4344,74 @@ __global__ __launch_bounds__(kSelNT) void cert_rerank_kernel(
     int nb = 0;
     for (int32_t c0 = 0; c0 < n; c0 += kCertChunk) {
       const int m = min(kCertChunk, n - c0);
-      for (int t = tid; t < m; t += kSelNT) rows[t] = slist[q * cap + c0 + t];
+      for (int t = tid; t < m; t += NT) rows[t] = slist[q * cap + c0 + t];
       __syncthreads();
-      for (int t0 = 4 * wave; t0 < m; t0 += 4 * (kSelNT / 64)) {
-        const int t = t0 + g;
-        const float* xr = X + int64_t(rows[min(t, m - 1)]) * d;
-        float acc = 0.f;
+      // eight rows per wave and round, four steps of their loads in flight
+      for (int t0 = 8 * wave; t0 < m; t0 += 8 * (NT / 64)) {
+        const int ta = t0 + g, tb = t0 + 4 + g;
+        const float* xa = X + int64_t(rows[min(ta, m - 1)]) * d;
+        const float* xb = X + int64_t(rows[min(tb, m - 1)]) * d;
+        float acca = 0.f, accb = 0.f;
         if (vec) {
+#pragma unroll 4
           for (int l = 4 * c16; l < d; l += 64) {
-            const float4 v = *reinterpret_cast<const float4*>(xr + l);
+            const float4 va = *reinterpret_cast<const float4*>(xa + l);
+            const float4 vb = *reinterpret_cast<const float4*>(xb + l);
             const float4 w = *reinterpret_cast<const float4*>(qv + l);
-            acc += v.x * w.x;
-            acc += v.y * w.y;
-            acc += v.z * w.z;
-            acc += v.w * w.w;
+            acca += va.x * w.x;
+            acca += va.y * w.y;
+            acca += va.z * w.z;
+            acca += va.w * w.w;
+            accb += vb.x * w.x;
+            accb += vb.y * w.y;
+            accb += vb.z * w.z;
+            accb += vb.w * w.w;
           }
         } else {
-          for (int l = c16; l < d; l += 16) acc += xr[l] * qv[l];
+          for (int l = c16; l < d; l += 16) {
+            acca += xa[l] * qv[l];
+            accb += xb[l] * qv[l];
+          }
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-        if (c16 == 0 && t < m) sc[t] = acc;
+        for (int o = 8; o > 0; o >>= 1) {
+          acca += __shfl_xor(acca, o);
+          accb += __shfl_xor(accb, o);
+        }
+        if (c16 == 0 && ta < m) sc[ta] = acca;
+        if (c16 == 0 && tb < m) sc[tb] = accb;
       }
       __syncthreads();
-      const int got = block_select<kSelNT>(
-          m + nb, k, KP,
-          [&](int i) { return i < m ? score_key(sc[i]) : uint32_t(best[i - m] >> 32); },
-          [&](int i) { return i < m ? uint32_t(perm32[rows[i]]) : uint32_t(best[i - m]); }, srt,
-          sidx, sh);
-      for (int t = tid; t < got; t += kSelNT) best[t] = srt[t];
+      const int tot = m + nb;
+      int got;
+      if (tot <= NT) {
+        // every entry's rank among all, by (key, id)
+        uint64_t me = ~uint64_t(0);
+        if (tid < m)
+          me = (uint64_t(score_key(sc[tid])) << 32) | uint32_t(perm32[rows[tid]]);
+        else if (tid < tot)
+          me = best[tid - m];
+        all[tid] = me;
+        __syncthreads();
+        int rank = 0;
+        if (tid < tot) {
+#pragma unroll 8
+          for (int u = 0; u < tot; ++u) rank += all[u] < me;
+        }
+        got = min(tot, k);
+        if (tid < tot && rank < got) best[rank] = me;
+      } else {
+        got = block_select<NT>(
+            tot, k, KP,
+            [&](int i) { return i < m ? score_key(sc[i]) : uint32_t(best[i - m] >> 32); },
+            [&](int i) { return i < m ? uint32_t(perm32[rows[i]]) : uint32_t(best[i - m]); }, srt,
+            sidx, sh);
+        for (int t = tid; t < got; t += NT) best[t] = srt[t];
+      }
       nb = got;
       __syncthreads();
     }
-    for (int t = tid; t < k; t += kSelNT) {
+    for (int t = tid; t < k; t += NT) {
       if (t < nb) {
         ids[q * k + t] = int64_t(best[t] & 0xffffffffu);
         scores[q * k + t] = key_score(uint32_t(best[t] >> 32));
@@ -4419,19 +4725,44 @@ void launch_wave_select(hipStream_t st, const Pair* pairs, const float* sbuf, in
                        (const uint32_t*)nullptr, 0);
 }
 
-// 64 < K <= 128 over at most 2,048 candidates per query.
+// 64 < K <= 128 over at most kWideMax candidates per query, a workgroup per
+// query.
+constexpr int64_t kWideMax = 16384;
+// The wave form is the faster one only for short rows and large batches (K =
+// 100, wave against workgroup: 512 candidates, 10,000 queries 71 against 87 us,
+// 500 queries 23 against 15; 2,048 candidates, 10,000 queries 152 against 105).
+inline bool wide_by_block(int64_t nmax, int64_t nq) {
+  return nmax <= kWideMax && (nmax > 1024 || nq <= 1024);
+}
+
+template <int MODE>
+void launch_block_wide(hipStream_t st, const Pair* pairs, const float* sbuf, int32_t rcap,
+                       int32_t c, int64_t nq, int32_t K, const int64_t* off, const int32_t* perm32,
+                       int64_t* ids, float* scores, int32_t kout, int32_t* slist, int drop,
+                       CertArgs ca) {
+  const int64_t nmax = int64_t(c) * rcap;
+#define LIDER_BW(R)                                                                               \
+  hipLaunchKernelGGL((block_select_wide_kernel<MODE, R>), dim3(unsigned(nq)), dim3(256), 0, st,   \
+                     pairs, sbuf, rcap, c, nq, K, off, perm32, ids, scores, kout, slist, drop, ca)
+  if (nmax <= 2048)
+    LIDER_BW(8);
+  else if (nmax <= 4096)
+    LIDER_BW(16);
+  else if (nmax <= 8192)
+    LIDER_BW(32);
+  else
+    LIDER_BW(64);
+#undef LIDER_BW
+}
+
+// 64 < K <= 128 over at most 1,024 candidates per query, a wave per query.
 template <int MODE>
 void launch_wave_wide(hipStream_t st, const Pair* pairs, const float* sbuf, int32_t rcap,
                       int32_t c, int64_t nq, int32_t K, const int64_t* off, const int32_t* perm32,
                       int64_t* ids, float* scores, int32_t kout, int32_t* slist, int drop,
                       CertArgs ca) {
-  const unsigned wgrid = unsigned((nq + 3) / 4);  // one wave per query (nq < 2^31)
-  if (int64_t(c) * rcap <= 1024)
-    hipLaunchKernelGGL((wave_select_wide_kernel<MODE, 16>), dim3(wgrid), dim3(256), 0, st, pairs,
-                       sbuf, rcap, c, nq, K, off, perm32, ids, scores, kout, slist, drop, ca);
-  else
-    hipLaunchKernelGGL((wave_select_wide_kernel<MODE, 32>), dim3(wgrid), dim3(256), 0, st, pairs,
-                       sbuf, rcap, c, nq, K, off, perm32, ids, scores, kout, slist, drop, ca);
+  hipLaunchKernelGGL((wave_select_wide_kernel<MODE, 16>), dim3(unsigned((nq + 3) / 4)), dim3(256), 0,
+                     st, pairs, sbuf, rcap, c, nq, K, off, perm32, ids, scores, kout, slist, drop, ca);
 }
 
 template <int RT, int NPCM>
@@ -4928,7 +5259,10 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     if (k <= 64)
       launch_wave_select<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids,
                             scores, k, slist, int(H > 1), CertArgs(), bkey, p.nbcap);
-    else if (k <= 128 && int64_t(c) * p.rcap <= 2048)
+    else if (k <= 128 && wide_by_block(int64_t(c) * p.rcap, nq))
+      launch_block_wide<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
+                           slist, int(H > 1), CertArgs());
+    else if (k <= 128 && int64_t(c) * p.rcap <= 1024)
       launch_wave_wide<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
                           slist, int(H > 1), CertArgs());
     else if (k <= 128)
@@ -4954,7 +5288,10 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     if (k <= 64)
       launch_wave_select<2>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
                             slist, int(H > 1), ca, bkey, p.nbcap);
-    else if (k <= 128 && int64_t(c) * p.rcap <= 2048)
+    else if (k <= 128 && wide_by_block(int64_t(c) * p.rcap, nq))
+      launch_block_wide<2>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
+                           slist, int(H > 1), ca);
+    else if (k <= 128 && int64_t(c) * p.rcap <= 1024)
       launch_wave_wide<2>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
                           slist, int(H > 1), ca);
     else if (k <= 128)
@@ -4969,12 +5306,15 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     if (k <= 64)
       hipLaunchKernelGGL(cert_wave_kernel, dim3(unsigned((nq + 3) / 4)), dim3(256), 0, st, ix.X,
                          ix.d, Q, nq, slist, ca.cap, ca.scnt, ix.perm32, k, vec, ids, scores);
-    else if (k <= 128)
-      hipLaunchKernelGGL(cert_rerank_kernel<128>, dim3(qgrid), dim3(kSelNT), 0, st, ix.X, ix.d, Q,
-                         nq, slist, ca.cap, ca.scnt, ix.perm32, k, vec, ids, scores);
-    else
-      hipLaunchKernelGGL(cert_rerank_kernel<1024>, dim3(qgrid), dim3(kSelNT), 0, st, ix.X, ix.d,
+    else if (k <= 128 && nq <= 1024)
+      hipLaunchKernelGGL((cert_rerank_kernel<128, 1024>), dim3(qgrid), dim3(1024), 0, st, ix.X, ix.d,
                          Q, nq, slist, ca.cap, ca.scnt, ix.perm32, k, vec, ids, scores);
+    else if (k <= 128)
+      hipLaunchKernelGGL((cert_rerank_kernel<128, kSelNT>), dim3(qgrid), dim3(kSelNT), 0, st, ix.X,
+                         ix.d, Q, nq, slist, ca.cap, ca.scnt, ix.perm32, k, vec, ids, scores);
+    else
+      hipLaunchKernelGGL((cert_rerank_kernel<1024, kSelNT>), dim3(qgrid), dim3(kSelNT), 0, st, ix.X,
+                         ix.d, Q, nq, slist, ca.cap, ca.scnt, ix.perm32, k, vec, ids, scores);
   } else {
     if (p.S <= 64)
       launch_wave_select<1>(st, pairs, sbuf, p.rcap, c, nq, p.S, ix.off, ix.perm32, ids,
