@@ -339,6 +339,182 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
   }
 }
 
+// The product for few centroids (C <= 16 NB <= 128): the wide tile would
+// multiply mostly padding, and the points' rows, read once, bound the time.  A
+// workgroup of 4 waves owns 64 RB points, a wave 16 RB of them and every
+// column; its rows are in flight four steps ahead (a ring of register sets),
+// the step's centroids go through two LDS slots, staged two steps ahead, and
+// no load stands under a condition.  66,872 x 768 points, 18 centroids: 85 us by
+// the fp32 product of 16 points per wave, 125 by the wide tile, 30 now; 97,695 points: 60
+// centroids 160 -> 46, 128 330 -> 68 us.
+template <int MODE, int NB, int RB>
+__global__ __launch_bounds__(256) void assign_narrow_kernel(
+    const float* __restrict__ X, int64_t n, int32_t d, const bf16x8* __restrict__ cs,
+    const float* __restrict__ cnorm, AssignOut o, float4* __restrict__ part) {
+  constexpr int ROWS = 64 * RB, P = 4, NS = (NB * 128 + 255) / 256;
+  __shared__ bf16x8 sb[2][NB * 128];
+  __shared__ float sbv[ROWS], ssv[ROWS], sss[ROWS];
+  __shared__ int32_t sbi[ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = lane & 15, s = lane >> 4;
+  const int64_t row0 = int64_t(blockIdx.x) * ROWS;
+  const int32_t nk = asg_steps(d);
+  const float* xt = X + row0 * d;
+  const int32_t rlast = int32_t(min(n - row0, int64_t(ROWS))) - 1;
+  int32_t xo[RB];
+#pragma unroll
+  for (int a = 0; a < RB; ++a) xo[a] = min(16 * (RB * wave + a) + i, rlast) * d + 8 * s;
+  float4 xa[P][RB][2];
+  bf16x8 st[2][NS];
+  auto load_points = [&](int32_t kc, float4 (&x)[RB][2]) {
+    kc = min(kc, nk - 1);
+    const float* xk = xt + 32 * kc;
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int32_t at = xo[a] + 4 * h, kd = 32 * kc + 8 * s + 4 * h;
+        if (MODE == 2) {
+          x[a][h] = *reinterpret_cast<const float4*>(xk + at);
+        } else if (MODE == 1) {
+          const float4 v = *reinterpret_cast<const float4*>(xk + at - max(kd - (d - 4), 0));
+          x[a][h] = kd < d ? v : float4{0.f, 0.f, 0.f, 0.f};
+        } else {
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = xk[at + e - max(kd + e - (d - 1), 0)];
+          x[a][h].x = kd < d ? v[0] : 0.f;
+          x[a][h].y = kd + 1 < d ? v[1] : 0.f;
+          x[a][h].z = kd + 2 < d ? v[2] : 0.f;
+          x[a][h].w = kd + 3 < d ? v[3] : 0.f;
+        }
+      }
+  };
+  auto load_cents = [&](int32_t kc, bf16x8 (&v)[NS]) {
+    const bf16x8* ck = cs + int64_t(min(kc, nk - 1)) * 128;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int32_t p = (tid + 256 * j) & (NB * 128 - 1);  // the same piece twice where threads are left
+      v[j] = ck[(p >> 7) * (nk * 128) + (p & 127)];
+    }
+  };
+  auto store_cents = [&](int slot, const bf16x8 (&v)[NS]) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j) sb[slot][(tid + 256 * j) & (NB * 128 - 1)] = v[j];
+  };
+  floatx4 acc[RB][NB];
+#pragma unroll
+  for (int a = 0; a < RB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float ss[RB] = {};
+  load_cents(0, st[0]);
+  load_cents(1, st[1]);
+#pragma unroll
+  for (int u = 0; u < P; ++u) load_points(u, xa[u]);
+  store_cents(0, st[0]);
+  __syncthreads();
+  auto step = [&](int u, int32_t kc) {
+    bf16x8 ah[RB], al[RB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a) {
+      const float v[8] = {xa[u][a][0].x, xa[u][a][0].y, xa[u][a][0].z, xa[u][a][0].w,
+                          xa[u][a][1].x, xa[u][a][1].y, xa[u][a][1].z, xa[u][a][1].w};
+      split8(v, ah[a], al[a]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ss[a] += v[e] * v[e];
+    }
+    load_cents(kc + 2, st[u & 1]);
+    load_points(kc + P, xa[u]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const bf16x8 bh = sb[u & 1][b * 128 + lane], bl = sb[u & 1][b * 128 + 64 + lane];
+#pragma unroll
+      for (int a = 0; a < RB; ++a)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[a], bh, acc[a][b], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < RB; ++a)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[a], bl, acc[a][b], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < RB; ++a)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[a], bh, acc[a][b], 0, 0, 0);
+    }
+    store_cents((u + 1) & 1, st[(u + 1) & 1]);
+    __syncthreads();
+  };
+  int32_t kc = 0;
+  for (; kc + P <= nk; kc += P) {
+#pragma unroll
+    for (int u = 0; u < P; ++u) step(u, kc + u);
+  }
+#pragma unroll
+  for (int u = 0; u + 1 < P; ++u)
+    if (kc + u < nk) step(u, kc + u);
+  float cn[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) cn[b] = cnorm[16 * b + i];
+#pragma unroll
+  for (int a = 0; a < RB; ++a) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      Best v{INFINITY, 0x7fffffff, INFINITY};
+#pragma unroll
+      for (int b = 0; b < NB; ++b) best_push(v, cn[b] - 2.f * acc[a][b][e], 16 * b + i);
+      v = best_merge(v, best_ror<8>(v));
+      v = best_merge(v, best_ror<4>(v));
+      v = best_merge(v, best_ror<2>(v));
+      v = best_merge(v, best_ror<1>(v));
+      if (i == 0) {
+        const int r = 16 * (RB * wave + a) + 4 * s + e;
+        sbv[r] = v.bv;
+        sbi[r] = v.bi;
+        ssv[r] = v.sv;
+      }
+    }
+    float q = ss[a];  // over the four dimension slots
+    q += __shfl_xor(q, 16);
+    q += __shfl_xor(q, 32);
+    if (s == 0) sss[16 * (RB * wave + a) + i] = q;
+  }
+  __syncthreads();
+  if (tid < ROWS && row0 + tid < n) {
+    const Best v{sbv[tid], sbi[tid], ssv[tid]};
+    if (!part)
+      assign_decide(o, row0 + tid, v, sss[tid]);
+    else
+      part[row0 + tid] = float4{v.bv, __int_as_float(v.bi), v.sv, sss[tid]};
+  }
+}
+
+// Most centroids of the narrow product.
+constexpr int32_t kAsgNarrow = 128;
+
+template <int MODE>
+static void launch_narrow(const float* X, int64_t n, int32_t d, const bf16x8* cs, const float* cnorm,
+                          const AssignOut& o, float4* part, hipStream_t st) {
+  // 64 points per workgroup while 128 would leave CUs without one
+  const bool few = n < 128 * 256;
+  const dim3 grid(unsigned((n + (few ? 63 : 127)) / (few ? 64 : 128)));
+#define LIDER_NARROW(NB)                                                                             \
+  if (few)                                                                                           \
+    hipLaunchKernelGGL((assign_narrow_kernel<MODE, NB, 1>), grid, dim3(256), 0, st, X, n, d, cs,     \
+                       cnorm, o, part);                                                              \
+  else                                                                                               \
+    hipLaunchKernelGGL((assign_narrow_kernel<MODE, NB, 2>), grid, dim3(256), 0, st, X, n, d, cs,     \
+                       cnorm, o, part);
+  if (o.C <= 16) {
+    LIDER_NARROW(1)
+  } else if (o.C <= 32) {
+    LIDER_NARROW(2)
+  } else if (o.C <= 64) {
+    LIDER_NARROW(4)
+  } else {
+    LIDER_NARROW(8)
+  }
+#undef LIDER_NARROW
+}
+
 // The groups' bests of each point merged and decided.
 __global__ __launch_bounds__(256) void assign_merge_kernel(const float4* __restrict__ part,
                                                            int64_t n, int32_t G, AssignOut o) {
@@ -461,7 +637,14 @@ static void launch_product(const float* X, int64_t n, int32_t d, const float* ce
                      cent, C, d, a.cs, a.cnorm, a.maxbits);
   const bool al = (reinterpret_cast<uintptr_t>(X) & 15) == 0;
   const dim3 grid(unsigned((n + kAsgTile - 1) / kAsgTile), unsigned(G));
-  if (al && d % 32 == 0)
+  if (C <= kAsgNarrow) {
+    if (al && d % 32 == 0)
+      launch_narrow<2>(X, n, d, a.cs, a.cnorm, o, part, st);
+    else if (al && d % 4 == 0)
+      launch_narrow<1>(X, n, d, a.cs, a.cnorm, o, part, st);
+    else
+      launch_narrow<0>(X, n, d, a.cs, a.cnorm, o, part, st);
+  } else if (al && d % 32 == 0)
     hipLaunchKernelGGL(assign_kernel<2>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles, o, part);
   else if (al && d % 4 == 0)
     hipLaunchKernelGGL(assign_kernel<1>, grid, dim3(512), 0, st, X, n, d, a.cs, a.cnorm, ntiles, o, part);

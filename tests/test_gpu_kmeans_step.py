@@ -10,7 +10,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,C,d", [(1, 1, 1), (1, 2, 3), (255, 255, 31), (256, 256, 32), (257, 257, 33),
-                                   (1000, 600, 100), (513, 1025, 130), (4000, 37, 96), (70000, 16, 64)])
+                                   (1000, 600, 100), (513, 1025, 130), (4000, 37, 96), (70000, 16, 64),
+                                   (63, 17, 32), (64, 32, 160), (65, 33, 100), (129, 64, 31), (40000, 65, 52),
+                                   (33000, 128, 36), (33000, 129, 68), (3000, 15, 7)])
 def test_tile_edges_and_ties(n, C, d):
     import torch
     from paper_2205_00970_amd import lider
