@@ -212,13 +212,14 @@ const char* lider_last_error(void);
  *                 exactly c they are rescored by sequential FP64 inner
  *                 products.  0 (default): one dense query x centroid product
  *                 on MFMA in bf16 (every centroid scored; each query's window
- *                 read from its row), split when c > 1 (as 3).  1: the dense
+ *                 read from its row), split when c > 1 or d is not a
+ *                 multiple of 64 (as 3).  1: the dense
  *                 product in fp32.  2: the plain bf16 product (bf16 roundings
  *                 of both operands).  3: the split bf16 product: each fp32
  *                 value x becomes h = bf16(x) and l = bf16(x - h), and the
  *                 score sums h_q h_mu + h_q l_mu + l_q h_mu (error about
  *                 3 2^-16 |q| |mu| instead of 2^-7 |q| |mu|: far fewer
- *                 candidates to rescore when c > 1; needs d a multiple of 64
+ *                 candidates to rescore when c > 1; needs d a multiple of 4
  *                 and 16-byte aligned queries, else acts as 2).  -1: the
  *                 window kernel (fp32 scores of the r1-windows only).  The
  *                 routed sets, and so all results, are identical.  With

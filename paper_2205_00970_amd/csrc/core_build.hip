@@ -478,7 +478,7 @@ __global__ void compose_kernel(const int64_t* __restrict__ permh, int64_t n,
 
 // Operand-ordered copy of the reordered corpus, one wave per 16-row block:
 // block b takes rows src[b].x .. src[b].x + src[b].y - 1 of X (zeros past
-// them).  fp32 (KS = 32): for every k-step and half h, lane l = i + 16 s writes
+// them, and past d).  fp32 (KS = 32): for every k-step and half h, lane l = i + 16 s writes
 // dims [32 ks + 16 h + 4 s, + 4) of row i at float offset ((b nks + ks) 2 + h)
 // 256 + 4 l.  bf16 (KS = 64): dims [64 ks + 32 h + 8 s, + 8), rounded to
 // nearest even like the row-major bf16 copy, at element offset
@@ -494,7 +494,8 @@ __global__ __launch_bounds__(256) void tile_corpus_kernel(const float* __restric
   constexpr int KS = BF ? 64 : kTileKS, EPL = BF ? 8 : 4;  // dims per k-step, per lane
   const int lane = threadIdx.x & 63;
   const int i = lane & 15, s = lane >> 4;
-  const int32_t nks = d / KS;
+  const int32_t nks = (d + KS - 1) / KS;  // bf16: d a multiple of 64
+  const bool vec = d % 4 == 0;
   for (int64_t b = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); b < nblk;
        b += int64_t(gridDim.x) * 4) {
     const int2 sr = src[b];
@@ -511,7 +512,14 @@ __global__ __launch_bounds__(256) void tile_corpus_kernel(const float* __restric
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = __float2bfloat16(ok ? xr[k + e] : 0.f);
         } else {
-          const float4 v = ok ? *reinterpret_cast<const float4*>(xr + k) : float4{0.f, 0.f, 0.f, 0.f};
+          float4 v = float4{0.f, 0.f, 0.f, 0.f};
+          if (ok && vec && k < d) v = *reinterpret_cast<const float4*>(xr + k);
+          if (ok && !vec) {
+            v.x = k < d ? xr[k] : 0.f;
+            v.y = k + 1 < d ? xr[k + 1] : 0.f;
+            v.z = k + 2 < d ? xr[k + 2] : 0.f;
+            v.w = k + 3 < d ? xr[k + 3] : 0.f;
+          }
           *reinterpret_cast<float4*>(static_cast<float*>(out) + at) = v;
           ss += v.x * v.x;
           ss += v.y * v.y;
@@ -656,7 +664,10 @@ int finish_index(Index& ix) {
   // clusters padded to whole 16-row blocks in the operand-ordered copy
   std::vector<int64_t> pblk(size_t(C) + 1, 0);  // first 16-row block of each cluster
   for (int32_t j = 0; j < C; ++j) pblk[j + 1] = pblk[j] + (ix.h_off[j + 1] - ix.h_off[j] + 15) / 16;
-  const bool want_t = ix.d % kTileKS == 0;
+  // the fp32 copy's rows are padded with zeros to whole k-steps; not where that
+  // would add more than half of the rows' bytes
+  const int32_t dpad = (ix.d + kTileKS - 1) / kTileKS * kTileKS;
+  const bool want_t = 2 * int64_t(dpad) <= 3 * int64_t(ix.d);
   const bool want_bt = ix.storage == LIDER_BF16 && ix.d % 64 == 0 && !ix.Xbt;
   if ((want_t || want_bt) && pblk[C] > 0) {
     const int64_t nblk = pblk[C];
@@ -667,7 +678,7 @@ int finish_index(Index& ix) {
         src[b] = make_int2(int32_t(r0), int32_t(std::min<int64_t>(16, ix.h_off[j + 1] - r0)));
       }
     int2* dsrc = nullptr;
-    const size_t elems = size_t(nblk) * 16 * size_t(ix.d);  // per copy
+    const size_t elems = size_t(nblk) * 16 * size_t(dpad);  // per copy (bf16: dpad = d)
     const size_t tab = al256(src.size() * sizeof(int2));  // then the largest norm
     if (hipMalloc(&dsrc, tab + 256) != hipSuccess)
       return set_error(LIDER_ENOMEM, "out of device memory (operand-ordered corpus)");

@@ -344,9 +344,9 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
 // workgroup of 4 waves owns 64 RB points, a wave 16 RB of them and every
 // column; its rows are in flight four steps ahead (a ring of register sets),
 // the step's centroids go through two LDS slots, staged two steps ahead, and
-// no load stands under a condition.  66,872 x 768 points, 18 centroids: 85 us by
-// the fp32 product of 16 points per wave, 125 by the wide tile, 30 now; 97,695 points: 60
-// centroids 160 -> 46, 128 330 -> 68 us.
+// no load stands under a condition.  A call with 66,872 x 768 points and 18
+// centroids: 133 us by the fp32 product of 16 points per wave, 171 by the wide
+// tile, 75 now; 97,695 points and 60 centroids 206 -> 91, 128 374 -> 113.
 template <int MODE, int NB, int RB>
 __global__ __launch_bounds__(256) void assign_narrow_kernel(
     const float* __restrict__ X, int64_t n, int32_t d, const bf16x8* __restrict__ cs,

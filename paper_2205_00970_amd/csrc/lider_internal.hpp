@@ -222,8 +222,8 @@ struct Index {
   // Per-array tables are array-major; array 0's sort order is the physical
   // row order (the reordered corpus, tiles, search positions).
   float* X = nullptr;          // [n x d] reordered by array 0's (cluster, key, id)
-  // The same rows in the rerank's MFMA operand order (d a multiple of 32):
-  // each cluster padded with zero rows to a multiple of 16; per 16-row block
+  // The same rows in the rerank's MFMA operand order (dims padded with zeros to
+  // a multiple of 32, where that adds at most half): each cluster padded with zero rows to a multiple of 16; per 16-row block
   // and 32-dim k-step one 2 KB chunk of two 1 KB halves, in which lane
   // l = i + 16 s holds dims [4 s, 4 s + 4) (then [16 + 4 s, 16 + 4 s + 4)) of
   // row i -- one contiguous 1 KB wave load per half.

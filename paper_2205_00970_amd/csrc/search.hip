@@ -113,7 +113,7 @@ void rerank_shape(const Index& ix, int64_t nq, int32_t c, int32_t r, const lider
   const double span = std::min(lbar, double(ix.H) * std::min(double(r), lbar));
   const double per_cluster = double(nq) * c / double(ix.C);
   const bool bf16 = o.precision == LIDER_BF16;
-  const bool wg_ok = o.persistent == 0 && (bf16 ? (ix.d % 64 == 0 && ix.Xbt) : (ix.d % 32 == 0 && ix.Xt));
+  const bool wg_ok = o.persistent == 0 && (bf16 ? (ix.d % 64 == 0 && ix.Xbt) : ix.Xt != nullptr);
   *pairs = per_cluster * std::min(1.0, (span + 128.0) / lbar);  // per 128-row tile
   if (wg_ok && (o.tile_rows == 0 || o.tile_rows == 128)) {
     *ti = 2;
@@ -204,12 +204,13 @@ Plan make_plan(const Index& ix, int64_t nq, int32_t k, int32_t c, int32_t r,
   // its lists take the room of the layer-1 scores, which nothing reads any more
   p.split = o.precision == LIDER_F32 && o.persistent == 0 && o.tile_rows == 0 &&
             o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && pairs > kSplitMinPairs && k <= kSplitMaxK &&
-            (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.x_norm_max < kSplitMaxRow;
+            (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.x_norm_max < kSplitMaxRow &&
+            ix.d % 32 == 0;
   // pair by pair: few queries whose windows hardly share a cluster (a quarter
   // as many pairs as clusters: 12% of them do), or few enough rows for the
   // caches to serve the shared ones
   const double wrows = double(nq) * c * double(std::min<int64_t>(r, ix.max_cluster) + 16);
-  const bool tiled = o.precision == LIDER_BF16 ? ix.d % 64 == 0 && ix.Xbt : ix.d % 32 == 0 && ix.Xt;
+  const bool tiled = o.precision == LIDER_BF16 ? ix.d % 64 == 0 && ix.Xbt : ix.Xt != nullptr;
   p.small = H == 1 && nq <= kSmallBatch && o.persistent == 0 && o.tile_rows == 0 && o.pass_pairs == 0 &&
             tiled && np <= 32768 &&
             (np * 4 <= ix.C || wrows * ix.d * (o.precision == LIDER_BF16 ? 2.0 : 4.0) <= double(64 << 20));
@@ -1633,7 +1634,9 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // plus KS/2 of the second.
 // 5: kF32W's rows and queries, each value x split into h = bf16(x) and l =
 // bf16(x - h) for three bf16 products (the workgroup rerank only).
-enum { kF32 = 0, kBF16 = 1, kFP8 = 2, kF32W = 3, kBF16W = 4, kF32S = 5 };
+// 6: kF32W's rows with zeros past d (any d), the queries read with clamped
+// addresses (the workgroup and pair reranks; the chain of kF32W without VEC).
+enum { kF32 = 0, kBF16 = 1, kFP8 = 2, kF32W = 3, kBF16W = 4, kF32S = 5, kF32P = 6 };
 
 template <int FMT, bool VEC>
 struct Feed;
@@ -1804,6 +1807,32 @@ struct Feed<kBF16W, VEC> {  // 64 dims per k-step: 8 + 8 per lane
   __device__ static void mfma(const T& q, const T& x, floatx4& acc) {
     Feed<kBF16, VEC>::mfma(q.a, x.a, acc);
     Feed<kBF16, VEC>::mfma(q.b, x.b, acc);
+  }
+};
+
+// Four values of a row of d, zeros past it, every load inside it and none under
+// a condition.
+__device__ inline floatx4 load_padded(const float* row, int k, int d) {
+  floatx4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = row[min(k + e, d - 1)];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = k + e < d ? v[e] : 0.f;
+  return v;
+}
+
+template <>
+struct Feed<kF32P, true> {
+  static constexpr int KS = 32, SUBW = 4;
+  typedef float XE;
+  typedef float QE;
+  typedef F32x2 T;
+  __device__ static T load(const float* row, int k, int d) {
+    return T{__builtin_bit_cast(float4, load_padded(row, k, d)),
+             __builtin_bit_cast(float4, load_padded(row, k + 16, d))};
+  }
+  __device__ static void mfma(const T& q, const T& x, floatx4& acc) {
+    Feed<kF32W, true>::mfma(q, x, acc);
   }
 };
 
@@ -2260,14 +2289,19 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
     const int u = tid + 256 * j;
     const int pc = min(u >> 7, NPC - 1), r = (u >> 3) & 15, part = u & 7;
     const int e = min(16 * pc + r, np - 1);
-    qsrc[j] = Q + int64_t(sh.lq[e]) * d + part * (16 / int(sizeof(QE)));
+    qsrc[j] = Q + int64_t(sh.lq[e]) * d + (FMT == kF32P ? 0 : part * (16 / int(sizeof(QE))));
     qdst[j] = pc * kWgQBlk + r * kWgQRow +
               (FMT == kF32S ? (part & 3) * 16 + (part >> 2) * 8 : part * 16);
   }
   floatx4 sg[2][NCH];
   auto stage_load = [&](int k, floatx4 (&dst)[NCH]) {
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) dst[j] = *reinterpret_cast<const floatx4*>(qsrc[j] + k * F::KS);
+    for (int j = 0; j < NCH; ++j) {
+      if constexpr (FMT == kF32P)
+        dst[j] = load_padded(qsrc[j], k * F::KS + 4 * (tid & 7), d);
+      else
+        dst[j] = *reinterpret_cast<const floatx4*>(qsrc[j] + k * F::KS);
+    }
   };
   auto stage_store = [&](int slot, const floatx4 (&src)[NCH]) {
 #pragma unroll
@@ -2402,7 +2436,7 @@ __global__ __launch_bounds__(256, 2) void rerank_wg_kernel(
   const int4 td = reinterpret_cast<const int4*>(tiles)[tile];
   const int32_t j = td.x, row0 = td.y, rows_here = td.w;
   const int32_t plo = cstart[j], phi = cstart[j + 1];
-  const int nsteps = d / F::KS;
+  const int nsteps = (d + F::KS - 1) / F::KS;
   WgRows<F> xr;
   {
     constexpr int kChunk = 2048 / int(sizeof(XE));  // elements per (block, k-step)
@@ -2583,10 +2617,10 @@ __global__ __launch_bounds__(256) void pair_score_kernel(
   const int32_t j = uni(pr.j), a = uni(pr.s), en = a + uni(pr.len);
   const int32_t b = (a >> 4) + int32_t(blockIdx.x) * 4 + wave;  // row block of the cluster
   if (j < 0 || 16 * b >= en) return;
-  const int32_t nsteps = d / F::KS;
+  const int32_t nsteps = (d + F::KS - 1) / F::KS;
   // tblk holds the first block of every 128-row tile; a cluster's are consecutive
   const XE* x0 = static_cast<const XE*>(Xv) + (int64_t(uni(tblk[tile_base[j]])) + b) * nsteps * (2 * kHalf);
-  const QE* q0 = static_cast<const QE*>(Qv) + (t / c) * d + F::SUBW * s;
+  const QE* q0 = static_cast<const QE*>(Qv) + (t / c) * d;
   T x[kPairRing], y[kPairRing];
   auto load = [&](int k, int u) {
     const int kk = min(k, nsteps - 1);
@@ -2594,7 +2628,7 @@ __global__ __launch_bounds__(256) void pair_score_kernel(
     const floatx4 h0 = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p));
     const floatx4 h1 = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p + kHalf));
     x[u] = T{__builtin_bit_cast(decltype(T::a), h0), __builtin_bit_cast(decltype(T::b), h1)};
-    y[u] = F::load(q0, kk * F::KS, d);
+    y[u] = F::load(q0, kk * F::KS + F::SUBW * s, d);
   };
   floatx4 acc{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -2755,7 +2789,7 @@ __device__ inline void split_bf16x8(const float4& a, const float4& b, bf16x8& hi
 // The first l1_blocks workgroups (a multiple of 8) instead run the layer-1
 // locate (l1_item) of 256 items each: both only need the hash kernel's
 // output, so one launch runs them side by side.
-template <bool SPLIT>
+template <bool SPLIT, bool PAD>
 __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
     const void* __restrict__ Qv, int64_t nq, const void* __restrict__ Cv, int32_t C, int32_t d,
     float* __restrict__ rs, L1Args la, unsigned l1_blocks) {
@@ -2799,12 +2833,15 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       if constexpr (SPLIT) {
-        const float4* qa = reinterpret_cast<const float4*>(qsrc[j] + kc * KCH);
-        const float4* ca = reinterpret_cast<const float4*>(csrc[j] + kc * KCH);
-        fa4[j][0] = qa[0];
-        fa4[j][1] = qa[1];
-        fb4[j][0] = ca[0];
-        fb4[j][1] = ca[1];
+        // PAD, d a multiple of 4: a float4 lies inside the row or past it (zeros)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int at = kc * KCH + lc + 4 * h, back = PAD ? max(at - (d - 4), 0) : 0;
+          const float4 a = *reinterpret_cast<const float4*>(qsrc[j] + kc * KCH + 4 * h - back);
+          const float4 b = *reinterpret_cast<const float4*>(csrc[j] + kc * KCH + 4 * h - back);
+          fa4[j][h] = !PAD || at < d ? a : float4{0.f, 0.f, 0.f, 0.f};
+          fb4[j][h] = !PAD || at < d ? b : float4{0.f, 0.f, 0.f, 0.f};
+        }
       } else {
         ra[j] = *reinterpret_cast<const bf16x8*>(qsrc[j] + kc * KCH);
         rb[j] = *reinterpret_cast<const bf16x8*>(csrc[j] + kc * KCH);
@@ -2835,7 +2872,7 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int nk = d / KCH;
+  const int nk = (d + KCH - 1) / KCH;
   gload(0);
   lstore();
   __syncthreads();
@@ -2918,7 +2955,7 @@ __global__ __launch_bounds__(256) void l1_small_kernel(const void* __restrict__ 
   const int32_t c0 = int32_t(t % ntc) * 16;
   const E* qr = static_cast<const E*>(Qv) + min(q0 + i, nq - 1) * d + 8 * s;
   const E* cr = static_cast<const E*>(Cv) + int64_t(min(c0 + i, C - 1)) * d + 8 * s;
-  const int32_t nk = d / 32, k0 = wave * nk / 4, k1 = (wave + 1) * nk / 4;
+  const int32_t nk = (d + 31) / 32, k0 = wave * nk / 4, k1 = (wave + 1) * nk / 4;
   floatx4 acc{0.f, 0.f, 0.f, 0.f};
   constexpr int U = SPLIT ? 4 : 8;
   for (int32_t kb = k0; kb < k1; kb += U) {
@@ -2926,11 +2963,18 @@ __global__ __launch_bounds__(256) void l1_small_kernel(const void* __restrict__ 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int32_t o = 32 * min(kb + u, k1 - 1);
-      x[u][0] = *reinterpret_cast<const floatx4*>(qr + o);
-      y[u][0] = *reinterpret_cast<const floatx4*>(cr + o);
-      if (SPLIT) {
-        x[u][1] = *reinterpret_cast<const floatx4*>(qr + o + 4);
-        y[u][1] = *reinterpret_cast<const floatx4*>(cr + o + 4);
+      if constexpr (SPLIT) {  // d a multiple of 4: a float4 lies inside the row or past it
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int32_t at = o + 8 * s + 4 * h, back = max(at - (d - 4), 0);
+          const floatx4 a = *reinterpret_cast<const floatx4*>(qr + o + 4 * h - back);
+          const floatx4 b = *reinterpret_cast<const floatx4*>(cr + o + 4 * h - back);
+          x[u][h] = at < d ? a : floatx4{0.f, 0.f, 0.f, 0.f};
+          y[u][h] = at < d ? b : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      } else {
+        x[u][0] = *reinterpret_cast<const floatx4*>(qr + o);
+        y[u][0] = *reinterpret_cast<const floatx4*>(cr + o);
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -4818,7 +4862,7 @@ bool launch_score_wg(const Index& ix, bool bf16, const int32_t* cstart, const in
                      float* sbuf, int32_t rcap, int npcm, const uint32_t* pmask, int32_t mw,
                      uint32_t* bkey, int32_t nbcap, bool split, hipStream_t st) {
   if (bf16 ? !(ix.d % 64 == 0 && ix.Xbt)
-           : !(ix.d % 32 == 0 && ix.Xt && (reinterpret_cast<uintptr_t>(Q) & 15) == 0))
+           : !(ix.Xt && (ix.d % 32 != 0 || (reinterpret_cast<uintptr_t>(Q) & 15) == 0)))
     return false;
 #define LIDER_WG(FMT, X, QP)                                                            \
   {                                                                                     \
@@ -4839,6 +4883,8 @@ bool launch_score_wg(const Index& ix, bool bf16, const int32_t* cstart, const in
     launch_wg_n<kF32S, 8>(ix, ix.Xt, Q, cstart, wl, pairs, c, sbuf, rcap, pmask, mw, bkey, nbcap, st);
   else if (bf16)
     LIDER_WG(kBF16W, (const void*)ix.Xbt, (const void*)Qb)
+  else if (ix.d % 32 != 0)
+    LIDER_WG(kF32P, (const void*)ix.Xt, (const void*)Q)
   else
     LIDER_WG(kF32W, (const void*)ix.Xt, (const void*)Q)
 #undef LIDER_WG
@@ -4854,6 +4900,9 @@ void launch_pair_scores(const Index& ix, bool bf16, int64_t np, const Pair* pair
   if (bf16)
     hipLaunchKernelGGL(pair_score_kernel<kBF16W>, grid, dim3(256), 0, st, (const void*)ix.Xbt, ix.d,
                        pairs, c, (const void*)Qb, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
+  else if (ix.d % 32 != 0)
+    hipLaunchKernelGGL(pair_score_kernel<kF32P>, grid, dim3(256), 0, st, (const void*)ix.Xt, ix.d,
+                       pairs, c, (const void*)Q, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
   else
     hipLaunchKernelGGL(pair_score_kernel<kF32W>, grid, dim3(256), 0, st, (const void*)ix.Xt, ix.d,
                        pairs, c, (const void*)Q, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
@@ -4960,7 +5009,9 @@ void launch_l1_gemm_mb(const Index& ix, bool fp8, int64_t nq, const float* Q,
 // aligned): the split product of the fp32 queries and centroids instead.
 void launch_l1_gemm_bf16(const Index& ix, int64_t nq, const __hip_bfloat16* Qb, float* rs,
                          hipStream_t st, const L1Args* la = nullptr, const float* Qf = nullptr) {
-  if (ix.d % kLdsK == 0 && nq <= kSmallBatch) {
+  // the small tiles also where the large ones would leave three of four CUs idle
+  const int64_t nbig = (nq + 127) / 128 * ((ix.C + 127) / 128);
+  if ((Qf || ix.d % kLdsK == 0) && (nq <= kSmallBatch || 4 * nbig <= ix.n_cu)) {
     const unsigned l1b = la ? unsigned((la->nq * la->H + 255) / 256) : 0u;
     const dim3 grid(l1b + unsigned((nq + 15) / 16 * ((ix.C + 15) / 16)));
     if (Qf)
@@ -4971,15 +5022,17 @@ void launch_l1_gemm_bf16(const Index& ix, int64_t nq, const __hip_bfloat16* Qb, 
                          (const void*)ix.cent_l1_b, ix.C, ix.d, rs, la ? *la : L1Args{}, l1b);
     return;
   }
-  if (ix.d % kLdsK == 0) {
-    const int64_t nblk = (nq + 127) / 128 * ((ix.C + 127) / 128);
+  if (Qf || ix.d % kLdsK == 0) {
     const unsigned l1b = la ? unsigned((la->nq * la->H + 255) / 256 + 7) / 8 * 8 : 0u;
-    const dim3 grid(l1b + unsigned((nblk + 7) / 8 * 8));
-    if (Qf)
-      hipLaunchKernelGGL(l1_gemm_lds_kernel<true>, grid, dim3(256), 0, st, (const void*)Qf, nq,
+    const dim3 grid(l1b + unsigned((nbig + 7) / 8 * 8));
+    if (Qf && ix.d % 32 != 0)
+      hipLaunchKernelGGL((l1_gemm_lds_kernel<true, true>), grid, dim3(256), 0, st, (const void*)Qf, nq,
+                         (const void*)ix.cent_l1, ix.C, ix.d, rs, la ? *la : L1Args{}, l1b);
+    else if (Qf)
+      hipLaunchKernelGGL((l1_gemm_lds_kernel<true, false>), grid, dim3(256), 0, st, (const void*)Qf, nq,
                          (const void*)ix.cent_l1, ix.C, ix.d, rs, la ? *la : L1Args{}, l1b);
     else
-      hipLaunchKernelGGL(l1_gemm_lds_kernel<false>, grid, dim3(256), 0, st, (const void*)Qb, nq,
+      hipLaunchKernelGGL((l1_gemm_lds_kernel<false, false>), grid, dim3(256), 0, st, (const void*)Qb, nq,
                          (const void*)ix.cent_l1_b, ix.C, ix.d, rs, la ? *la : L1Args{}, l1b);
     return;
   }
@@ -5024,7 +5077,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
   Plan p = make_plan(ix, nq, k, c, r, o);
   // queries that 16-byte loads cannot read take the kernels that do without
   const bool q16 = (reinterpret_cast<uintptr_t>(Q) & 15) == 0;
-  p.small = p.small && (q16 || o.precision == LIDER_BF16);
+  p.small = p.small && (q16 || o.precision == LIDER_BF16 || ix.d % 32 != 0);
   if (ws_bytes < p.total)
     return set_error(LIDER_EINVAL, "workspace too small: need " + std::to_string(p.total) +
                                        " bytes, got " + std::to_string(ws_bytes));
@@ -5072,9 +5125,12 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
   // written by the hash kernel.
   const bool l1b = !fp8 && (o.l1_dense == 0 || o.l1_dense >= 2) && ix.cent_l1_b;
   // the split bf16 product (three MFMAs per fragment pair) when c > 1 or asked
-  // for; it reads the fp32 queries with 16-byte loads
-  const bool split = l1b && ix.d % kLdsK == 0 && (reinterpret_cast<uintptr_t>(Q) & 15) == 0 &&
-                     (o.l1_dense == 3 || (o.l1_dense == 0 && c > 1));
+  // for, and where d is not a multiple of 64, which the plain product's staged
+  // form needs (100 dimensions, 127 centroids, 777 queries: fp32 product 17 us,
+  // split 4); it
+  // reads the fp32 queries with 16-byte loads
+  const bool split = p.l1_dense_rows && ix.d % 4 == 0 && q16 &&
+                     (o.l1_dense == 3 || (o.l1_dense == 0 && (c > 1 || ix.d % kLdsK != 0)));
   mark(0);
   // the hash launch also clears the counters (it writes no status: digits are clamped)
   const HashZero zr{ctr, int32_t(kCtrWords), ccount, cfill, kCntCopies * C, 0};
@@ -5087,7 +5143,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
                   o.expand_bits > 0 ? kq : (uint64_t*)nullptr};
   // the dense bf16 product on the LDS kernel carries the layer-1 locate in its
   // launch; otherwise it has a launch of its own
-  const bool l1_fused = p.l1_dense_rows && l1b && ix.d % kLdsK == 0;
+  const bool l1_fused = split || (p.l1_dense_rows && l1b && ix.d % kLdsK == 0);
   if (l1_fused)
     launch_l1_gemm_bf16(ix, nq, qb, rs, st, &la, split ? Q : nullptr);
   else
