@@ -3959,7 +3959,7 @@ __global__ __launch_bounds__(256) void wave_select_wide_kernel(
   }
 }
 
-// Per query top K for 64 < K <= 128 by a workgroup of 256 threads with the
+// Per query top K (K <= 128) by a workgroup of 256 threads with the
 // candidates' keys in registers (n <= 256 R).  The (K+1)-th smallest of the 256
 // threads' own minima is a threshold that at least K + 1 candidates reach and
 // that about -256 ln(1 - (K+1) / 256) pass (130 for K = 100), so one look at the
@@ -4769,8 +4769,7 @@ void launch_wave_select(hipStream_t st, const Pair* pairs, const float* sbuf, in
                        (const uint32_t*)nullptr, 0);
 }
 
-// 64 < K <= 128 over at most kWideMax candidates per query, a workgroup per
-// query.
+// Most candidates per query of the workgroup selection (64 keys per thread).
 constexpr int64_t kWideMax = 16384;
 // The wave form is the faster one only for short rows and large batches (K =
 // 100, wave against workgroup: 512 candidates, 10,000 queries 71 against 87 us,
@@ -4778,7 +4777,17 @@ constexpr int64_t kWideMax = 16384;
 inline bool wide_by_block(int64_t nmax, int64_t nq) {
   return nmax <= kWideMax && (nmax > 1024 || nq <= 1024);
 }
+// K <= 64 without block keys: the wave form needs 64 or more registers per lane
+// for the keys of more than 2,048 candidates, or reads them again, and lists
+// too many for a large K (K = 64, 10,000 queries, wave against workgroup: 4,096
+// candidates 820 against 120 us, 14,400: 5,858 against 386; K = 17: 4,096: 121
+// against 100, 8,192: 191 against 173, but 14,400: 183 against 353, and 500
+// queries 68 against 30).
+inline bool narrow_by_block(int32_t K, int64_t nmax, int64_t nq, const uint32_t* bkey) {
+  return !bkey && nmax > 2048 && nmax <= kWideMax && (K > 32 || nmax <= 4096 || nq <= 1024);
+}
 
+// K <= 128 over at most kWideMax candidates per query, a workgroup per query.
 template <int MODE>
 void launch_block_wide(hipStream_t st, const Pair* pairs, const float* sbuf, int32_t rcap,
                        int32_t c, int64_t nq, int32_t K, const int64_t* off, const int32_t* perm32,
@@ -5312,7 +5321,10 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
                        ix.d, Q, nq, list, ca.scnt, ca.sthr, pairs, sbuf, p.rcap, c, ix.off,
                        H > 1 ? pmask : (const uint32_t*)nullptr, p.mw, ix.perm32, k, ids, scores);
   } else if (!bf16) {
-    if (k <= 64)
+    if (k <= 64 && narrow_by_block(k, int64_t(c) * p.rcap, nq, bkey))
+      launch_block_wide<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
+                           slist, int(H > 1), CertArgs());
+    else if (k <= 64)
       launch_wave_select<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids,
                             scores, k, slist, int(H > 1), CertArgs(), bkey, p.nbcap);
     else if (k <= 128 && wide_by_block(int64_t(c) * p.rcap, nq))
@@ -5341,7 +5353,10 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     ca.xbmax = ix.xb_bound[2];
     ca.scnt = reinterpret_cast<int32_t*>(W + p.o_scnt);
     ca.cap = int64_t(c) * p.rcap;
-    if (k <= 64)
+    if (k <= 64 && narrow_by_block(k, int64_t(c) * p.rcap, nq, bkey))
+      launch_block_wide<2>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
+                           slist, int(H > 1), ca);
+    else if (k <= 64)
       launch_wave_select<2>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
                             slist, int(H > 1), ca, bkey, p.nbcap);
     else if (k <= 128 && wide_by_block(int64_t(c) * p.rcap, nq))

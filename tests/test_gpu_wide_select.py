@@ -1,4 +1,4 @@
-"""The workgroup selection for 64 < k <= 128 and the ranking of certified lists:
+"""The workgroup selection (k <= 128) and the ranking of certified lists:
 every register count (2,048 to 16,384 candidates), the radix forms past their
 limits, exact ties at the boundary and past the list's room, several arrays,
 fewer candidates than k, against the FP64 oracle."""
@@ -36,7 +36,8 @@ def test_top_k_equals_the_oracle(H, copies, precision):
     for nq in (40, 1100):
         Qd = torch.from_numpy(Q[:nq]).cuda()
         for k, c, r in ((100, 1, 1000), (65, 1, 60), (128, 4, 500), (100, 4, 1000), (127, 8, 1000),
-                        (100, 12, 1300), (100, 12, 5000)):
+                        (100, 12, 1300), (100, 12, 5000), (17, 4, 1000), (64, 8, 1000),
+                        (33, 12, 1300)):
             ids, sc = gi.search(Qd, k, c, r, r1=12, precision=precision)
             oids, osc = oi.search(Q[:nq], k, c, r, 12)
             compare_topk(X, Q[:nq], ids.cpu().numpy(), sc.cpu().numpy(), oids, osc)
