@@ -4755,8 +4755,9 @@ void launch_wave_select(hipStream_t st, const Pair* pairs, const float* sbuf, in
     hipLaunchKernelGGL((wave_select_kernel<MODE, 32>), dim3(wgrid), dim3(256), 0, st, pairs, sbuf,
                        rcap, c, nq, K, off, perm32, ids, scores, kout, slist, drop, ca,
                        (const uint32_t*)nullptr, 0);
-  else if (nmax <= 4096)
-    hipLaunchKernelGGL((wave_select_kernel<MODE, 64>), dim3(wgrid), dim3(256), 0, st, pairs, sbuf,
+  else if ((MODE == 1 || MODE == 3) && nmax <= 4096)  // the other modes go to a workgroup here
+    hipLaunchKernelGGL((wave_select_kernel<MODE == 1 || MODE == 3 ? MODE : 1, 64>), dim3(wgrid),
+                       dim3(256), 0, st, pairs, sbuf,
                        rcap, c, nq, K, off, perm32, ids, scores, kout, slist, drop, ca,
                        (const uint32_t*)nullptr, 0);
   else if (nmax <= 6144)
@@ -4769,11 +4770,13 @@ void launch_wave_select(hipStream_t st, const Pair* pairs, const float* sbuf, in
                        (const uint32_t*)nullptr, 0);
 }
 
-// Most candidates per query of the workgroup selection (64 keys per thread).
-constexpr int64_t kWideMax = 16384;
+// Most candidates per query of the workgroup selection (128 keys per thread).
+constexpr int64_t kWideMax = 32768;
 // The wave form is the faster one only for short rows and large batches (K =
 // 100, wave against workgroup: 512 candidates, 10,000 queries 71 against 87 us,
 // 500 queries 23 against 15; 2,048 candidates, 10,000 queries 152 against 105).
+// At 31,200 candidates the radix form took 4,000 us for 6,000 queries and 397
+// for 20, the workgroup 1,194 and 52.
 inline bool wide_by_block(int64_t nmax, int64_t nq) {
   return nmax <= kWideMax && (nmax > 1024 || nq <= 1024);
 }
@@ -4782,7 +4785,8 @@ inline bool wide_by_block(int64_t nmax, int64_t nq) {
 // too many for a large K (K = 64, 10,000 queries, wave against workgroup: 4,096
 // candidates 820 against 120 us, 14,400: 5,858 against 386; K = 17: 4,096: 121
 // against 100, 8,192: 191 against 173, but 14,400: 183 against 353, and 500
-// queries 68 against 30).
+// queries 68 against 30; 31,200: 500 queries 108 against 97, 20 queries 91
+// against 50).
 inline bool narrow_by_block(int32_t K, int64_t nmax, int64_t nq, const uint32_t* bkey) {
   return !bkey && nmax > 2048 && nmax <= kWideMax && (K > 32 || nmax <= 4096 || nq <= 1024);
 }
@@ -4803,8 +4807,10 @@ void launch_block_wide(hipStream_t st, const Pair* pairs, const float* sbuf, int
     LIDER_BW(16);
   else if (nmax <= 8192)
     LIDER_BW(32);
-  else
+  else if (nmax <= 16384)
     LIDER_BW(64);
+  else
+    LIDER_BW(128);
 #undef LIDER_BW
 }
 

@@ -1,5 +1,5 @@
 """The workgroup selection (k <= 128) and the ranking of certified lists:
-every register count (2,048 to 16,384 candidates), the radix forms past their
+every register count (2,048 to 32,768 candidates), the radix forms past their
 limits, exact ties at the boundary and past the list's room, several arrays,
 fewer candidates than k, against the FP64 oracle."""
 import numpy as np
@@ -41,3 +41,14 @@ def test_top_k_equals_the_oracle(H, copies, precision):
             ids, sc = gi.search(Qd, k, c, r, r1=12, precision=precision)
             oids, osc = oi.search(Q[:nq], k, c, r, 12)
             compare_topk(X, Q[:nq], ids.cpu().numpy(), sc.cpu().numpy(), oids, osc)
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_past_the_workgroup_limit_equals_the_oracle(precision):
+    import torch
+    X, Q, gi, oi = _pair(n=44000)
+    Qd = torch.from_numpy(Q[:50]).cuda()
+    for k, c, r in ((100, 8, 3700), (100, 12, 5000), (64, 8, 3700), (40, 12, 5000)):
+        ids, sc = gi.search(Qd, k, c, r, r1=12, precision=precision)
+        oids, osc = oi.search(Q[:50], k, c, r, 12)
+        compare_topk(X, Q[:50], ids.cpu().numpy(), sc.cpu().numpy(), oids, osc)
