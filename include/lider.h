@@ -397,9 +397,9 @@ int lider_hash(const float* X_dev, int64_t n, int32_t d, const float* A_dev, con
                int32_t nh, double w, int32_t* out_dev, void* stream);
 
 /* One k-means assignment step (Section 3.2): assign_dev[i] = argmin_j
- * ||X[i] - cent[j]||^2 decided in FP64 (ties to the smaller j); fp32 MFMA
- * distances, FP64 recompute where the rounding-error bands of the two best
- * overlap.  X_dev [n x d], cent_dev [C x d].  Allocates temporaries;
+ * ||X[i] - cent[j]||^2 decided in FP64 (ties to the smaller j); split
+ * bf16 MFMA distances, FP64 recompute where the rounding-error bands of the two
+ * best overlap.  X_dev [n x d], cent_dev [C x d].  Allocates temporaries;
  * synchronises `stream`. */
 int lider_kmeans_assign(const float* X_dev, int64_t n, int32_t d, const float* cent_dev,
                         int32_t C, int32_t* assign_dev, void* stream);

@@ -19,6 +19,8 @@
 namespace lider {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
+// four floats at any float's address (global loads need no more alignment)
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ inline double wave_sum_f64(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -70,27 +72,28 @@ __device__ void hash_decide_wave(const float* __restrict__ xr, const float* __re
   }
 }
 
-// Projection kernel.  Block = 4 waves = 16 rows x (up to) 32 hashes, the
+// Projection kernel.  Block = NW waves = 16 rows x (up to) 32 hashes, the
 // hashes [32 y, 32 y + 32) of grid row y; the waves split the dimension range
-// (wave w owns a contiguous quarter of the 16-dimension steps).  Lane l of a
-// wave owns row / hash (l % 16) and the dimension slot s = l / 16: per step it
-// loads 4 consecutive dims [k0 + 4s, k0 + 4s + 4) of its row and of its hash
-// vectors and feeds them to 4 MFMAs (the k index of an MFMA only needs to map
-// to the same dimension on both operands).  FULL (d a multiple of 16, 16-byte
-// aligned rows): the operands of the next three steps are in flight while a
-// step's MFMAs run, with no load under a condition (which would make the
-// compiler wait for all of them each step); else those of the next one.  The
-// kernel is bound by the latency of these chains (10,000 queries x 768: 16
-// hashes 22 -> 20 us, 20 signs 28 -> 22 us, 160 hashes 87 -> 76 us against one
-// step ahead with conditional loads).  Partial projections are added in wave
-// order through LDS; the projections inside the band are listed in LDS and
-// decided by hash_decide_wave after the block's other outputs.
+// (wave w owns a contiguous share of the 16-dimension steps, the last one also
+// the dimensions past the last whole step).  Lane l of a wave owns row / hash
+// (l % 16) and the dimension slot s = l / 16: per step it loads 4 consecutive
+// dims [k0 + 4s, k0 + 4s + 4) of its row and of its hash vectors (VEC: at
+// 16-byte addresses) and feeds them to 4 MFMAs (the k index of an MFMA only
+// needs to map to the same dimension on both operands).  The operands of the
+// next steps are in flight while a step's MFMAs run, with no load under a
+// condition (which would make the compiler wait for all of them each step); a
+// wave with fewer steps than that loads each operand once.  The kernel is
+// bound by the latency of these chains (10,000 queries x 768: 16 hashes 22 ->
+// 20 us, 20 signs 28 -> 22 us, 160 hashes 87 -> 76 us against one step ahead
+// with conditional loads).  Partial projections are added in wave order
+// through LDS; the projections inside the band are listed in LDS and decided
+// by hash_decide_wave after the block's other outputs.
 // xb (nullable): the rows rounded to bf16 (round to nearest even), written by
 // the blocks of grid row 0 from the values they load anyway.  z: counters
 // the caller's later kernels need cleared, cleared by the blocks of grid row
 // 0 (status must not be among them unless clamp is set: this kernel only
 // writes status when it is not).
-template <bool VEC, bool FULL, int NW>
+template <bool VEC, int NW>
 __global__ __launch_bounds__(64 * NW) void hash_kernel(
     const float* __restrict__ X, int64_t n, int32_t d, const float* __restrict__ A,
     const float* __restrict__ bvec, const float* __restrict__ anorm, int32_t nh, double w,
@@ -121,33 +124,10 @@ __global__ __launch_bounds__(64 * NW) void hash_kernel(
   const float* a0 = A + int64_t(h0) * d;
   const float* a1 = A + int64_t(h1) * d;
   const bool two = nhc > 16;
-  __hip_bfloat16* xbr = (xb && blockIdx.y == 0 && row0 + i < n) ? xb + (row0 + i) * d : nullptr;
   doublex4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
   float ss = 0.f;
-  const int nk = (d + 15) / 16;
+  const int nk = d / 16;  // whole steps
   const int k0s = wave * nk / NW, k1s = (wave + 1) * nk / NW;
-  float xe[4], ae[4], be[4] = {0.f, 0.f, 0.f, 0.f};
-  auto load = [&](int ks, float* xo, float* ao, float* bo) {
-    const int kk = ks * 16 + 4 * s;
-    if (VEC && kk + 3 < d) {
-      const float4 xv = *reinterpret_cast<const float4*>(xr + kk);
-      const float4 av = *reinterpret_cast<const float4*>(a0 + kk);
-      xo[0] = xv.x; xo[1] = xv.y; xo[2] = xv.z; xo[3] = xv.w;
-      ao[0] = av.x; ao[1] = av.y; ao[2] = av.z; ao[3] = av.w;
-      if (two) {
-        const float4 bv = *reinterpret_cast<const float4*>(a1 + kk);
-        bo[0] = bv.x; bo[1] = bv.y; bo[2] = bv.z; bo[3] = bv.w;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool in = kk + e < d;
-        xo[e] = in ? xr[kk + e] : 0.f;
-        ao[e] = in ? a0[kk + e] : 0.f;
-        if (two) bo[e] = in ? a1[kk + e] : 0.f;
-      }
-    }
-  };
   // one step's products (xo: this lane's four values of its row)
   auto feed = [&](const float (&xo)[4], const float (&ao)[4], const float (&bo)[4], bool second) {
 #pragma unroll
@@ -157,85 +137,89 @@ __global__ __launch_bounds__(64 * NW) void hash_kernel(
       if (second) acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(double(xo[e]), double(bo[e]), acc1, 0, 0, 0);
     }
   };
-  if constexpr (FULL) {
-    // a row past the last writes its bf16 values where row n - 1 does
-    __hip_bfloat16* xw = xb ? xb + myrow * d : nullptr;
-    auto run = [&](auto second, auto copy) {
-      constexpr bool SECOND = decltype(second)::value, COPY = decltype(copy)::value;
-      constexpr int RING = 4;
-      float4 xr4[RING], ar4[RING], br4[RING];
-      auto fetch = [&](int ks, int u) {
-        const int kk = min(ks, k1s - 1) * 16 + 4 * s;
-        xr4[u] = *reinterpret_cast<const float4*>(xr + kk);
-        ar4[u] = *reinterpret_cast<const float4*>(a0 + kk);
-        if (SECOND) br4[u] = *reinterpret_cast<const float4*>(a1 + kk);
-      };
-      auto step = [&](int ks, int u) {
-        const float xo[4] = {xr4[u].x, xr4[u].y, xr4[u].z, xr4[u].w};
-        const float ao[4] = {ar4[u].x, ar4[u].y, ar4[u].z, ar4[u].w};
-        float bo[4] = {0.f, 0.f, 0.f, 0.f};
-        if (SECOND) {
-          bo[0] = br4[u].x;
-          bo[1] = br4[u].y;
-          bo[2] = br4[u].z;
-          bo[3] = br4[u].w;
-        }
-        if (COPY) {
-          __hip_bfloat16 v4[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v4[e] = __float2bfloat16(xo[e]);
-          *reinterpret_cast<uint2*>(xw + ks * 16 + 4 * s) = *reinterpret_cast<const uint2*>(v4);
-        }
-        feed(xo, ao, bo, SECOND);
-      };
-#pragma unroll
-      for (int u = 0; u + 1 < RING; ++u) fetch(k0s + u, u);
-      int ks = k0s;
-      for (; ks + RING <= k1s; ks += RING) {
-#pragma unroll
-        for (int u = 0; u < RING; ++u) {
-          fetch(ks + u + RING - 1, (u + RING - 1) % RING);
-          __builtin_amdgcn_sched_barrier(0);
-          step(ks + u, u);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u + 1 < RING; ++u)
-        if (ks + u < k1s) step(ks + u, u);
+  // a row past the last writes its bf16 values where row n - 1 does
+  __hip_bfloat16* xw = xb ? xb + myrow * d : nullptr;
+  auto run = [&](auto second, auto copy) {
+    constexpr bool SECOND = decltype(second)::value, COPY = decltype(copy)::value;
+    constexpr int RING = NW == 1 ? 3 : 4;
+    using V4 = std::conditional_t<VEC, floatx4, floatx4u>;
+    floatx4 xr4[RING], ar4[RING], br4[RING];
+    auto fetch = [&](int ks, int u) {
+      const int kk = min(ks, k1s - 1) * 16 + 4 * s;
+      xr4[u] = *reinterpret_cast<const V4*>(xr + kk);
+      ar4[u] = *reinterpret_cast<const V4*>(a0 + kk);
+      if (SECOND) br4[u] = *reinterpret_cast<const V4*>(a1 + kk);
     };
-    if (k0s < k1s) {
-      const bool copy = xb && blockIdx.y == 0;
-      if (two && copy) run(std::true_type(), std::true_type());
-      else if (two) run(std::true_type(), std::false_type());
-      else if (copy) run(std::false_type(), std::true_type());
-      else run(std::false_type(), std::false_type());
-    }
-  } else {
-    if (k0s < k1s) load(k0s, xe, ae, be);
-    for (int ks = k0s; ks < k1s; ++ks) {
-      float xn[4], an[4], bn[4] = {0.f, 0.f, 0.f, 0.f};
-      load(ks + 1 < k1s ? ks + 1 : ks, xn, an, bn);
-      if (xbr) {
-        const int kk = ks * 16 + 4 * s;
-        if (VEC && kk + 3 < d) {
-          __hip_bfloat16 v4[4];
+    auto step = [&](int ks, int u) {
+      const float xo[4] = {xr4[u][0], xr4[u][1], xr4[u][2], xr4[u][3]};
+      const float ao[4] = {ar4[u][0], ar4[u][1], ar4[u][2], ar4[u][3]};
+      float bo[4] = {0.f, 0.f, 0.f, 0.f};
+      if (SECOND) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v4[e] = __float2bfloat16(xe[e]);
-          *reinterpret_cast<uint2*>(xbr + kk) = *reinterpret_cast<const uint2*>(v4);
+        for (int e = 0; e < 4; ++e) bo[e] = br4[u][e];
+      }
+      if (COPY) {
+        __hip_bfloat16 v4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v4[e] = __float2bfloat16(xo[e]);
+        __hip_bfloat16* at = xw + ks * 16 + 4 * s;
+        if (VEC) {
+          *reinterpret_cast<uint2*>(at) = *reinterpret_cast<const uint2*>(v4);
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (kk + e < d) xbr[kk + e] = __float2bfloat16(xe[e]);
+          for (int e = 0; e < 4; ++e) at[e] = v4[e];
         }
       }
-      feed(xe, ae, be, two);
+      feed(xo, ao, bo, SECOND);
+    };
+    const int ns = k1s - k0s;
+    if (ns < RING) {  // short rows: each operand once
+      fetch(k0s, 0);
+      if (ns > 1) fetch(k0s + 1, 1);
+      if (ns > 2) fetch(k0s + 2, 2);
+      step(k0s, 0);
+      if (ns > 1) step(k0s + 1, 1);
+      if (ns > 2) step(k0s + 2, 2);
+      return;
+    }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        xe[e] = xn[e];
-        ae[e] = an[e];
-        be[e] = bn[e];
+    for (int u = 0; u + 1 < RING; ++u) fetch(k0s + u, u);
+    int ks = k0s;
+    for (; ks + RING <= k1s; ks += RING) {
+#pragma unroll
+      for (int u = 0; u < RING; ++u) {
+        fetch(ks + u + RING - 1, (u + RING - 1) % RING);
+        __builtin_amdgcn_sched_barrier(0);
+        step(ks + u, u);
       }
     }
+#pragma unroll
+    for (int u = 0; u + 1 < RING; ++u)
+      if (ks + u < k1s) step(ks + u, u);
+  };
+  if (k0s < k1s) {
+    const bool copy = xb && blockIdx.y == 0;
+    if (two && copy) run(std::true_type(), std::true_type());
+    else if (two) run(std::true_type(), std::false_type());
+    else if (copy) run(std::false_type(), std::true_type());
+    else run(std::false_type(), std::false_type());
+  }
+  if (wave == NW - 1 && 16 * nk < d) {  // the dimensions past the last whole step
+    float xo[4], ao[4], bo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int kk = 16 * nk + 4 * s + e, at = min(kk, d - 1);
+      const float xv = xr[at], av = a0[at], bv = a1[at];
+      xo[e] = kk < d ? xv : 0.f;
+      ao[e] = kk < d ? av : 0.f;
+      bo[e] = kk < d ? bv : 0.f;
+    }
+    if (xw && blockIdx.y == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (16 * nk + 4 * s + e < d) xw[16 * nk + 4 * s + e] = __float2bfloat16(xo[e]);
+    }
+    feed(xo, ao, bo, two);
   }
   // |x|^2 of row i over this wave's dims: sum the four dimension slots
   ss += __shfl_xor(ss, 16);
@@ -341,21 +325,32 @@ int run_hash_ex(const float* X, int64_t n, int32_t d, const float* A, const floa
                    ((reinterpret_cast<uintptr_t>(A) & 15) == 0) &&
                    ((reinterpret_cast<uintptr_t>(xb) & 7) == 0);
   const dim3 grid(unsigned((n + 15) / 16), unsigned((nh + 31) / 32));
-  // few workgroups: sixteen waves each, a quarter of the chain per wave (one
-  // query, 768 dimensions, 16 hashes: 13 -> 7 us)
-  const bool few = int64_t(grid.x) * grid.y <= 256 && d >= 256;
-  if (vec && d % 16 == 0 && few)
-    hipLaunchKernelGGL((hash_kernel<true, true, 16>), grid, dim3(1024), 0, st, X, n, d, A, b, anorm,
-                       nh, w, out, status, clamp, rownorm, kind, xb, z);
-  else if (vec && d % 16 == 0)
-    hipLaunchKernelGGL((hash_kernel<true, true, 4>), grid, dim3(256), 0, st, X, n, d, A, b, anorm,
-                       nh, w, out, status, clamp, rownorm, kind, xb, z);
-  else if (vec)
-    hipLaunchKernelGGL((hash_kernel<true, false, 4>), grid, dim3(256), 0, st, X, n, d, A, b, anorm,
-                       nh, w, out, status, clamp, rownorm, kind, xb, z);
-  else
-    hipLaunchKernelGGL((hash_kernel<false, false, 4>), grid, dim3(256), 0, st, X, n, d, A, b, anorm,
-                       nh, w, out, status, clamp, rownorm, kind, xb, z);
+  // Waves per workgroup: with few workgroups the chain of a row's steps is the
+  // time, so sixteen waves share it (one query, 768 dimensions, 16 hashes: 13
+  // -> 7 us; 32 hashes have twice the sums to add up and gain nothing); with
+  // many, one wave does all of it and the LDS round and the idle lanes of the
+  // output loop go (whole call, four waves against one: 200,000 x 64, 4 hashes
+  // 81 -> 54 us; x 256, 16 hashes 143 -> 105; x 768, 4 hashes 223 -> 217;
+  // 20,000 x 768 91 against 95), two waves between (20,000 x 300, 32 hashes 73
+  // -> 69).
+  const int64_t blocks = int64_t(grid.x) * grid.y;
+#define LIDER_HASH(NW)                                                                             \
+  if (vec)                                                                                         \
+    hipLaunchKernelGGL((hash_kernel<true, NW>), grid, dim3(64 * NW), 0, st, X, n, d, A, b, anorm,  \
+                       nh, w, out, status, clamp, rownorm, kind, xb, z);                           \
+  else                                                                                             \
+    hipLaunchKernelGGL((hash_kernel<false, NW>), grid, dim3(64 * NW), 0, st, X, n, d, A, b, anorm, \
+                       nh, w, out, status, clamp, rownorm, kind, xb, z)
+  if (blocks <= 256 && d >= 512 && nh <= 16) {
+    LIDER_HASH(16);
+  } else if (blocks >= 5 * int64_t(d)) {
+    LIDER_HASH(1);
+  } else if (d <= 512 && blocks >= 2 * int64_t(d)) {
+    LIDER_HASH(2);
+  } else {
+    LIDER_HASH(4);
+  }
+#undef LIDER_HASH
   return check_hip(hipGetLastError(), "hash kernel");
 }
 

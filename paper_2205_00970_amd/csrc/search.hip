@@ -1,21 +1,24 @@
 // Batched LIDER search (Section 3.3.2) on gfx950.
 //
-//   1. E2LSH digits of every query for both layers (fp32 MFMA + FP64 edge
-//      recompute, hash.hip).
+//   1. E2LSH digits of every query for both layers (FP64 MFMA, near a bucket
+//      edge the sequential FP64 sum, hash.hip).
 //   2. Centroids retriever: key, RMI location, window of r1 centroids in its
 //      sorted order (contiguous rows of the layer-1-ordered centroid copy).
 //   3. Routing: inner products with the window centroids, top c clusters.  The
-//      set of routed clusters is decided in FP64 (an fp32 near-tie at the c-th
-//      place triggers a sequential FP64 rescoring of the window).
+//      set of routed clusters is decided in FP64 (the centroids whose score is
+//      within the product's error bound of the c-th best are rescored).
 //   4. In-cluster retrievers: per (query, routed cluster) pair the key, RMI
 //      location and window of r rows; pairs are grouped by cluster.
 //   5. Rerank (where the time goes): cluster-major; one workgroup per tile of
 //      consecutive rows of one cluster (rows are stored in sorted order, so a
 //      window is a contiguous slab) scores the tile against every pair whose
 //      window overlaps it with fp32 (or bf16) MFMA, writing each pair's window
-//      scores.  Optionally persistent over the tile list.
-//   6. Per query, top k over the union of its windows (score desc, id asc)
-//      with a radix select + bitonic sort in LDS (Section 6.2's final merge).
+//      scores.  Optionally persistent over the tile list.  Small batches score
+//      each pair's window by itself (pair_score_kernel).
+//   6. Per query, top k over the union of its windows (score desc, id asc):
+//      keys in registers, a threshold over lane or thread minima and a ranked
+//      list; a radix select + bitonic sort past their limits (Section 6.2's
+//      final merge).
 #include <hip/hip_fp8.h>
 
 #include <algorithm>
