@@ -785,8 +785,8 @@ int run_centroid_means(const float* X, int64_t n, int32_t d, const int32_t* assi
 // round, and so the centroids, are those of the plain form.  Where the bounds
 // are too wide for a single pick (values of D_i far below |x|^2), D_i itself is
 // kept for every row from then on.  200,000 x 768, 200 centroids: 61 ms as a
-// full pass and four launches per centroid, 5.1 ms as 5 lists (a full pass
-// 0.37 ms, a list's values 0.1 ms, a round 7 us, 20-40 us where it has to
+// full pass and four launches per centroid, 4.5 ms as 6 lists (a full pass
+// 0.15 ms, a list's values 0.1 ms, a round 7 us, 20-40 us where it has to
 // decide among several candidates).
 constexpr double kFFRel = 1.1920928955078125e-07;  // 2^-23 per dimension (fp32 + FP64 side)
 
