@@ -2390,28 +2390,30 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
   __builtin_amdgcn_sched_barrier(0);
   stage_store(0, sg[0]);
   __syncthreads();
-  // step K at place J of its group; rows: the rows of step K + 3 are loaded
-  auto step = [&](int J, int K, bool rows) {
-    stage_load(min(K + 2, nsteps - 1), sg[J & 1]);
+  // step K at place J of its group; rows: the rows of step K + 3 are loaded,
+  // stage: the queries of step K + 2, store: those of step K + 1 go to LDS (the
+  // last steps leave these out, or the pass would end in a wait for them)
+  auto step = [&](int J, int K, bool rows, bool stage, bool store) {
+    if (stage) stage_load(min(K + 2, nsteps - 1), sg[J & 1]);
     if (rows) xload(K + 3, xs[(J + 3) & 3]);
     __builtin_amdgcn_sched_barrier(0);
     products(xs[J], J & 1);
-    stage_store((J + 1) & 1, sg[(J + 1) & 1]);
+    if (store) stage_store((J + 1) & 1, sg[(J + 1) & 1]);
     __syncthreads();
   };
   constexpr bool kPeel = NPCM <= 2;
   int k = 0;
   for (; k + 4 < nsteps + (kPeel ? 0 : 1); k += 4) {
 #pragma unroll
-    for (int J = 0; J < 4; ++J) step(J, k + J, true);
+    for (int J = 0; J < 4; ++J) step(J, k + J, true, true, true);
   }
   if (kPeel && k + 4 == nsteps) {
 #pragma unroll
-    for (int J = 0; J < 4; ++J) step(J, k + J, J == 0);
+    for (int J = 0; J < 4; ++J) step(J, k + J, J == 0, J < 2, J < 3);
   } else {
 #pragma unroll
     for (int J = 0; J < 3; ++J)
-      if (k + J < nsteps) step(J, k + J, false);
+      if (k + J < nsteps) step(J, k + J, false, k + J + 2 < nsteps, k + J + 1 < nsteps);
   }
 }
 
