@@ -253,6 +253,7 @@ __device__ inline float key_score(uint32_t key) {
 }
 
 constexpr int kTieCap = 1024;
+constexpr int kSelMaxNT = 1024;  // largest workgroup of block_select
 
 struct SelShared {
   uint32_t hist[256];
@@ -260,8 +261,8 @@ struct SelShared {
   int32_t cnt_less, cnt_tie;
   uint32_t tie_id[kTieCap];
   int32_t tie_idx[kTieCap];
-  uint32_t red_id[8];
-  int32_t red_idx[8];
+  uint32_t red_id[kSelMaxNT / 64];  // one entry per wave
+  int32_t red_idx[kSelMaxNT / 64];
 };
 
 // Block-wide selection of the K smallest (key, id) among n candidates (ids
@@ -272,6 +273,7 @@ struct SelShared {
 template <int NT, class KeyF, class IdF>
 __device__ int block_select(int n, int K, int KP, KeyF key_of, IdF id_of, uint64_t* srt,
                             int32_t* idx, SelShared& sh) {
+  static_assert(NT % 64 == 0 && NT <= kSelMaxNT, "red_id and red_idx hold an entry per wave");
   const int tid = threadIdx.x;
   int outn;
   if (n <= K) {
