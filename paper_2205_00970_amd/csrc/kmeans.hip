@@ -929,8 +929,9 @@ __global__ __launch_bounds__(256) void ff_values_kernel(const float* __restrict_
 }
 
 // U_i <- min(U_i, |x_i|^2 + g + E), rounded up, from the assignment product's
-// best value g over the last centroids (the smallest over its groups); with
-// no product, U already holds the values.  The largest U_i.
+// best value g over the last centroids (the smallest over its groups), or +inf
+// where a part of it overflowed: such a row goes on the list, and its distances
+// decide; with no product, U already holds the values.  The largest U_i.
 __global__ __launch_bounds__(256) void ff_bound_kernel(const float4* __restrict__ part, int64_t n,
                                                        int32_t d, int32_t G,
                                                        const uint32_t* __restrict__ maxbits,
@@ -952,7 +953,11 @@ __global__ __launch_bounds__(256) void ff_bound_kernel(const float4* __restrict_
       const double b = xn * xn + double(g) + assign_err(d, xn, double(__uint_as_float(*maxbits)));
       u = float(b);
       if (double(u) < b) u = nextafterf(u, INFINITY);
-      if (u < 0.f) u = 0.f;  // a NaN stays
+      if (u < 0.f) u = 0.f;
+      // no bound where the square sum, the product or the largest |mu|
+      // overflowed (g = -inf: the product did); |x|^2 is a NaN only with one in
+      // the row, which is never a candidate
+      if (!(b < double(INFINITY)) || !(g > -INFINITY)) u = ss == ss ? INFINITY : ss;
       if (!first) u = fminf(u, U[i]);
       U[i] = u;
     } else {
