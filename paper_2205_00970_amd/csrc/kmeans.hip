@@ -156,8 +156,7 @@ __device__ inline double norm_above(float ss, int32_t d) {
 __device__ inline void assign_decide(const AssignOut& o, int64_t row, const Best& b, float ssr) {
   const double E = assign_err(o.d, norm_above(ssr, o.d), double(__uint_as_float(*o.maxbits)));
   const double gap = double(b.sv) - double(b.bv);
-  // a value of -inf is a product that overflowed, not the nearest centroid
-  if (o.C == 1 || (gap > 4.0 * E && b.bv > -INFINITY)) {
+  if (o.C == 1 || gap > 4.0 * E) {
     const int32_t bi = o.C == 1 ? 0 : b.bi;
     o.assign[row] = bi;
     if (o.prev && o.prev[row] != bi) atomicAdd(o.changed, 1);
