@@ -539,9 +539,7 @@ __global__ __launch_bounds__(256) void tile_corpus_kernel(const float* __restric
     if (!BF) {
       ss += __shfl_xor(ss, 16);
       ss += __shfl_xor(ss, 32);
-      const double gam = double(d + 2) * 5.9604644775390625e-08;
-      const float ub = float(sqrt(double(ss) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07));
-      mx = max(mx, __float_as_uint(ub) & 0x7fffffffu);
+      mx = max(mx, __float_as_uint(float(norm_above(ss, d))) & 0x7fffffffu);
     }
   }
   if (!BF) {

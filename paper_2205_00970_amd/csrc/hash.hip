@@ -234,7 +234,6 @@ __global__ __launch_bounds__(64 * NW) void hash_kernel(
   if (threadIdx.x == 0) qn = 0;
   __syncthreads();
   const double u = 1.1102230246251565e-16;  // 2^-53
-  const double gam = double(d + 2) * 5.9604644775390625e-08;
   for (int o = threadIdx.x; o < 16 * nhc; o += 64 * NW) {
     const int ri = o / nhc, hl = o - ri * nhc, hash = hb + hl;
     const int64_t row = row0 + ri;
@@ -246,7 +245,7 @@ __global__ __launch_bounds__(64 * NW) void hash_kernel(
       ssr += pss[v][ri];
       sv += part[v][hl][ri];
     }
-    const double xn = sqrt(double(ssr) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07);
+    const double xn = norm_above(ssr, d);
     if (rownorm && hash == 0) rownorm[row] = float(xn * (1.0 + 9.5367431640625e-07));
     const int64_t oi = row * nh + hash;
     // sum |a_i x_i| <= |a| |x|; the last term covers fp32 subnormal inputs

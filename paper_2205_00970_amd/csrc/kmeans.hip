@@ -76,9 +76,7 @@ __global__ __launch_bounds__(256) void cent_split_kernel(const float* __restrict
   if (lane == 0) {
     cnorm[j] = j < C ? s : INFINITY;
     if (j < C) {
-      const double gam = double(d + 2) * 5.9604644775390625e-08;
-      float ub = float(sqrt(double(s) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07));
-      atomicMax(maxbits, __float_as_uint(ub));
+      atomicMax(maxbits, __float_as_uint(float(norm_above(s, d))));
     }
   }
 }
@@ -143,12 +141,6 @@ __device__ inline double assign_err(int32_t d, double xn, double M) {
          6.0 * sqrt(double(d)) * 1.1754943508222875e-38 * (xn + M) +
          double(d + 2) * 8.881784197001252e-16 * (xn + M) * (xn + M) +
          6.0 * double(d) * 7.888609052210118e-31;
-}
-
-// Upper bound of |x| from its fp32 square sum.
-__device__ inline double norm_above(float ss, int32_t d) {
-  const double gam = double(d + 2) * 5.9604644775390625e-08;
-  return sqrt(double(ss) * (1.0 + 2.0 * gam)) * (1.0 + 9.5367431640625e-07);
 }
 
 // Decides one point from its best and second-best value and |x|^2 (fp32), or

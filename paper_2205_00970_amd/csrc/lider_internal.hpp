@@ -204,6 +204,16 @@ __host__ __device__ inline double dot_err_coef(int d) {
   return double(d + 2) * (5.9604644775390625e-08 /* 2^-24 */ + 2.220446049250313e-16);
 }
 
+// Upper bound of |x| from the square sum of its d elements in fp32, in any
+// order.  The last term covers squares and partial sums below 2^-126, which are
+// rounded absolutely or flushed (elements below 2^-63; at most 4 d 2^-126 in
+// all): without it the bound of a row of such elements is 0.
+__host__ __device__ inline double norm_above(float ss, int32_t d) {
+  const double gam = double(d + 2) * 5.9604644775390625e-08;  // 2^-24
+  return (sqrt(double(ss) * (1.0 + 2.0 * gam)) + sqrt(double(d)) * 2.168404344971009e-19 /* 2^-62 */) *
+         (1.0 + 9.5367431640625e-07);
+}
+
 inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
 // ----------------------------------------------------------------- the index
