@@ -2,11 +2,12 @@
 //
 // Assignment = argmin_j |x - mu_j|^2 decided in FP64 with ties to the smaller
 // j.  The distances come from a split bf16 MFMA product (g_j = |mu_j|^2 -
-// 2 x.mu_j, the |x|^2 term is common to all j); when the best and second-best
+// 2 x.mu_j, the |x|^2 term is common to all j).  When the best and second-best
 // values are closer than a rigorous rounding-error bound allows, the point is
-// queued and all its distances are recomputed sequentially in FP64 (sum over
-// dimensions of (x_l - mu_l)^2, no contraction), which reproduces the FP64
-// definition.
+// queued for the same product in FP64 (assign_f64_kernel); one that its bound
+// cannot decide either (ties, in effect) has all its distances formed
+// sequentially in FP64 (sum over dimensions of (x_l - mu_l)^2, no contraction),
+// which is the definition itself.
 //
 // Update = FP64 mean of each cluster's members summed in ascending id order,
 // rounded once to fp32; an empty cluster keeps its centroid.
@@ -48,10 +49,12 @@ __device__ inline void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo) {
 // h part and the l part, 1 KB each, lane i + 16 s holding dims [8 s, 8 s + 8)
 // of centroid i (zeros past d and past C).  One wave per centroid; it also
 // writes |mu_j|^2 in fp32 (+inf for the centroids past C, which are never
-// nearest) and an upper bound of max_j |mu_j| (as float bits, atomicMax).
+// nearest) and in FP64, and an upper bound of max_j |mu_j| (as float bits,
+// atomicMax).
 __global__ __launch_bounds__(256) void cent_split_kernel(const float* __restrict__ cent, int32_t C,
                                                          int32_t d, bf16x8* __restrict__ out,
                                                          float* __restrict__ cnorm,
+                                                         double* __restrict__ cn64,
                                                          uint32_t* __restrict__ maxbits) {
   const int lane = threadIdx.x & 63;
   const int64_t j = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
@@ -59,12 +62,14 @@ __global__ __launch_bounds__(256) void cent_split_kernel(const float* __restrict
   const float* mu = cent + j * d;
   bf16x8* o = out + (j >> 4) * (int64_t(nk) * 128) + (j & 15);
   float s = 0.f;
+  double s64 = 0.0;
   for (int32_t u = lane; u < 4 * nk; u += 64) {  // eight dims per lane
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       v[e] = j < C && 8 * u + e < d ? mu[8 * u + e] : 0.f;
       s += v[e] * v[e];
+      s64 += double(v[e]) * double(v[e]);
     }
     bf16x8 h, l;
     split8(v, h, l);
@@ -72,9 +77,13 @@ __global__ __launch_bounds__(256) void cent_split_kernel(const float* __restrict
     q[0] = h;
     q[64] = l;
   }
-  for (int x = 32; x > 0; x >>= 1) s += __shfl_xor(s, x);
+  for (int x = 32; x > 0; x >>= 1) {
+    s += __shfl_xor(s, x);
+    s64 += __shfl_xor(s64, x);
+  }
   if (lane == 0) {
     cnorm[j] = j < C ? s : INFINITY;
+    cn64[j] = j < C ? s64 : double(INFINITY);
     if (j < C) {
       atomicMax(maxbits, __float_as_uint(float(norm_above(s, d))));
     }
@@ -522,50 +531,215 @@ __global__ __launch_bounds__(256) void assign_merge_kernel(const float4* __restr
   assign_decide(o, row, v, ss);
 }
 
-// FP64 recompute for queued points: one block per point, threads over
-// centroids, each distance a sequential sum without contraction.
-__global__ __launch_bounds__(256) void assign_fixup_kernel(
-    const float* __restrict__ X, int32_t d, const float* __restrict__ cent, int32_t C,
-    int32_t* __restrict__ assign, const int32_t* __restrict__ prev, int32_t* __restrict__ changed,
-    const int64_t* __restrict__ amb, const int32_t* __restrict__ amb_count) {
+// Second decision of the queued points: the values g_j by FP64 MFMA
+// (v_mfma_f64_16x16x4f64), whose bound is some 2^-28 of the split product's, so
+// that only ties remain.  How many points the first bound leaves is the data's
+// choice (120,000 x 768, 1,000 centroids: none of a mixture of separated blobs,
+// tens of thousands of unit rows with a common mean); the sequential FP64 sums of all C
+// distances would then cost many times the product itself, while this one is
+// bounded by 2 C d FP64 operations a point at the MFMA rate (120,000 x 768,
+// 1,000 centroids, whole call: isotropic rows 17.3 ms with the sequential sums
+// alone, 1.14 ms now; unit rows with a common mean 51.7 and 1.84; d = 64: 0.29
+// and 0.18, 0.48 and 0.19).
+// A workgroup of 16 waves takes 32 points (16 while the queue fits the chip that
+// way, for the shorter chain) and sweeps 512 centroids at a time, 32 per wave;
+// operands straight from L2, one step of 16 dimensions ahead: 32 MFMAs of 64
+// cycles hide them.  Lane (i, s) feeds dims [4 s, 4 s + 4) of a step to four
+// MFMAs, as in the hash kernel.
+// |g - (|mu|^2 - 2 x.mu)| <= (d + 2) 2^-53 (|x| + M)^2 (the fp32 x fp32 products
+// are exact) and the definition's own sum is within (d + 3) 2^-53 (|x| + M)^2,
+// so values further apart than 4 (d + 3) 2^-53 (|x| + M)^2 are in the
+// definition's order; 16 (d + 8) is used.  The other term covers fp32 subnormals
+// flushed on the way into FP64.
+constexpr int kF64Waves = 16, kF64Grid = 512;
+
+struct Best64 {
+  double bv, sv;
+  int32_t bi;
+};
+
+// The definition: a workgroup's threads over the centroids, each distance a
+// sequential sum without contraction, the smallest one's centroid (ties to the
+// smaller id) left in sj[0].
+template <int NT>
+__device__ void assign_sequential(const float* __restrict__ xr, int32_t d,
+                                  const float* __restrict__ cent, int32_t C, double* sd, int32_t* sj) {
 #pragma clang fp contract(off)
-  __shared__ double sd[256];
-  __shared__ int32_t sj[256];
-  const int32_t cnt = *amb_count;
-  for (int32_t t = blockIdx.x; t < cnt; t += gridDim.x) {
-    const int64_t row = amb[t];
-    const float* xr = X + row * d;
-    double bd = INFINITY;
-    int32_t bj = 0x7fffffff;
-    for (int32_t j = threadIdx.x; j < C; j += blockDim.x) {
-      const float* mu = cent + int64_t(j) * d;
-      double acc = 0.0;
-      for (int l = 0; l < d; ++l) {
-        double df = double(xr[l]) - double(mu[l]);
-        acc = acc + df * df;
-      }
-      if (acc < bd) {
-        bd = acc;
-        bj = j;
+  const int tid = threadIdx.x;
+  double bd = INFINITY;
+  int32_t bj = 0x7fffffff;
+  for (int32_t j = tid; j < C; j += NT) {
+    const float* mu = cent + int64_t(j) * d;
+    double acc = 0.0;
+    for (int l = 0; l < d; ++l) {
+      double df = double(xr[l]) - double(mu[l]);
+      acc = acc + df * df;
+    }
+    if (acc < bd) {
+      bd = acc;
+      bj = j;
+    }
+  }
+  sd[tid] = bd;
+  sj[tid] = bj;
+  __syncthreads();
+#pragma unroll 1
+  for (int o = NT / 2; o > 0; o >>= 1) {
+    if (tid < o) {
+      double od = sd[tid + o];
+      int32_t oj = sj[tid + o];
+      if (od < sd[tid] || (od == sd[tid] && oj < sj[tid])) {
+        sd[tid] = od;
+        sj[tid] = oj;
       }
     }
-    sd[threadIdx.x] = bd;
-    sj[threadIdx.x] = bj;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (threadIdx.x < o) {
-        double od = sd[threadIdx.x + o];
-        int32_t oj = sj[threadIdx.x + o];
-        if (od < sd[threadIdx.x] || (od == sd[threadIdx.x] && oj < sj[threadIdx.x])) {
-          sd[threadIdx.x] = od;
-          sj[threadIdx.x] = oj;
+  }
+}
+
+__device__ inline Best64 best_merge(const Best64& a, const Best64& b) {
+  Best64 r;
+  r.sv = fmin(fmin(a.sv, b.sv), fmax(a.bv, b.bv));
+  r.bi = b.bv < a.bv ? b.bi : a.bi;
+  r.bv = fmin(a.bv, b.bv);
+  return r;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(64 * kF64Waves) void assign_f64_kernel(
+    const float* __restrict__ X, const float* __restrict__ cent, const double* __restrict__ cn64,
+    AssignOut o) {
+  typedef double doublex4 __attribute__((ext_vector_type(4)));
+  __shared__ double sbv[kF64Waves][32], ssv[kF64Waves][32], sss[32];
+  __shared__ int32_t sbi[kF64Waves][32];
+  __shared__ double sd[64 * kF64Waves];
+  __shared__ int32_t sj[64 * kF64Waves];
+  __shared__ int64_t open[32];  // points that the bound leaves open
+  __shared__ int32_t nopen;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = lane & 15, s = lane >> 4;
+  const int32_t cnt = *o.amb_count, d = o.d, C = o.C;
+  const bool two = cnt > 16 * kF64Grid;
+  const int32_t per = two ? 32 : 16;
+  const double M = double(__uint_as_float(*o.maxbits));
+  // four values of a row of d from dim kk on, zeros past it, every load inside it
+  auto load4 = [&](const float* row, int32_t kk) {
+    float4 v;
+    if (VEC) {  // d a multiple of 4: a float4 lies inside the row or past it
+      v = *reinterpret_cast<const float4*>(row + min(kk, d - 4));
+      if (kk >= d) v = float4{0.f, 0.f, 0.f, 0.f};
+    } else {
+      const float w[4] = {row[min(kk, d - 1)], row[min(kk + 1, d - 1)], row[min(kk + 2, d - 1)],
+                          row[min(kk + 3, d - 1)]};
+      v.x = kk < d ? w[0] : 0.f;
+      v.y = kk + 1 < d ? w[1] : 0.f;
+      v.z = kk + 2 < d ? w[2] : 0.f;
+      v.w = kk + 3 < d ? w[3] : 0.f;
+    }
+    return v;
+  };
+  for (int64_t t0 = int64_t(blockIdx.x) * per; t0 < cnt; t0 += int64_t(kF64Grid) * per) {
+    const float* xr[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+      xr[a] = X + o.amb[min(t0 + (two ? 16 * a : 0) + i, int64_t(cnt) - 1)] * d;
+    bool any = false;  // this wave has columns (wave-uniform)
+    for (int32_t c0 = 32 * wave; c0 < C; c0 += 32 * kF64Waves) {
+      const float* cr[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) cr[b] = cent + int64_t(min(c0 + 16 * b + i, C - 1)) * d;
+      doublex4 acc[2][2];
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+      float4 nx[2], nc[2];
+      auto fetch = [&](int32_t k0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          nx[u] = load4(xr[u], k0 + 4 * s);
+          nc[u] = load4(cr[u], k0 + 4 * s);
+        }
+      };
+      if (VEC) fetch(0);
+      for (int32_t k0 = 0; k0 < d; k0 += 16) {
+        if (!VEC) fetch(k0);  // scalar loads a step ahead would spill
+        const float x[2][4] = {{nx[0].x, nx[0].y, nx[0].z, nx[0].w}, {nx[1].x, nx[1].y, nx[1].z, nx[1].w}};
+        const float y[2][4] = {{nc[0].x, nc[0].y, nc[0].z, nc[0].w}, {nc[1].x, nc[1].y, nc[1].z, nc[1].w}};
+        if (VEC) fetch(k0 + 16);  // past the row: zeros
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double x0 = double(x[0][e]), x1 = double(x[1][e]);
+          const double y0 = double(y[0][e]), y1 = double(y[1][e]);
+          acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
+          acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
+          if (two) {
+            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, acc[1][1], 0, 0, 0);
+          }
         }
       }
-      __syncthreads();
+      // result layout: element e of lane (i, s) is point 16 a + s + 4 e, centroid
+      // c0 + 16 b + i
+      const double n0 = c0 + i < C ? cn64[c0 + i] : double(INFINITY);
+      const double n1 = c0 + 16 + i < C ? cn64[c0 + 16 + i] : double(INFINITY);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double inf = double(INFINITY);
+          Best64 v = best_merge(Best64{n0 - 2.0 * acc[a][0][e], inf, c0 + i},
+                                Best64{n1 - 2.0 * acc[a][1][e], inf, c0 + 16 + i});
+#pragma unroll
+          for (int x = 1; x < 16; x <<= 1)
+            v = best_merge(v, Best64{__shfl_xor(v.bv, x), __shfl_xor(v.sv, x), __shfl_xor(v.bi, x)});
+          const int r = 16 * a + s + 4 * e;
+          if (i == 0) {  // this wave's own entries
+            if (any) v = best_merge(Best64{sbv[wave][r], ssv[wave][r], sbi[wave][r]}, v);
+            sbv[wave][r] = v.bv;
+            ssv[wave][r] = v.sv;
+            sbi[wave][r] = v.bi;
+          }
+        }
+      any = true;
     }
-    if (threadIdx.x == 0) {
-      assign[row] = sj[0];
-      if (prev && prev[row] != sj[0]) atomicAdd(changed, 1);
+    if (tid == 0) nopen = 0;
+    {  // |x|^2: half a wave per point
+      const int r = tid >> 5;
+      const float* x = X + o.amb[min(t0 + r, int64_t(cnt) - 1)] * d;
+      double q = 0.0;
+#pragma unroll 4
+      for (int32_t l = tid & 31; l < d; l += 32) q += double(x[l]) * double(x[l]);
+      for (int h = 16; h > 0; h >>= 1) q += __shfl_xor(q, h);
+      if ((tid & 31) == 0) sss[r] = q;
+    }
+    __syncthreads();
+    if (tid < per && t0 + tid < cnt) {
+      Best64 v{sbv[0][tid], ssv[0][tid], sbi[0][tid]};
+      for (int w = 1; w < kF64Waves && 32 * w < C; ++w)
+        v = best_merge(v, Best64{sbv[w][tid], ssv[w][tid], sbi[w][tid]});
+      const int64_t row = o.amb[t0 + tid];
+      const double r = sqrt(sss[tid]) * (1.0 + 9.5367431640625e-07) + M;
+      const double E = 16.0 * double(d + 8) * 1.1102230246251565e-16 * r * r +
+                       8.0 * sqrt(double(d)) * 1.1754943508222875e-38 * r;
+      if (v.sv - v.bv > E) {  // false with a NaN or an infinite bound
+        o.assign[row] = v.bi;
+        if (o.prev && o.prev[row] != v.bi) atomicAdd(o.changed, 1);
+      } else {
+        open[atomicAdd(&nopen, 1)] = row;
+      }
+    }
+    __syncthreads();
+    const int32_t no = nopen;
+    for (int32_t t = 0; t < no; ++t) {
+      const int64_t row = open[t];
+      assign_sequential<64 * kF64Waves>(X + row * d, d, cent, C, sd, sj);
+      if (tid == 0) {
+        o.assign[row] = sj[0];
+        if (o.prev && o.prev[row] != sj[0]) atomicAdd(o.changed, 1);
+      }
+      __syncthreads();
     }
     __syncthreads();
   }
@@ -580,20 +754,22 @@ static int32_t asg_groups(int64_t n, int32_t C) {
   return int32_t(std::min(ct, std::max<int64_t>(1, 256 / pt)));
 }
 
-// scratch: cnorm [256 tiles] f32 | maxbits u32 | amb_count i32 | amb [n] i64 |
-// split centroids [256 tiles x 32 steps] 2 bf16 | groups' bests [G x n] float4
+// scratch: cnorm [256 tiles] f32 | cn64 [256 tiles] f64 | maxbits u32 |
+// amb_count i32 | amb [n] i64 | split centroids [256 tiles x 32 steps] 2 bf16 |
+// groups' bests [G x n] float4
 static size_t asg_split_bytes(int32_t C, int32_t d) {
   return size_t((int64_t(C) + kAsgTile - 1) / kAsgTile) * kAsgTile * size_t(asg_steps(d)) * 32 * 4;
 }
 
 size_t kmeans_assign_scratch(int64_t n, int32_t d, int32_t C) {
   const int32_t G = asg_groups(n, C);
-  return al256((size_t(C) + kAsgTile) * 4) + 256 + al256(size_t(n) * 8) + asg_split_bytes(C, d) +
-         (G > 1 ? size_t(G) * n * sizeof(float4) : 0);
+  return al256((size_t(C) + kAsgTile) * 4) + al256((size_t(C) + kAsgTile) * 8) + 256 +
+         al256(size_t(n) * 8) + asg_split_bytes(C, d) + (G > 1 ? size_t(G) * n * sizeof(float4) : 0);
 }
 
 struct AsgScratch {
   float* cnorm;
+  double* cn64;
   uint32_t* maxbits;
   int32_t* amb_count;
   int64_t* amb;
@@ -606,6 +782,8 @@ static AsgScratch asg_scratch(void* scratch, int64_t n, int32_t d, int32_t C) {
   char* p = static_cast<char*>(scratch);
   a.cnorm = reinterpret_cast<float*>(p);
   p += al256((size_t(C) + kAsgTile) * 4);
+  a.cn64 = reinterpret_cast<double*>(p);
+  p += al256((size_t(C) + kAsgTile) * 8);
   a.maxbits = reinterpret_cast<uint32_t*>(p);
   a.amb_count = reinterpret_cast<int32_t*>(p + 4);
   p += 256;
@@ -626,7 +804,7 @@ static void launch_product(const float* X, int64_t n, int32_t d, const float* ce
   hipLaunchKernelGGL(zero_i32_kernel2, dim3(1), dim3(64), 0, st,
                      reinterpret_cast<int32_t*>(a.maxbits), int64_t(2));
   hipLaunchKernelGGL(cent_split_kernel, dim3(unsigned(ntiles) * (kAsgTile / 4)), dim3(256), 0, st,
-                     cent, C, d, a.cs, a.cnorm, a.maxbits);
+                     cent, C, d, a.cs, a.cnorm, a.cn64, a.maxbits);
   const bool al = (reinterpret_cast<uintptr_t>(X) & 15) == 0;
   const dim3 grid(unsigned((n + kAsgTile - 1) / kAsgTile), unsigned(G));
   if (C <= kAsgNarrow) {
@@ -667,8 +845,13 @@ int run_kmeans_assign(const float* X, int64_t n, int32_t d, const float* cent, i
   if (G > 1)
     hipLaunchKernelGGL(assign_merge_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st,
                        a.part, n, G, o);
-  hipLaunchKernelGGL(assign_fixup_kernel, dim3(1024), dim3(256), 0, st, X, d, cent, C, assign,
-                     prev, changed, a.amb, a.amb_count);
+  const bool vec = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(cent)) & 15) == 0;
+  if (vec)
+    hipLaunchKernelGGL(assign_f64_kernel<true>, dim3(kF64Grid), dim3(64 * kF64Waves), 0, st, X, cent,
+                       a.cn64, o);
+  else
+    hipLaunchKernelGGL(assign_f64_kernel<false>, dim3(kF64Grid), dim3(64 * kF64Waves), 0, st, X, cent,
+                       a.cn64, o);
   return check_hip(hipGetLastError(), "k-means assignment kernels");
 }
 
