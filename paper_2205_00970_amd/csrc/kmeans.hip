@@ -135,18 +135,14 @@ struct AssignOut {
 };
 
 // Bound of the error of a value g_j of the split product for a point with
-// |x| <= xn and centroids with |mu| <= M.  The split values x = h + l + r (|x -
-// h| <= u |x|, |l| <= u (1 + u) |x|, |r| <= u^2 |x|, u = 2^-8) and the products
-// h h + h l + l h leave x.mu within ((2 (1 + u)^2 + 1) u^2 + dot_err_coef(3 d)
-// (1 + u)^2 (1 + 2 u)) |x| |mu|, plus absolute terms for parts below 2^-126;
-// |mu|^2 in fp32 is within dot_err_coef(d) |mu|^2, the fp32 combination adds
-// 2^-22, and the FP64 reference has its own rounding.
+// |x| <= xn and centroids with |mu| <= M: x.mu within split_err_coef(d) |x| |mu|
+// plus absolute terms for parts below 2^-126; |mu|^2 in fp32 is within
+// dot_err_coef(d) |mu|^2, the fp32 combination adds 2^-22, and the FP64 reference
+// has its own rounding.  Two values further apart than 2 E are in the exact
+// order; assign_decide asks for 4 E.
 __device__ inline double assign_err(int32_t d, double xn, double M) {
-  const double u = 0.00390625;
-  const double dotc = ((2.0 * (1.0 + u) * (1.0 + u) + 1.0) * u * u +
-                       dot_err_coef(3 * d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u)) * 1.01;
   return (dot_err_coef(d) + 2.384185791015625e-07) * M * M +
-         2.0 * (dotc + 2.384185791015625e-07) * xn * M +
+         2.0 * (split_err_coef(d) + 2.384185791015625e-07) * xn * M +
          6.0 * sqrt(double(d)) * 1.1754943508222875e-38 * (xn + M) +
          double(d + 2) * 8.881784197001252e-16 * (xn + M) * (xn + M) +
          6.0 * double(d) * 7.888609052210118e-31;

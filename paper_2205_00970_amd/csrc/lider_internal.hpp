@@ -214,6 +214,22 @@ __host__ __device__ inline double norm_above(float ss, int32_t d) {
          (1.0 + 9.5367431640625e-07);
 }
 
+// Split bf16 products: x = h + l + r with |x - h| <= u |x|, |l| <= u (1 + u) |x|,
+// |r| <= u^2 |x| (u = 2^-8) elementwise for both operands; the terms that the
+// three products h h + h l + l h drop are within (2 (1 + u)^2 + 1) u^2 sum |x_l
+// y_l|, and the fp32 accumulation of the 3d exact products within dot_err_coef(3d)
+// of their absolute sum, at most (1 + u)^2 (1 + 2u) sum |x_l y_l|; sum |x_l y_l|
+// <= |x| |y|.  No factor is needed for the matrix cores' accumulation: the bound
+// grants 2^-24 of the sum to each addition, and v_mfma_f32_16x16x32_bf16 rounds to
+// nearest after several exact additions (measured on gfx950: 32 equal products of
+// 0.5 to 2 2^-24 added to 1 come out exact to one rounding; random chains of
+// 2,048 positive products are off by 16 2^-24 of the sum, the bound is 2,050).
+__host__ __device__ inline double split_err_coef(int d) {
+  const double u = 0.00390625;
+  return ((2.0 * (1.0 + u) * (1.0 + u) + 1.0) * u * u +
+          dot_err_coef(3 * d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u)) * 1.01;
+}
+
 inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
 // ----------------------------------------------------------------- the index

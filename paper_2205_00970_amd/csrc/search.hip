@@ -457,8 +457,8 @@ __host__ __device__ inline int pow2_at_least(int v) {
 //   E = |q - bf16(q)| |x| + |bf16(q)| |x - bf16(x)| + 2 g_d |bf16(q)| |bf16(x)|
 // (q.x - bq.bx = (q - bq).x + bq.(x - bx), each term bounded by
 // Cauchy-Schwarz; the products of bf16 values are exact in fp32 and g_d =
-// d u / (1 - d u), u = 2^-24, bounds their fp32 accumulation in any order,
-// doubled to cover the accumulator's rounding mode).  The index keeps
+// d u / (1 - d u), u = 2^-24, bounds their fp32 accumulation in any order; the
+// factor 2 on it is reserve).  The index keeps
 // Xmax >= |x|, Xres >= |x - bf16(x)| and XBmax >= |bf16(x)| over its rows, so
 // E_q bounds every row of query q.  A row of the exact top k then has
 // s~ >= T - 2 E_q, with T the k-th best s~ (at least k rows have
@@ -5207,15 +5207,7 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     }
   } else if (split) {
     if (!l1_fused) launch_l1_gemm_bf16(ix, nq, qb, rs, st, nullptr, Q);
-    // x = h + l + r with |x - h| <= u |x|, |l| <= u (1 + u) |x|, |r| <= u^2 |x|
-    // (u = 2^-8) for q and mu elementwise; the terms the three products drop,
-    // h_q r_mu + l_q l_mu + l_q r_mu + r_q mu, are within (2 (1 + u)^2 + 1) u^2
-    // sum |q_l mu_l|, and the fp32 accumulation of the 3d exact products within
-    // dot_err_coef(3d) of their absolute sum, at most (1 + u)^2 (1 + 2u) sum
-    // |q_l mu_l|; sum |q_l mu_l| <= |q| |mu|
-    const double u = 0.00390625;
-    ecoef = ((2.0 * (1.0 + u) * (1.0 + u) + 1.0) * u * u +
-             dot_err_coef(3 * ix.d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u)) * 1.01;
+    ecoef = split_err_coef(ix.d);
     eadd = 3.0 * double(ix.d) * 7.888609052210118e-31;
     esub = 3.0 * std::sqrt(double(ix.d)) * 1.1754943508222875e-38;  // 2^-126
   } else if (l1b) {
@@ -5320,12 +5312,8 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     int32_t* list = reinterpret_cast<int32_t*>(rs);  // layer 1 is done
     ca.scnt = list + nq * kSplitCap;
     ca.sthr = reinterpret_cast<uint32_t*>(ca.scnt + nq);
-    // the split product's error (as for the layer-1 scores, both accumulations
-    // doubled to cover the accumulator's rounding mode) plus the fp32 product's
-    const double u = 0.00390625;
-    ca.ecoef = ((2.0 * (1.0 + u) * (1.0 + u) + 1.0) * u * u +
-                2.0 * dot_err_coef(3 * ix.d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u) +
-                2.0 * dot_err_coef(ix.d)) * 1.01;
+    // the split product's error plus the fp32 product's
+    ca.ecoef = split_err_coef(ix.d) + dot_err_coef(ix.d) * 1.01;
     ca.eadd = 4.0 * double(ix.d) * 7.888609052210118e-31;
     ca.esub = 3.0 * std::sqrt(double(ix.d)) * 1.1754943508222875e-38;  // 2^-126
     launch_wave_select<3>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k, list,
