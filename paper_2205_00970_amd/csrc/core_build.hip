@@ -643,6 +643,92 @@ __global__ void amap16_kernel(const int32_t* __restrict__ amap, const int64_t* _
 // Host copy of the offsets, largest cluster, the 16-bit position maps and the
 // rerank tile tables (all derived from the offsets and maps); shared by the
 // build and the index loader.
+// How the split window scores' lists come out on this corpus: sample b, a row
+// taken as a query, is scored in fp32 against up to kProbeRows rows around it in
+// its own cluster, and counts as long when more than half a list's room lies
+// within the margin of the kSplitMaxK-th best.  at: (row, first, count) of every
+// sample.  128 samples of 1,000 rows x 768: 80 us, once per build or load.
+constexpr int kProbeSamples = 128, kProbeRows = 2048, kProbeThreads = 1024;
+
+__global__ __launch_bounds__(kProbeThreads) void split_probe_kernel(
+    const float* __restrict__ X, int32_t d, const int4* __restrict__ at, double ecoef, float xmax,
+    int32_t* __restrict__ nlong) {
+  __shared__ float sc[kProbeRows];
+  __shared__ float s_best;
+  __shared__ int32_t s_cnt;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int4 p = at[blockIdx.x];
+  const float* q = X + int64_t(p.x) * d;
+  for (int r0 = 4 * wave; r0 < p.z; r0 += 4 * (kProbeThreads / 64)) {
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int l = 4 * lane; l < d; l += 256) {  // d a multiple of 32
+      const float4 a = *reinterpret_cast<const float4*>(q + l);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float4 b = *reinterpret_cast<const float4*>(X + int64_t(p.y + min(r0 + u, p.z - 1)) * d + l);
+        s[u] += a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      for (int o = 32; o > 0; o >>= 1) s[u] += __shfl_xor(s[u], o);
+      if (lane == 0 && r0 + u < p.z) sc[r0 + u] = s[u];
+    }
+  }
+  if (tid == 0) s_cnt = 0;
+  __syncthreads();
+  // the kSplitMaxK-th best (of equal ones the first is the better)
+  const int k = min(kSplitMaxK, p.z);
+  for (int r = tid; r < p.z; r += kProbeThreads) {
+    const float v = sc[r];
+    int rank = 0;
+#pragma unroll 8
+    for (int u = 0; u < p.z; ++u) rank += sc[u] > v || (sc[u] == v && u < r);
+    if (rank == k - 1) s_best = v;
+  }
+  __syncthreads();
+  const double qn = sqrt(double(sc[p.x - p.y]));
+  const double thr = double(s_best) - 2.0 * ecoef * qn * double(xmax);
+  int n = 0;
+  for (int r = tid; r < p.z; r += kProbeThreads) n += double(sc[r]) >= thr;
+  atomicAdd(&s_cnt, n);
+  __syncthreads();
+  if (tid == 0 && s_cnt > kSplitCap / 2) atomicAdd(nlong, 1);
+}
+
+// Sets ix.split_long (ix.X in place, ix.x_norm_max known).
+static int probe_split(Index& ix) {
+  if (ix.n <= 0 || ix.d % 32 != 0 || !(ix.x_norm_max < kSplitMaxRow)) return LIDER_OK;
+  const int ns = int(std::min<int64_t>(kProbeSamples, ix.n));
+  std::vector<int4> at(static_cast<size_t>(ns));
+  for (int b = 0; b < ns; ++b) {
+    const int64_t row = (2 * int64_t(b) + 1) * ix.n / (2 * ns);
+    const int64_t j = std::upper_bound(ix.h_off.begin(), ix.h_off.end(), row) - ix.h_off.begin() - 1;
+    const int64_t a = ix.h_off[j], e = ix.h_off[j + 1], len = std::min<int64_t>(kProbeRows, e - a);
+    const int64_t first = std::min(std::max(a, row - len / 2), e - len);
+    at[b] = make_int4(int32_t(row), int32_t(first), int32_t(len), 0);
+  }
+  const size_t tab = al256(at.size() * sizeof(int4));
+  char* buf = nullptr;
+  if (hipMalloc(&buf, tab + 256) != hipSuccess) {  // no split windows without it
+    (void)hipGetLastError();
+    return LIDER_OK;
+  }
+  int32_t h = 0;
+  int32_t* nlong = reinterpret_cast<int32_t*>(buf + tab);
+  int rc = check_hip(hipMemcpy(buf, at.data(), at.size() * sizeof(int4), hipMemcpyHostToDevice), "split samples");
+  if (rc == LIDER_OK) {
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, nullptr, nlong, int64_t(1), 0);
+    hipLaunchKernelGGL(split_probe_kernel, dim3(unsigned(ns)), dim3(kProbeThreads), 0, nullptr, ix.X, ix.d,
+                       reinterpret_cast<const int4*>(buf), split_window_ecoef(ix.d), ix.x_norm_max, nlong);
+    rc = check_hip(hipGetLastError(), "split samples");
+  }
+  if (rc == LIDER_OK) rc = check_hip(hipMemcpy(&h, nlong, 4, hipMemcpyDeviceToHost), "split samples");
+  (void)hipFree(buf);
+  if (rc == LIDER_OK) ix.split_long = float(h) / float(ns);
+  return rc;
+}
+
 int finish_index(Index& ix) {
   const int32_t C = ix.C;
   int rc = LIDER_OK;
@@ -716,6 +802,7 @@ int finish_index(Index& ix) {
       rc = check_hip(hipMemcpy(&ix.x_norm_max, mb, 4, hipMemcpyDeviceToHost), "largest row norm");
     if (rc == LIDER_OK) rc = check_hip(hipDeviceSynchronize(), "operand-ordered corpus");
     (void)hipFree(dsrc);
+    if (rc == LIDER_OK && ix.Xt) rc = probe_split(ix);
     if (rc != LIDER_OK) return rc;
   }
   // the row-major bf16 copy only where the operand-ordered one is missing

@@ -230,6 +230,15 @@ __host__ __device__ inline double split_err_coef(int d) {
           dot_err_coef(3 * d) * (1.0 + u) * (1.0 + u) * (1.0 + 2.0 * u)) * 1.01;
 }
 
+// Split window scores: lists for result lists of up to kSplitMaxK hold
+// kSplitCap rows per query; the bound is the split product's error plus the fp32
+// product's.  Largest row norm of an index that takes them: kSplitMaxRow.
+static constexpr int32_t kSplitMaxK = 16, kSplitCap = 62;
+static constexpr float kSplitMaxRow = 1e15f;
+__host__ __device__ inline double split_window_ecoef(int d) {
+  return split_err_coef(d) + dot_err_coef(d) * 1.01;
+}
+
 inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
 // ----------------------------------------------------------------- the index
@@ -287,6 +296,9 @@ struct Index {
   // max |x - bf16(x)| and max |bf16(x)| (host copies)
   float xb_bound[3] = {0.f, 0.f, 0.f};
   float x_norm_max = INFINITY;  // upper bound of max |x| (where Xt is built)
+  // share of sampled rows that, taken as queries, list many rows of their cluster
+  // within the split window scores' bound (1: not sampled, no split windows)
+  float split_long = 1.f;
   Model* models = nullptr;     // [H x (C+1)], model h*(C+1) + C = array h of layer 1
   double* leaves = nullptr;    // [H x (C*F2 + F1) x 2]
   int32_t* leaf_err = nullptr; // [H x (C*F2 + F1) x 2]

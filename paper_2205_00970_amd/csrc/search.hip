@@ -80,12 +80,17 @@ struct Plan {
 // us; c = 4, r = 1,000, 40 pairs: 980 against 987; four arrays, c = 6, r = 128,
 // 60 pairs: 1373 against 1184, and 1399 against 1318 at k = 16; c = 8, r =
 // 1,000, 80 pairs: 1548 against 1224).
-constexpr int32_t kSplitMaxK = 16;
+// The bound grows with the largest row norm, so on some corpora (one row of 100
+// times the others' norm, rows far from the origin, near-duplicates) it takes in
+// much of a window; the index finds out from a sample of its rows
+// (Index::split_long) and keeps the fp32 windows where more than an eighth of
+// the samples list many rows (300,000 x 768, 3,000 queries, c = 8, r = 1,000:
+// 463 us split, 630 in fp32; with such a row 4,960 by split windows whose long
+// lists were gathered).  A single query with a longer list than there is room
+// for, or without a bound, has its windows scored again in fp32, tile by tile.
 constexpr double kSplitMinPairs = 48.0;
-constexpr int32_t kSplitCap = 62;  // rows listed per query; a longer list is found again
-// Largest row norm of an index that takes it: no part or product of the split
-// overflows while |q| |x| stays below kSplitMaxNorm (decided per query).
-constexpr float kSplitMaxRow = 1e15f;
+// No part or product of the split overflows while |q| |x| stays below
+// kSplitMaxNorm (decided per query).
 constexpr double kSplitMaxNorm = 1e37;
 
 // Batches up to this many queries take the small batches' layer-1 product
@@ -207,8 +212,7 @@ Plan make_plan(const Index& ix, int64_t nq, int32_t k, int32_t c, int32_t r,
   // its lists take the room of the layer-1 scores, which nothing reads any more
   p.split = o.precision == LIDER_F32 && o.persistent == 0 && o.tile_rows == 0 &&
             o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && pairs > kSplitMinPairs && k <= kSplitMaxK &&
-            (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.x_norm_max < kSplitMaxRow &&
-            ix.d % 32 == 0;
+            (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.split_long <= 0.125f;
   // pair by pair: few queries whose windows hardly share a cluster (a quarter
   // as many pairs as clusters: 12% of them do), or few enough rows for the
   // caches to serve the shared ones
@@ -475,11 +479,15 @@ struct CertArgs {
   // split window scores: a score differs from the fp32 product's by at most
   // E_q = ecoef |q| max|x| + eadd + esub (|q| + max|x|); scnt[q] counts the
   // rows within the margin, of which the first cap are listed, or is -1 where
-  // no margin holds (values that can overflow); sthr[q] is the margin's key
+  // no margin holds (values that can overflow); nlong is set where a list is
+  // long (past cap, or -1).  MODE 0 with scnt: the queries with long lists
   const float* qnorm = nullptr;
   double ecoef = 0.0, eadd = 0.0, esub = 0.0;
-  uint32_t* sthr = nullptr;
+  int32_t* nlong = nullptr;
 };
+
+// A list that split_rescore_kernel leaves to the fp32 windows.
+__device__ inline bool split_long_list(int32_t n, int64_t cap) { return n < 0 || n > cap; }
 
 // Largest key (lowest score) listed for query q of the split window scores,
 // from the k-th best key T (0xffffffff: fewer than k candidates).
@@ -2419,16 +2427,22 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
   }
 }
 
-template <int FMT, int NPCM, bool BK>
+// LONG: only the pairs of queries with a long list (lcnt, see CertArgs), nothing
+// while nlong says that there is none.
+template <int FMT, int NPCM, bool BK, bool LONG>
 __global__ __launch_bounds__(256, 2) void rerank_wg_kernel(
     const void* __restrict__ Xv, int32_t d, const int32_t* __restrict__ tiles, int32_t ntiles,
     const int32_t* __restrict__ cstart, const int32_t* __restrict__ wl,
     const Pair* __restrict__ pairs, int32_t c, const void* __restrict__ Qv,
     float* __restrict__ sbuf, int32_t rcap, const uint32_t* __restrict__ pmask, int32_t mw,
-    const int32_t* __restrict__ tblk, uint32_t* __restrict__ bkey, int32_t nbcap) {
+    const int32_t* __restrict__ tblk, uint32_t* __restrict__ bkey, int32_t nbcap,
+    const int32_t* __restrict__ lcnt, const int32_t* __restrict__ nlong) {
   typedef Feed<FMT, true> F;
   typedef typename F::XE XE;
   typedef typename F::QE QE;
+  if constexpr (LONG) {
+    if (*nlong == 0) return;
+  }
   constexpr int PP = 16 * NPCM;
   constexpr int CAP = WgShared<FMT, NPCM>::CAP;
   __shared__ WgShared<FMT, NPCM> sh;
@@ -2468,6 +2482,7 @@ __global__ __launch_bounds__(256, 2) void rerank_wg_kernel(
         pi = wl ? wl[u] : u;
         pr = pairs[pi];
         hit = pr.s < row0 + rows_here && pr.s + pr.len > row0;
+        if constexpr (LONG) hit = hit && split_long_list(lcnt[pi / c], kSplitCap);
       }
       const uint64_t m = __ballot(hit);
       int base = 0;
@@ -3168,6 +3183,7 @@ __global__ __launch_bounds__(256) void wave_select_kernel(
   // into registers held across queries
   const int64_t q = int64_t(blockIdx.x) * 4 + wave;
   if (q >= nq) return;
+  if (MODE == 0 && ca.scnt && !split_long_list(ca.scnt[q], ca.cap)) return;
   {
     const float* sbq = sbuf + q * int64_t(c) * rcap;
     // R > 0 (n <= 64 R): candidate i = lane + 64 j keeps its key in register
@@ -3682,9 +3698,11 @@ __global__ __launch_bounds__(256) void wave_select_kernel(
       if (MODE == 3) {
         bool finite;
         thr = split_threshold(ca, q, tk, &finite);
-        if (lane == 0) ca.sthr[q] = thr;
         if (!finite) {  // wave-uniform
-          if (lane == 0) ca.scnt[q] = -1;
+          if (lane == 0) {
+            ca.scnt[q] = -1;
+            *ca.nlong = 1;
+          }
           return;
         }
       } else {
@@ -3702,7 +3720,10 @@ __global__ __launch_bounds__(256) void wave_select_kernel(
         for_blocks(thr, cert);
       else
         scan(cert);
-      if (lane == 0) ca.scnt[q] = m;
+      if (lane == 0) {
+        ca.scnt[q] = m;
+        if (MODE == 3 && m > ca.cap) *ca.nlong = 1;
+      }
     }
     __threadfence_block();
     __builtin_amdgcn_wave_barrier();
@@ -4579,134 +4600,76 @@ __global__ __launch_bounds__(256) void cert_wave_kernel(
 }
 
 // Second pass of the split window scores (k <= kSplitMaxK), one wave per
-// query: the fp32 score of every row within the margin, then the top k by
-// (score desc, id asc).  Sixteen rows at a time form the column operand of
+// query: the fp32 score of every listed row, then the top k by (score desc, id
+// asc).  Sixteen rows at a time form the column operand of
 // v_mfma_f32_16x16x4f32, the query (in all sixteen rows) the other, over the
 // same k-steps in the same order as the rerank's fp32 feed, so a score has the
 // bits that feed gives it.  The rows are gathered from X, 128 bytes of each per
 // step, two steps ahead; the gather bounds it (10,000 queries, k = 10, 10.3
-// rows each on average: 317 MB in 80 us).
-// A list past its room, or no margin at all (scnt -1), is taken from the score
-// rows again, 64 positions at a time; without a margin every candidate counts,
-// by the membership masks where there are several arrays (drop), since its
-// score may be a NaN.
+// rows each on average: 317 MB in 80 us).  Queries with a long list are left to
+// the fp32 windows.
 __global__ __launch_bounds__(256) void split_rescore_kernel(
     const float* __restrict__ X, int32_t d, const float* __restrict__ Q, int64_t nq,
     const int32_t* __restrict__ slist, const int32_t* __restrict__ scnt,
-    const uint32_t* __restrict__ sthr, const Pair* __restrict__ pairs,
-    const float* __restrict__ sbuf, int32_t rcap, int32_t c, const int64_t* __restrict__ off,
-    const uint32_t* __restrict__ pmask, int32_t mw, const int32_t* __restrict__ perm32, int32_t k,
-    int64_t* __restrict__ ids, float* __restrict__ scores) {
-  __shared__ int32_t rows[4][64];
-  __shared__ uint32_t bkey[4][kSplitMaxK], bid[4][kSplitMaxK];
+    const int32_t* __restrict__ perm32, int32_t k, int drop, int64_t* __restrict__ ids,
+    float* __restrict__ scores) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));  // uniform
   const int i = lane & 15, s = lane >> 4;
   const int64_t q = int64_t(blockIdx.x) * 4 + wave;
   if (q >= nq) return;
-  const bool drop = pmask != nullptr;
+  const int32_t n = scnt[q];
+  if (split_long_list(n, kSplitCap)) return;
   const float* qv = Q + q * d + 4 * s;
   const int nsteps = d / 32;
-  int nb = 0;  // entries of the best list (wave-uniform)
-  // merges the rows of lanes 0 .. m - 1 into the best list
-  auto take = [&](int32_t myrow, int m) {
-    float sc = 0.f;
-    for (int b = 0; 16 * b < m; ++b) {
-      const float* xr = X + int64_t(__shfl(myrow, min(16 * b + i, m - 1))) * d + 4 * s;
-      floatx4 acc{0.f, 0.f, 0.f, 0.f};
-      floatx4 x[3][2], y[3][2];
-      auto load = [&](int ks, floatx4 (&xo)[2], floatx4 (&yo)[2]) {
-        const int o = 32 * min(ks, nsteps - 1);
-        xo[0] = *reinterpret_cast<const floatx4*>(xr + o);
-        xo[1] = *reinterpret_cast<const floatx4*>(xr + o + 16);
-        yo[0] = *reinterpret_cast<const floatx4*>(qv + o);
-        yo[1] = *reinterpret_cast<const floatx4*>(qv + o + 16);
-      };
-      load(0, x[0], y[0]);
-      load(1, x[1], y[1]);
-      for (int ks = 0; ks < nsteps; ks += 3) {
+  const int32_t myrow = lane < n ? slist[q * kSplitCap + lane] : 0;
+  float sc = 0.f;
+  for (int b = 0; 16 * b < n; ++b) {
+    const float* xr = X + int64_t(__shfl(myrow, min(16 * b + i, n - 1))) * d + 4 * s;
+    floatx4 acc{0.f, 0.f, 0.f, 0.f};
+    floatx4 x[3][2], y[3][2];
+    auto load = [&](int ks, floatx4 (&xo)[2], floatx4 (&yo)[2]) {
+      const int o = 32 * min(ks, nsteps - 1);
+      xo[0] = *reinterpret_cast<const floatx4*>(xr + o);
+      xo[1] = *reinterpret_cast<const floatx4*>(xr + o + 16);
+      yo[0] = *reinterpret_cast<const floatx4*>(qv + o);
+      yo[1] = *reinterpret_cast<const floatx4*>(qv + o + 16);
+    };
+    load(0, x[0], y[0]);
+    load(1, x[1], y[1]);
+    for (int ks = 0; ks < nsteps; ks += 3) {
 #pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          if (ks + u < nsteps) {
-            load(ks + u + 2, x[(u + 2) % 3], y[(u + 2) % 3]);
+      for (int u = 0; u < 3; ++u) {
+        if (ks + u < nsteps) {
+          load(ks + u + 2, x[(u + 2) % 3], y[(u + 2) % 3]);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+          for (int h = 0; h < 2; ++h)
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y[u][h][e], x[u][h][e], acc, 0, 0, 0);
-          }
+            for (int e = 0; e < 4; ++e)
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y[u][h][e], x[u][h][e], acc, 0, 0, 0);
         }
       }
-      if (s == b) sc = acc[0];  // every lane of column i holds row 16 b + i's score
     }
-    const uint32_t ka = lane < m ? score_key(sc) : 0xffffffffu;
-    const uint32_t ia = lane < m ? uint32_t(perm32[myrow]) : 0xffffffffu;
-    const bool ok = lane < m && !(drop && ka == 0xffffffffu);
-    const uint64_t okm = __ballot(ok);
-    const uint32_t kb = lane < nb ? bkey[wave][lane] : 0xffffffffu;
-    const uint32_t ib = lane < nb ? bid[wave][lane] : 0xffffffffu;
-    int ra = 0, rb = 0;
-    for (int u = 0; u < m; ++u) {
-      if (!((okm >> u) & 1u)) continue;  // wave-uniform
-      const uint32_t ku = uint32_t(__builtin_amdgcn_readlane(int(ka), u));
-      const uint32_t iu = uint32_t(__builtin_amdgcn_readlane(int(ia), u));
-      ra += (ku < ka) || (ku == ka && iu < ia);
-      rb += (ku < kb) || (ku == kb && iu < ib);
-    }
-    for (int u = 0; u < nb; ++u) {
-      const uint32_t kv = uint32_t(__builtin_amdgcn_readlane(int(kb), u));
-      const uint32_t iv = uint32_t(__builtin_amdgcn_readlane(int(ib), u));
-      ra += (kv < ka) || (kv == ka && iv < ia);
-      rb += (kv < kb) || (kv == kb && iv < ib);
-    }
-    __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
-    if (ok && ra < k) {
-      bkey[wave][ra] = ka;
-      bid[wave][ra] = ia;
-    }
-    if (lane < nb && rb < k) {
-      bkey[wave][rb] = kb;
-      bid[wave][rb] = ib;
-    }
-    nb = min(k, nb + __popcll(okm));
-    __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
-  };
-  const int32_t n = scnt[q];
-  if (n >= 0 && n <= kSplitCap) {
-    take(lane < n ? slist[q * kSplitCap + lane] : 0, n);
-  } else {
-    const uint32_t thr = sthr[q];
-    for (int32_t t = 0; t < c; ++t) {
-      const Pair pr = pairs[q * c + t];
-      if (pr.j < 0) continue;  // wave-uniform
-      const float* sb = sbuf + (q * c + t) * int64_t(rcap);
-      const uint32_t* pm = drop ? pmask + (q * c + t) * int64_t(mw) : nullptr;
-      const int64_t base = off[pr.j] + pr.s;
-      for (int32_t p0 = 0; p0 < pr.len; p0 += 64) {
-        const int32_t p = p0 + lane;
-        bool in = p < pr.len;
-        if (in && n >= 0) in = score_key(sb[p]) <= thr;
-        if (in && n < 0 && drop) in = (pm[(pr.s + p) >> 5] >> ((pr.s + p) & 31)) & 1u;
-        const uint64_t bal = __ballot(in);
-        if (!bal) continue;  // wave-uniform
-        if (in) rows[wave][__popcll(bal & ((uint64_t(1) << lane) - 1))] = int32_t(base + p);
-        __threadfence_block();
-        __builtin_amdgcn_wave_barrier();
-        const int m = __popcll(bal);
-        take(lane < m ? rows[wave][lane] : 0, m);
-      }
-    }
+    if (s == b) sc = acc[0];  // every lane of column i holds row 16 b + i's score
   }
-  if (lane < k) {
-    if (lane < nb) {
-      ids[q * k + lane] = int64_t(bid[wave][lane]);
-      scores[q * k + lane] = key_score(bkey[wave][lane]);
-    } else {
-      ids[q * k + lane] = -1;
-      scores[q * k + lane] = -INFINITY;
-    }
+  const uint32_t ka = lane < n ? score_key(sc) : 0xffffffffu;
+  const uint32_t ia = lane < n ? uint32_t(perm32[myrow]) : 0xffffffffu;
+  const bool ok = lane < n && !(drop && ka == 0xffffffffu);
+  const uint64_t okm = __ballot(ok);
+  int rank = 0;
+  for (int u = 0; u < n; ++u) {
+    if (!((okm >> u) & 1u)) continue;  // wave-uniform
+    const uint32_t ku = uint32_t(__builtin_amdgcn_readlane(int(ka), u));
+    const uint32_t iu = uint32_t(__builtin_amdgcn_readlane(int(ia), u));
+    rank += (ku < ka) || (ku == ka && iu < ia);
+  }
+  if (ok && rank < k) {
+    ids[q * k + rank] = int64_t(ia);
+    scores[q * k + rank] = key_score(ka);
+  }
+  if (lane >= __popcll(okm) && lane < k) {
+    ids[q * k + lane] = -1;
+    scores[q * k + lane] = -INFINITY;
   }
 }
 
@@ -4860,21 +4823,21 @@ void launch_score_n(const Index& ix, bool bf16, bool vec, bool bvec, unsigned gr
                        alist, pmask, mw, ix.tile_blk[ti], bkey, nbcap);
 }
 
-template <int FMT, int NPCM>
+template <int FMT, int NPCM, bool LONG = false>
 void launch_wg_n(const Index& ix, const void* X, const void* Qv, const int32_t* cstart,
                  const int32_t* wl, const Pair* pairs, int32_t c, float* sbuf, int32_t rcap,
                  const uint32_t* pmask, int32_t mw, uint32_t* bkey, int32_t nbcap,
-                 hipStream_t st) {
+                 hipStream_t st, const int32_t* lcnt = nullptr, const int32_t* nlong = nullptr) {
   const int32_t nt = ix.n_tiles[2];
   // the block keys' epilogue only in the instantiation that writes them
   if (bkey)
-    hipLaunchKernelGGL((rerank_wg_kernel<FMT, NPCM, true>), dim3(chunk_grid(nt, tile_chunk(128))),
+    hipLaunchKernelGGL((rerank_wg_kernel<FMT, NPCM, true, LONG>), dim3(chunk_grid(nt, tile_chunk(128))),
                        dim3(256), 0, st, X, ix.d, ix.tiles[2], nt, cstart, wl, pairs, c, Qv, sbuf,
-                       rcap, pmask, mw, ix.tile_blk[2], bkey, nbcap);
+                       rcap, pmask, mw, ix.tile_blk[2], bkey, nbcap, lcnt, nlong);
   else
-    hipLaunchKernelGGL((rerank_wg_kernel<FMT, NPCM, false>), dim3(chunk_grid(nt, tile_chunk(128))),
+    hipLaunchKernelGGL((rerank_wg_kernel<FMT, NPCM, false, LONG>), dim3(chunk_grid(nt, tile_chunk(128))),
                        dim3(256), 0, st, X, ix.d, ix.tiles[2], nt, cstart, wl, pairs, c, Qv, sbuf,
-                       rcap, pmask, mw, ix.tile_blk[2], bkey, nbcap);
+                       rcap, pmask, mw, ix.tile_blk[2], bkey, nbcap, lcnt, nlong);
 }
 
 // The workgroup rerank (128-row tiles, direct schedule) on the operand-ordered
@@ -5311,16 +5274,20 @@ int run_search(const Index& ix, const float* Q, int64_t nq, int32_t k, int32_t c
     ca.cap = kSplitCap;
     int32_t* list = reinterpret_cast<int32_t*>(rs);  // layer 1 is done
     ca.scnt = list + nq * kSplitCap;
-    ca.sthr = reinterpret_cast<uint32_t*>(ca.scnt + nq);
-    // the split product's error plus the fp32 product's
-    ca.ecoef = split_err_coef(ix.d) + dot_err_coef(ix.d) * 1.01;
+    ca.nlong = ctr + 2;
+    ca.ecoef = split_window_ecoef(ix.d);
     ca.eadd = 4.0 * double(ix.d) * 7.888609052210118e-31;
     ca.esub = 3.0 * std::sqrt(double(ix.d)) * 1.1754943508222875e-38;  // 2^-126
+    const uint32_t* pm = H > 1 ? pmask : (const uint32_t*)nullptr;
     launch_wave_select<3>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k, list,
                           int(H > 1), ca, bkey, p.nbcap);
     hipLaunchKernelGGL(split_rescore_kernel, dim3(unsigned((nq + 3) / 4)), dim3(256), 0, st, ix.X,
-                       ix.d, Q, nq, list, ca.scnt, ca.sthr, pairs, sbuf, p.rcap, c, ix.off,
-                       H > 1 ? pmask : (const uint32_t*)nullptr, p.mw, ix.perm32, k, ids, scores);
+                       ix.d, Q, nq, list, ca.scnt, ix.perm32, k, int(H > 1), ids, scores);
+    // the queries with long lists: fp32 windows, then the selection over them
+    launch_wg_n<kF32W, 8, true>(ix, ix.Xt, Q, cstart, wl, pairs, c, sbuf, p.rcap, pm, p.mw, bkey,
+                                p.nbcap, st, ca.scnt, ca.nlong);
+    launch_wave_select<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k, list,
+                          int(H > 1), ca, bkey, p.nbcap);
   } else if (!bf16) {
     if (k <= 64 && narrow_by_block(k, int64_t(c) * p.rcap, nq, bkey))
       launch_block_wide<0>(st, pairs, sbuf, p.rcap, c, nq, k, ix.off, ix.perm32, ids, scores, k,
