@@ -739,6 +739,14 @@ int finish_index(Index& ix) {
   ix.max_cluster = 0;
   for (int32_t j = 0; j < C; ++j)
     ix.max_cluster = std::max<int64_t>(ix.max_cluster, ix.h_off[j + 1] - ix.h_off[j]);
+  ix.size_asc.resize(size_t(C));
+  for (int32_t j = 0; j < C; ++j) ix.size_asc[j] = double(ix.h_off[j + 1] - ix.h_off[j]);
+  std::sort(ix.size_asc.begin(), ix.size_asc.end());
+  ix.size_cubes.assign(size_t(C) + 1, 0.0);
+  ix.size_rest.assign(size_t(C) + 1, 0.0);
+  for (int32_t j = 0; j < C; ++j)
+    ix.size_cubes[j + 1] = ix.size_cubes[j] + ix.size_asc[j] * ix.size_asc[j] * ix.size_asc[j];
+  for (int32_t j = C; j > 0; --j) ix.size_rest[j - 1] = ix.size_rest[j] + ix.size_asc[j - 1];
   if (ix.H > 1 && ix.max_cluster > kMaxMultiCluster)
     return set_error(LIDER_EINVAL, "with n_arrays > 1 no cluster may hold more than 65536 rows");
   // several arrays: the position maps as positions within the cluster, 16 bits

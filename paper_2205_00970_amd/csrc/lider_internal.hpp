@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 #include <cstdint>
@@ -312,6 +313,17 @@ struct Index {
   int32_t n_l1_tiles = 0;
   int32_t* l1_tiles = nullptr;  // [n_l1_tiles x 4]: 0, row0, row0, rows
   std::vector<int64_t> h_off;  // host copy of off
+  // cluster sizes ascending, with the sums of L^3 before and of L from each on
+  std::vector<double> size_asc, size_cubes, size_rest;
+
+  // Rows that windows of r rows of `pairs` (query, cluster) pairs read more than
+  // once, roughly: pairs^2 / 2 times the overlap of two windows, with a cluster
+  // chosen as often as it has rows and the windows anywhere in it.
+  double shared_rows(double pairs, double r) const {
+    if (n <= 0) return 0.0;
+    const size_t u = size_t(std::upper_bound(size_asc.begin(), size_asc.end(), r) - size_asc.begin());
+    return 0.5 * (pairs / double(n)) * (pairs / double(n)) * (size_cubes[u] + r * r * size_rest[u]);
+  }
 };
 
 int set_error(int status, const std::string& msg);

@@ -214,13 +214,20 @@ Plan make_plan(const Index& ix, int64_t nq, int32_t k, int32_t c, int32_t r,
             o.pass_pairs == 0 && p.ti == 2 && p.npcm == 8 && pairs > kSplitMinPairs && k <= kSplitMaxK &&
             (p.l1_dense_rows ? ix.C : r1) >= kSplitCap + 2 && ix.split_long <= 0.125f;
   // pair by pair: few queries whose windows hardly share a cluster (a quarter
-  // as many pairs as clusters: 12% of them do), or few enough rows for the
-  // caches to serve the shared ones
+  // as many pairs as clusters), or few enough rows for the caches to serve the
+  // shared ones; and not where uneven clusters make the windows share many rows
+  // all the same, which the tiles read once (1M x 768, 1,024 clusters, the
+  // largest 60,000 rows, whole clusters, pair by pair against tiles: 10 queries
+  // sharing some 135 MB 249 against 292 us, 25: 844 MB 321 and 337, 50: 3.4 GB
+  // 496 and 383, 250: 84 GB 1,989 and 581; bf16, 25: 422 MB 392 and 398, 50:
+  // 1.7 GB 489 and 427)
   const double wrows = double(nq) * c * double(std::min<int64_t>(r, ix.max_cluster) + 16);
+  const double rowb = ix.d * (o.precision == LIDER_BF16 ? 2.0 : 4.0);
   const bool tiled = o.precision == LIDER_BF16 ? ix.d % 64 == 0 && ix.Xbt : ix.Xt != nullptr;
   p.small = H == 1 && nq <= kSmallBatch && o.persistent == 0 && o.tile_rows == 0 && o.pass_pairs == 0 &&
             tiled && np <= 32768 &&
-            (np * 4 <= ix.C || wrows * ix.d * (o.precision == LIDER_BF16 ? 2.0 : 4.0) <= double(64 << 20));
+            (np * 4 <= ix.C || wrows * rowb <= double(64 << 20)) &&
+            ix.shared_rows(double(np), double(r)) * rowb <= 1e9;
   if (p.small) {  // no block keys either: their readers are for large batches
     p.split = false;
     p.nbcap = 0;
