@@ -770,47 +770,49 @@ int finish_index(Index& ix) {
   const int32_t dpad = (ix.d + kTileKS - 1) / kTileKS * kTileKS;
   const bool want_t = 2 * int64_t(dpad) <= 3 * int64_t(ix.d);
   const bool want_bt = ix.storage == LIDER_BF16 && ix.d % 64 == 0 && !ix.Xbt;
-  if ((want_t || want_bt) && pblk[C] > 0) {
-    const int64_t nblk = pblk[C];
+  const int64_t nblk = pblk[C];
+  // An operand-ordered copy of the corpus (bf16: dpad = d), the fp32 one with the
+  // largest row norm.  The copies are an optimisation: without room, the pointer
+  // stays null and the rerank reads the row-major rows instead.
+  auto operand_copy = [&](bool bf, void** out) {
+    int2* dsrc = nullptr;
     std::vector<int2> src(static_cast<size_t>(nblk));
     for (int32_t j = 0; j < C; ++j)
       for (int64_t b = pblk[j]; b < pblk[j + 1]; ++b) {
         const int64_t r0 = ix.h_off[j] + 16 * (b - pblk[j]);
         src[b] = make_int2(int32_t(r0), int32_t(std::min<int64_t>(16, ix.h_off[j + 1] - r0)));
       }
-    int2* dsrc = nullptr;
-    const size_t elems = size_t(nblk) * 16 * size_t(dpad);  // per copy (bf16: dpad = d)
+    const size_t elems = size_t(nblk) * 16 * size_t(dpad);
     const size_t tab = al256(src.size() * sizeof(int2));  // then the largest norm
-    if (hipMalloc(&dsrc, tab + 256) != hipSuccess)
-      return set_error(LIDER_ENOMEM, "out of device memory (operand-ordered corpus)");
-    // the copies are an optimisation: without room for one, the rerank reads
-    // the row-major rows instead
-    if (want_t && hipMalloc(&ix.Xt, al256(elems * 4)) != hipSuccess) {
+    if (hipMalloc(&dsrc, tab + 256) != hipSuccess || hipMalloc(out, al256(elems * (bf ? 2 : 4))) != hipSuccess) {
       (void)hipGetLastError();
-      ix.Xt = nullptr;
+      if (dsrc) (void)hipFree(dsrc);
+      *out = nullptr;
+      return int(LIDER_OK);
     }
-    if (want_bt && hipMalloc(&ix.Xbt, al256(elems * 2)) != hipSuccess) {
-      (void)hipGetLastError();
-      ix.Xbt = nullptr;
-    }
-    rc = check_hip(hipMemcpy(dsrc, src.data(), src.size() * sizeof(int2), hipMemcpyHostToDevice),
-                   "copy block table");
+    int st = check_hip(hipMemcpy(dsrc, src.data(), src.size() * sizeof(int2), hipMemcpyHostToDevice),
+                       "copy block table");
     uint32_t* mb = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(dsrc) + tab);
     const dim3 grid(unsigned(std::min<int64_t>((nblk + 3) / 4, 8192)));
-    if (rc == LIDER_OK && ix.Xt) {
-      hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, nullptr, reinterpret_cast<int32_t*>(mb), int64_t(1), 0);
-      hipLaunchKernelGGL(tile_corpus_kernel<false>, grid, dim3(256), 0, nullptr, ix.X, ix.d, dsrc,
-                         nblk, (void*)ix.Xt, mb);
+    if (st == LIDER_OK) {
+      if (bf) {
+        hipLaunchKernelGGL(tile_corpus_kernel<true>, grid, dim3(256), 0, nullptr, ix.X, ix.d, dsrc,
+                           nblk, *out, (uint32_t*)nullptr);
+      } else {
+        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, nullptr, reinterpret_cast<int32_t*>(mb), int64_t(1), 0);
+        hipLaunchKernelGGL(tile_corpus_kernel<false>, grid, dim3(256), 0, nullptr, ix.X, ix.d, dsrc,
+                           nblk, *out, mb);
+      }
+      st = check_hip(hipGetLastError(), "operand-ordered corpus");
     }
-    if (rc == LIDER_OK && ix.Xbt)
-      hipLaunchKernelGGL(tile_corpus_kernel<true>, grid, dim3(256), 0, nullptr, ix.X, ix.d, dsrc,
-                         nblk, (void*)ix.Xbt, (uint32_t*)nullptr);
-    if (rc == LIDER_OK) rc = check_hip(hipGetLastError(), "operand-ordered corpus");
-    if (rc == LIDER_OK && ix.Xt)
-      rc = check_hip(hipMemcpy(&ix.x_norm_max, mb, 4, hipMemcpyDeviceToHost), "largest row norm");
-    if (rc == LIDER_OK) rc = check_hip(hipDeviceSynchronize(), "operand-ordered corpus");
+    if (st == LIDER_OK && !bf)
+      st = check_hip(hipMemcpy(&ix.x_norm_max, mb, 4, hipMemcpyDeviceToHost), "largest row norm");
+    if (st == LIDER_OK) st = check_hip(hipDeviceSynchronize(), "operand-ordered corpus");
     (void)hipFree(dsrc);
-    if (rc == LIDER_OK && ix.Xt) rc = probe_split(ix);
+    return st;
+  };
+  if (want_bt && nblk > 0) {
+    rc = operand_copy(true, reinterpret_cast<void**>(&ix.Xbt));
     if (rc != LIDER_OK) return rc;
   }
   // the row-major bf16 copy only where the operand-ordered one is missing
@@ -890,6 +892,9 @@ int finish_index(Index& ix) {
     rc = check_hip(hipMemcpy(ix.l1_tiles, t.data(), t.size() * 4, hipMemcpyHostToDevice),
                    "copy layer-1 tiles");
   }
+  // last, so that it takes no room that anything above needs
+  if (rc == LIDER_OK && want_t && nblk > 0) rc = operand_copy(false, reinterpret_cast<void**>(&ix.Xt));
+  if (rc == LIDER_OK && ix.Xt) rc = probe_split(ix);
   return rc;
 }
 
