@@ -93,11 +93,8 @@ constexpr double kSplitMinPairs = 48.0;
 // kSplitMaxNorm (decided per query).
 constexpr double kSplitMaxNorm = 1e37;
 
-// Batches up to this many queries take the small batches' layer-1 product
-// (1,000 centroids x 768, product and routing together, 256 queries: 18.6 us
-// against 24.8 with the large tiles, 32 against 49 split; the small tiles'
-// time grows by 0.025 and 0.045 us a query, the large ones' not up to some 600)
-// and may take their routing and window scores.
+// Batches up to this many queries may take the small batches' routing and window
+// scores.
 constexpr int64_t kSmallBatch = 512;
 
 // Rerank shape: rows per tile (index into the tile tables: 32, 64, 128) and
@@ -2958,13 +2955,13 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
   }
 }
 
-// Layer-1 product of a small batch (d a multiple of 32): a workgroup owns 16
-// queries x 16 centroids, its 4 waves a quarter of the dimension range each,
-// eight steps' operands in flight straight from L2; the partial tiles are
-// added through LDS.  The 128 x 128 tiles of l1_gemm_lds_kernel give one query
-// eight workgroups with a chain of 12 or 24 chunks each (14 us); this takes 3
-// us, 5.4 with 100 queries.  SPLIT as there, from the fp32 operands.  The first l1_blocks
-// workgroups run the layer-1 locate.
+// Layer-1 product of a small batch (d a multiple of 64, SPLIT of 4): a workgroup
+// owns 16 queries x 16 centroids, its 4 waves a quarter of the dimension range
+// each, eight steps' operands (SPLIT four) in flight straight from L2; the partial
+// tiles are added through LDS.  The 128 x 128 tiles of l1_gemm_lds_kernel give one
+// query eight workgroups with a chain of 12 or 24 chunks each (14 us); this takes 3
+// us, 5.4 with 100 queries.  SPLIT as there, from the fp32 operands.  The first
+// l1_blocks workgroups run the layer-1 locate.
 template <bool SPLIT>
 __global__ __launch_bounds__(256) void l1_small_kernel(const void* __restrict__ Qv, int64_t nq,
                                                        const void* __restrict__ Cv, int32_t C,
@@ -4996,14 +4993,24 @@ void launch_l1_gemm_mb(const Index& ix, bool fp8, int64_t nq, const float* Q,
 }
 
 // bf16 query x bf16 centroid product (candidate scores of the exact routing).
-// With la (d a multiple of 64 only), the same launch also runs the layer-1
-// locate of every (query, array) item.  Qf (d a multiple of 64, 16-byte
+// With la (d a multiple of 64, or Qf), the same launch also runs the layer-1
+// locate of every (query, array) item.  Qf (d a multiple of 4, 16-byte
 // aligned): the split product of the fp32 queries and centroids instead.
 void launch_l1_gemm_bf16(const Index& ix, int64_t nq, const __hip_bfloat16* Qb, float* rs,
                          hipStream_t st, const L1Args* la = nullptr, const float* Qf = nullptr) {
-  // the small tiles also where the large ones would leave three of four CUs idle
+  // Small tiles while the large ones leave seven of eight CUs idle, or three of
+  // four and the centroids, which small tiles read from L2 once per 16 queries
+  // instead of 128, come to no more than 32 MB that way; and for a first two rows
+  // of small tiles, which read them no more often.  Routing stage, large against
+  // small, split: 1,000 x 768 centroids, 200 queries (16 large tiles) 50.7 and 33.4
+  // us, 700 (48) 52.3 and 53.0; 4,000, 128 (32) 104.6 and 100.8, 256 (64) 106.8 and
+  // 120.9, 512 (128) 124 and 180; 10,000, 32 (79) 216 and 205, 512 (316) 271 and
+  // 443; 1,000 x 100, 700 (48) 31.3 and 26.5.  bf16: 1,000 x 768, 512 (32) 34.5 and
+  // 33.6, 700 (48) 35.1 and 38.6.
   const int64_t nbig = (nq + 127) / 128 * ((ix.C + 127) / 128);
-  if ((Qf || ix.d % kLdsK == 0) && (nq <= kSmallBatch || 4 * nbig <= ix.n_cu)) {
+  const int64_t reads = (nq + 15) / 16 * ix.C * int64_t(ix.d) * (Qf ? 4 : 2);
+  if ((Qf || ix.d % kLdsK == 0) &&
+      (nq <= 32 || 8 * nbig <= ix.n_cu || (4 * nbig <= ix.n_cu && reads <= (int64_t(32) << 20)))) {
     const unsigned l1b = la ? unsigned((la->nq * la->H + 255) / 256) : 0u;
     const dim3 grid(l1b + unsigned((nq + 15) / 16 * ((ix.C + 15) / 16)));
     if (Qf)

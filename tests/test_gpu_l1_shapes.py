@@ -1,0 +1,28 @@
+"""The layer-1 product at both sides of the rule between its small and large
+tiles (number of large tiles, bytes that small tiles read, a first few
+queries), plain and split: the routed clusters are the c best centroids by
+FP64 inner products."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,C,batches", [(64, 4200, (32, 33, 129)), (64, 1000, (512, 513, 1024, 1025)),
+                                         (768, 1000, (200, 513, 700)), (100, 1000, (700, 1030)),
+                                         (100, 4200, (31, 40)), (128, 300, (1300,))])
+def test_routed_clusters(d, C, batches):
+    import torch
+    from paper_2205_00970_amd import datagen, lider
+    g = torch.Generator("cuda").manual_seed(d + C)
+    n = 2 * C
+    lab = torch.arange(n, device="cuda") % C
+    X = torch.randn(C, d, generator=g, device="cuda")[lab]  # centroids are exactly the rows
+    A, b = datagen.lsh_params(4, d, 2.0, seed=150)
+    gi = lider.Index(X.contiguous(), C, 4, 2.0, 8, (A, b), assignment=lab.int())
+    cent = torch.from_numpy(gi.export("centroids").reshape(C, d)).cuda().double()
+    Q = torch.randn(max(batches), d, generator=g, device="cuda")
+    for c in (1, 5):
+        want = torch.topk(Q.double() @ cent.T, c, dim=1).indices.sort(dim=1).values
+        for nq in batches:
+            _, _, dbg = gi.search(Q[:nq], 3, c, 8, r1=C, debug=True)
+            assert torch.equal(dbg["routed"].long().sort(dim=1).values, want[:nq]), (c, nq)
