@@ -128,6 +128,9 @@ void rerank_shape(const Index& ix, int64_t nq, int32_t c, int32_t r, const lider
       // 16 or 32 pairs keep three waves per SIMD; wider passes hold two
       // either way, so beyond 32 the widest (one pass for most tiles)
       *npcm = 2.0 * *pairs <= 16.0 ? 1 : 2.0 * *pairs <= 32.0 ? 2 : 8;
+      // fp32 rows of fewer than four k-steps: the 64-pair form, which reads a short
+      // row once, while the split windows (128 pairs) are out of question
+      if (*npcm == 8 && !bf16 && ix.d < 128 && *pairs <= kSplitMinPairs) *npcm = 4;
     }
     return;
   }
@@ -2276,13 +2279,18 @@ struct WgRows {
 // depends on the path, the compiler waits for all of them, and a step then
 // takes the whole latency of the loads it has just issued.  So the staging has
 // no idle threads (an odd block count has its last block staged twice), and a
-// load past the last step reads the last one again.  Passes of up to 32 pairs,
-// which the row stream bounds, have their last four steps, whose rows are all
-// on their way, as code of their own (precision form, 1M x 768: 305 -> 288
-// us); wider ones would spill.  1M x 768, 10,000 queries: c = 8, r = 256: 802 ->
-// 712 us; ten arrays, split: 995 -> 943 us; whole clusters: 533 -> 522 us (483
-// -> 468 on another card), bf16 291 -> 289 us (274 -> 260); uneven clusters, c
-// = 16, r = 512, 2,048 queries: 591 -> 536 us.
+// load past the last step reads the last one again.  The last four steps, whose
+// rows are all on their way, are code of their own in passes of up to 96 pairs
+// (padded feeds 64); beyond, the registers would not do.  Rows of fewer than four
+// steps load each operand once, in the forms that can spare the registers (bf16,
+// and up to 64 pairs per pass).  The 128-pair forms hold 256 VGPRs: in bf16 a
+// scheduling barrier every four column blocks keeps the LDS reads of all eight
+// from being in flight together (no spills; fp32 spills 0 to 9 registers, none in
+// its loops, split windows 12 to 18, padded feeds 28 to 32).  1M x 768, 10,000 queries, rerank, conditional loads against
+// this: c = 8, r = 256: 855 and 716 us; ten arrays, split (995) and 898; whole
+// clusters 537 and 530, bf16 290 and 287, bf16 c = 8, r = 256 374 and 343; 300,000
+// rows, 6,000 queries, bf16: d = 64 38.3 and 37.6, 256 58.1 and 53.1, 768 105 and
+// 98.
 template <int FMT, int NPC, int NPCM, int RING>
 __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Feed<FMT, true>>& xr,
                                         const typename Feed<FMT, true>::QE* __restrict__ Q, int32_t d,
@@ -2393,17 +2401,9 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
           for (int rc = 0; rc < RC; ++rc) F::mfma(qv[g], xp[rc], acc[rc][pc]);
         }
       }
+      if (FMT == kBF16W && NPC > 4 && p0 % 4 == 2) __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // prologue: block 0 in LDS slot 0, block 1 staged, rows of
-  // steps 0 .. RING - 2 in flight
-  stage_load(0, sg[0]);
-  stage_load(min(1, nsteps - 1), sg[1]);
-#pragma unroll
-  for (int u = 0; u + 1 < RING; ++u) xload(u, xs[u]);
-  __builtin_amdgcn_sched_barrier(0);
-  stage_store(0, sg[0]);
-  __syncthreads();
   // step K at place J of its group; rows: the rows of step K + 3 are loaded,
   // stage: the queries of step K + 2, store: those of step K + 1 go to LDS (the
   // last steps leave these out, or the pass would end in a wait for them)
@@ -2415,7 +2415,32 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
     if (store) stage_store((J + 1) & 1, sg[(J + 1) & 1]);
     __syncthreads();
   };
-  constexpr bool kPeel = NPCM <= 2;
+  if constexpr (FMT == kBF16W || NPCM <= 4) {
+    if (nsteps < 4) {  // short rows: each operand once
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (u < nsteps) {
+          if (u < 2) stage_load(u, sg[u]);
+          xload(u, xs[u]);
+        }
+      stage_store(0, sg[0]);
+      __syncthreads();
+#pragma unroll
+      for (int J = 0; J < 3; ++J)
+        if (J < nsteps) step(J, J, false, J + 2 < nsteps, J + 1 < nsteps);
+      return;
+    }
+  }
+  // prologue: block 0 in LDS slot 0, block 1 staged, rows of
+  // steps 0 .. RING - 2 in flight
+  stage_load(0, sg[0]);
+  stage_load(min(1, nsteps - 1), sg[1]);
+#pragma unroll
+  for (int u = 0; u + 1 < RING; ++u) xload(u, xs[u]);
+  __builtin_amdgcn_sched_barrier(0);
+  stage_store(0, sg[0]);
+  __syncthreads();
+  constexpr bool kPeel = NPC <= (FMT == kF32P ? 4 : 6);
   int k = 0;
   for (; k + 4 < nsteps + (kPeel ? 0 : 1); k += 4) {
 #pragma unroll
