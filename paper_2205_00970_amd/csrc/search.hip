@@ -1656,7 +1656,8 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // bf16(x - h) for three bf16 products (the workgroup rerank only).
 // 6: kF32W's rows with zeros past d (any d), the queries read with clamped
 // addresses (the workgroup and pair reranks; the chain of kF32W without VEC).
-enum { kF32 = 0, kBF16 = 1, kFP8 = 2, kF32W = 3, kBF16W = 4, kF32S = 5, kF32P = 6 };
+// 7: the same with the queries in 16-byte loads (d a multiple of 4, aligned).
+enum { kF32 = 0, kBF16 = 1, kFP8 = 2, kF32W = 3, kBF16W = 4, kF32S = 5, kF32P = 6, kF32Q = 7 };
 
 template <int FMT, bool VEC>
 struct Feed;
@@ -1830,16 +1831,28 @@ struct Feed<kBF16W, VEC> {  // 64 dims per k-step: 8 + 8 per lane
   }
 };
 
-// Four values of a row of d, zeros past it, every load inside it and none under
-// a condition.
-__device__ inline floatx4 load_padded(const float* row, int k, int d) {
+// Four values of a row of d from k on, every load inside the row (VEC: d a
+// multiple of 4, the four lie inside the row or past it).  Those past the row are
+// some of its other values until padded() makes them zeros, which is left to
+// where they are used: at the load it would wait for the load (masked at the load,
+// then here, rerank: 100,003 x 100, 777 queries, c = 3, 37.8 and 25.3 us; 3,000
+// queries x 300 120 and 99, x 130, in scalar loads, 82.8 and 79.5).
+template <bool VEC>
+__device__ inline floatx4 load_clamped(const float* row, int k, int d) {
+  if (VEC) return *reinterpret_cast<const floatx4*>(row + min(k, d - 4));
   floatx4 v;
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = row[min(k + e, d - 1)];
+  return v;
+}
+
+__device__ inline floatx4 padded(floatx4 v, int k, int d) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = k + e < d ? v[e] : 0.f;
   return v;
 }
+
+constexpr bool padded_feed(int fmt) { return fmt == kF32P || fmt == kF32Q; }
 
 template <>
 struct Feed<kF32P, true> {
@@ -1847,12 +1860,26 @@ struct Feed<kF32P, true> {
   typedef float XE;
   typedef float QE;
   typedef F32x2 T;
+  static constexpr bool QV = false;
   __device__ static T load(const float* row, int k, int d) {
-    return T{__builtin_bit_cast(float4, load_padded(row, k, d)),
-             __builtin_bit_cast(float4, load_padded(row, k + 16, d))};
+    return T{__builtin_bit_cast(float4, load_clamped<QV>(row, k, d)),
+             __builtin_bit_cast(float4, load_clamped<QV>(row, k + 16, d))};
+  }
+  __device__ static T pad(const T& v, int k, int d) {
+    return T{__builtin_bit_cast(float4, padded(__builtin_bit_cast(floatx4, v.a), k, d)),
+             __builtin_bit_cast(float4, padded(__builtin_bit_cast(floatx4, v.b), k + 16, d))};
   }
   __device__ static void mfma(const T& q, const T& x, floatx4& acc) {
     Feed<kF32W, true>::mfma(q, x, acc);
+  }
+};
+
+template <>
+struct Feed<kF32Q, true> : Feed<kF32P, true> {
+  static constexpr bool QV = true;
+  __device__ static T load(const float* row, int k, int d) {
+    return T{__builtin_bit_cast(float4, load_clamped<QV>(row, k, d)),
+             __builtin_bit_cast(float4, load_clamped<QV>(row, k + 16, d))};
   }
 };
 
@@ -2283,10 +2310,11 @@ struct WgRows {
 // rows are all on their way, are code of their own in passes of up to 96 pairs
 // (padded feeds 64); beyond, the registers would not do.  Rows of fewer than four
 // steps load each operand once, in the forms that can spare the registers (bf16,
-// and up to 64 pairs per pass).  The 128-pair forms hold 256 VGPRs: in bf16 a
-// scheduling barrier every four column blocks keeps the LDS reads of all eight
-// from being in flight together (no spills; fp32 spills 0 to 9 registers, none in
-// its loops, split windows 12 to 18, padded feeds 28 to 32).  1M x 768, 10,000 queries, rerank, conditional loads against
+// and up to 64 pairs per pass).  The 128-pair forms hold 256 VGPRs: in bf16 and
+// with padded queries a scheduling barrier every four column blocks keeps the LDS
+// reads of all eight from being in flight together (bf16: no spills; fp32 0 to 9
+// registers, none in its loops; split windows 12 to 18; padded feeds 8 to 11 with
+// wide loads, 28 without).  1M x 768, 10,000 queries, rerank, conditional loads against
 // this: c = 8, r = 256: 855 and 716 us; ten arrays, split (995) and 898; whole
 // clusters 537 and 530, bf16 290 and 287, bf16 c = 8, r = 256 374 and 343; 300,000
 // rows, 6,000 queries, bf16: d = 64 38.3 and 37.6, 256 58.1 and 53.1, 768 105 and
@@ -2314,7 +2342,7 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
     const int u = tid + 256 * j;
     const int pc = min(u >> 7, NPC - 1), r = (u >> 3) & 15, part = u & 7;
     const int e = min(16 * pc + r, np - 1);
-    qsrc[j] = Q + int64_t(sh.lq[e]) * d + (FMT == kF32P ? 0 : part * (16 / int(sizeof(QE))));
+    qsrc[j] = Q + int64_t(sh.lq[e]) * d + (padded_feed(FMT) ? 0 : part * (16 / int(sizeof(QE))));
     qdst[j] = pc * kWgQBlk + r * kWgQRow +
               (FMT == kF32S ? (part & 3) * 16 + (part >> 2) * 8 : part * 16);
   }
@@ -2322,13 +2350,13 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
   auto stage_load = [&](int k, floatx4 (&dst)[NCH]) {
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-      if constexpr (FMT == kF32P)
-        dst[j] = load_padded(qsrc[j], k * F::KS + 4 * (tid & 7), d);
+      if constexpr (padded_feed(FMT))
+        dst[j] = load_clamped<F::QV>(qsrc[j], k * F::KS + 4 * (tid & 7), d);
       else
         dst[j] = *reinterpret_cast<const floatx4*>(qsrc[j] + k * F::KS);
     }
   };
-  auto stage_store = [&](int slot, const floatx4 (&src)[NCH]) {
+  auto stage_store = [&](int slot, int k, const floatx4 (&src)[NCH]) {  // step k's queries
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
       if constexpr (FMT == kF32S) {
@@ -2342,6 +2370,8 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
         }
         *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j]]) = h;
         *reinterpret_cast<bf16x4*>(&sh.qs[slot][qdst[j] + 64]) = l;
+      } else if constexpr (padded_feed(FMT)) {
+        *reinterpret_cast<floatx4*>(&sh.qs[slot][qdst[j]]) = padded(src[j], k * F::KS + 4 * (tid & 7), d);
       } else {
         *reinterpret_cast<floatx4*>(&sh.qs[slot][qdst[j]]) = src[j];
       }
@@ -2401,7 +2431,7 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
           for (int rc = 0; rc < RC; ++rc) F::mfma(qv[g], xp[rc], acc[rc][pc]);
         }
       }
-      if (FMT == kBF16W && NPC > 4 && p0 % 4 == 2) __builtin_amdgcn_sched_barrier(0);
+      if ((FMT == kBF16W || FMT == kF32Q) && NPC > 4 && p0 % 4 == 2) __builtin_amdgcn_sched_barrier(0);
     }
   };
   // step K at place J of its group; rows: the rows of step K + 3 are loaded,
@@ -2412,7 +2442,7 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
     if (rows) xload(K + 3, xs[(J + 3) & 3]);
     __builtin_amdgcn_sched_barrier(0);
     products(xs[J], J & 1);
-    if (store) stage_store((J + 1) & 1, sg[(J + 1) & 1]);
+    if (store) stage_store((J + 1) & 1, K + 1, sg[(J + 1) & 1]);
     __syncthreads();
   };
   if constexpr (FMT == kBF16W || NPCM <= 4) {
@@ -2423,7 +2453,7 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
           if (u < 2) stage_load(u, sg[u]);
           xload(u, xs[u]);
         }
-      stage_store(0, sg[0]);
+      stage_store(0, 0, sg[0]);
       __syncthreads();
 #pragma unroll
       for (int J = 0; J < 3; ++J)
@@ -2438,9 +2468,9 @@ __device__ __forceinline__ void wg_pass(WgShared<FMT, NPCM>& sh, const WgRows<Fe
 #pragma unroll
   for (int u = 0; u + 1 < RING; ++u) xload(u, xs[u]);
   __builtin_amdgcn_sched_barrier(0);
-  stage_store(0, sg[0]);
+  stage_store(0, 0, sg[0]);
   __syncthreads();
-  constexpr bool kPeel = NPC <= (FMT == kF32P ? 4 : 6);
+  constexpr bool kPeel = NPC <= (padded_feed(FMT) ? 4 : 6);
   int k = 0;
   for (; k + 4 < nsteps + (kPeel ? 0 : 1); k += 4) {
 #pragma unroll
@@ -2682,6 +2712,12 @@ __global__ __launch_bounds__(256) void pair_score_kernel(
     y[u] = F::load(q0, kk * F::KS + F::SUBW * s, d);
   };
   floatx4 acc{0.f, 0.f, 0.f, 0.f};
+  auto product = [&](int k, int u) {
+    if constexpr (padded_feed(FMT))
+      F::mfma(F::pad(y[u], k * F::KS + F::SUBW * s, d), x[u], acc);
+    else
+      F::mfma(y[u], x[u], acc);
+  };
 #pragma unroll
   for (int u = 0; u + 1 < kPairRing; ++u) load(u, u);
   int k = 0;
@@ -2690,12 +2726,12 @@ __global__ __launch_bounds__(256) void pair_score_kernel(
     for (int u = 0; u < kPairRing; ++u) {
       load(k + u + kPairRing - 1, (u + kPairRing - 1) % kPairRing);
       __builtin_amdgcn_sched_barrier(0);
-      F::mfma(y[u], x[u], acc);
+      product(k + u, u);
     }
   }
 #pragma unroll
   for (int u = 0; u + 1 < kPairRing; ++u)
-    if (k + u < nsteps) F::mfma(y[u], x[u], acc);
+    if (k + u < nsteps) product(k + u, u);
   // every lane of column i holds row i's score
   const int32_t row = 16 * b + i;
   if (s == 0 && row >= a && row < en) sbuf[t * rcap + (row - a)] = acc[0];
@@ -4897,6 +4933,8 @@ bool launch_score_wg(const Index& ix, bool bf16, const int32_t* cstart, const in
     launch_wg_n<kF32S, 8>(ix, ix.Xt, Q, cstart, wl, pairs, c, sbuf, rcap, pmask, mw, bkey, nbcap, st);
   else if (bf16)
     LIDER_WG(kBF16W, (const void*)ix.Xbt, (const void*)Qb)
+  else if (ix.d % 4 == 0 && ix.d % 32 != 0 && (reinterpret_cast<uintptr_t>(Q) & 15) == 0)
+    LIDER_WG(kF32Q, (const void*)ix.Xt, (const void*)Q)
   else if (ix.d % 32 != 0)
     LIDER_WG(kF32P, (const void*)ix.Xt, (const void*)Q)
   else
@@ -4914,6 +4952,9 @@ void launch_pair_scores(const Index& ix, bool bf16, int64_t np, const Pair* pair
   if (bf16)
     hipLaunchKernelGGL(pair_score_kernel<kBF16W>, grid, dim3(256), 0, st, (const void*)ix.Xbt, ix.d,
                        pairs, c, (const void*)Qb, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
+  else if (ix.d % 4 == 0 && ix.d % 32 != 0 && (reinterpret_cast<uintptr_t>(Q) & 15) == 0)
+    hipLaunchKernelGGL(pair_score_kernel<kF32Q>, grid, dim3(256), 0, st, (const void*)ix.Xt, ix.d,
+                       pairs, c, (const void*)Q, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
   else if (ix.d % 32 != 0)
     hipLaunchKernelGGL(pair_score_kernel<kF32P>, grid, dim3(256), 0, st, (const void*)ix.Xt, ix.d,
                        pairs, c, (const void*)Q, ix.tile_base[2], ix.tile_blk[2], sbuf, rcap);
