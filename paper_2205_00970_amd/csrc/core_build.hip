@@ -647,8 +647,10 @@ __global__ void amap16_kernel(const int32_t* __restrict__ amap, const int64_t* _
 // taken as a query, is scored in fp32 against up to kProbeRows rows around it in
 // its own cluster, and counts as long when more than half a list's room lies
 // within the margin of the kSplitMaxK-th best.  at: (row, first, count) of every
-// sample.  128 samples of 1,000 rows x 768: 80 us, once per build or load.
-constexpr int kProbeSamples = 128, kProbeRows = 2048, kProbeThreads = 1024;
+// sample.  Once per build or load (128 samples of 1,000 rows x 768 took 172 us,
+// mostly the latency of one workgroup's rows and ranks; 512 rows 79).
+constexpr int kProbeSamples = 128, kProbeRows = 512, kProbeThreads = 1024;
+constexpr size_t kProbeBytes = kProbeSamples * sizeof(int4) + 256;
 
 __global__ __launch_bounds__(kProbeThreads) void split_probe_kernel(
     const float* __restrict__ X, int32_t d, const int4* __restrict__ at, double ecoef, float xmax,
@@ -696,8 +698,8 @@ __global__ __launch_bounds__(kProbeThreads) void split_probe_kernel(
   if (tid == 0 && s_cnt > kSplitCap / 2) atomicAdd(nlong, 1);
 }
 
-// Sets ix.split_long (ix.X in place, ix.x_norm_max known).
-static int probe_split(Index& ix) {
+// Sets ix.split_long (ix.X in place, ix.x_norm_max known); buf: kProbeBytes.
+static int probe_split(Index& ix, char* buf) {
   if (ix.n <= 0 || ix.d % 32 != 0 || !(ix.x_norm_max < kSplitMaxRow)) return LIDER_OK;
   const int ns = int(std::min<int64_t>(kProbeSamples, ix.n));
   std::vector<int4> at(static_cast<size_t>(ns));
@@ -708,14 +710,8 @@ static int probe_split(Index& ix) {
     const int64_t first = std::min(std::max(a, row - len / 2), e - len);
     at[b] = make_int4(int32_t(row), int32_t(first), int32_t(len), 0);
   }
-  const size_t tab = al256(at.size() * sizeof(int4));
-  char* buf = nullptr;
-  if (hipMalloc(&buf, tab + 256) != hipSuccess) {  // no split windows without it
-    (void)hipGetLastError();
-    return LIDER_OK;
-  }
   int32_t h = 0;
-  int32_t* nlong = reinterpret_cast<int32_t*>(buf + tab);
+  int32_t* nlong = reinterpret_cast<int32_t*>(buf + kProbeSamples * sizeof(int4));
   int rc = check_hip(hipMemcpy(buf, at.data(), at.size() * sizeof(int4), hipMemcpyHostToDevice), "split samples");
   if (rc == LIDER_OK) {
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, nullptr, nlong, int64_t(1), 0);
@@ -724,7 +720,6 @@ static int probe_split(Index& ix) {
     rc = check_hip(hipGetLastError(), "split samples");
   }
   if (rc == LIDER_OK) rc = check_hip(hipMemcpy(&h, nlong, 4, hipMemcpyDeviceToHost), "split samples");
-  (void)hipFree(buf);
   if (rc == LIDER_OK) ix.split_long = float(h) / float(ns);
   return rc;
 }
@@ -783,8 +778,8 @@ int finish_index(Index& ix) {
         src[b] = make_int2(int32_t(r0), int32_t(std::min<int64_t>(16, ix.h_off[j + 1] - r0)));
       }
     const size_t elems = size_t(nblk) * 16 * size_t(dpad);
-    const size_t tab = al256(src.size() * sizeof(int2));  // then the largest norm
-    if (hipMalloc(&dsrc, tab + 256) != hipSuccess || hipMalloc(out, al256(elems * (bf ? 2 : 4))) != hipSuccess) {
+    const size_t tab = al256(src.size() * sizeof(int2));  // then the largest norm and the samples
+    if (hipMalloc(&dsrc, tab + 256 + kProbeBytes) != hipSuccess || hipMalloc(out, al256(elems * (bf ? 2 : 4))) != hipSuccess) {
       (void)hipGetLastError();
       if (dsrc) (void)hipFree(dsrc);
       *out = nullptr;
@@ -808,6 +803,7 @@ int finish_index(Index& ix) {
     if (st == LIDER_OK && !bf)
       st = check_hip(hipMemcpy(&ix.x_norm_max, mb, 4, hipMemcpyDeviceToHost), "largest row norm");
     if (st == LIDER_OK) st = check_hip(hipDeviceSynchronize(), "operand-ordered corpus");
+    if (st == LIDER_OK && !bf) st = probe_split(ix, reinterpret_cast<char*>(mb) + 256);
     (void)hipFree(dsrc);
     return st;
   };
@@ -894,7 +890,6 @@ int finish_index(Index& ix) {
   }
   // last, so that it takes no room that anything above needs
   if (rc == LIDER_OK && want_t && nblk > 0) rc = operand_copy(false, reinterpret_cast<void**>(&ix.Xt));
-  if (rc == LIDER_OK && ix.Xt) rc = probe_split(ix);
   return rc;
 }
 
