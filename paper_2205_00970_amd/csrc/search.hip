@@ -5066,17 +5066,18 @@ void launch_l1_gemm_bf16(const Index& ix, int64_t nq, const __hip_bfloat16* Qb, 
                          hipStream_t st, const L1Args* la = nullptr, const float* Qf = nullptr) {
   // Small tiles while the large ones leave seven of eight CUs idle, or three of
   // four and the centroids, which small tiles read from L2 once per 16 queries
-  // instead of 128, come to no more than 32 MB that way; and for a first two rows
+  // instead of 128, come to no more than 32 MB that way (128 MB split, where the
+  // large tiles take longer); and for a first two rows
   // of small tiles, which read them no more often.  Routing stage, large against
   // small, split: 1,000 x 768 centroids, 200 queries (16 large tiles) 50.7 and 33.4
   // us, 700 (48) 52.3 and 53.0; 4,000, 128 (32) 104.6 and 100.8, 256 (64) 106.8 and
   // 120.9, 512 (128) 124 and 180; 10,000, 32 (79) 216 and 205, 512 (316) 271 and
-  // 443; 1,000 x 100, 700 (48) 31.3 and 26.5.  bf16: 1,000 x 768, 512 (32) 34.5 and
+  // 443; 1,000 x 100, 700 (48) 31.3 and 26.5; 1,000 x 300, 777 (56) 43 and 32.  bf16: 1,000 x 768, 512 (32) 34.5 and
   // 33.6, 700 (48) 35.1 and 38.6.
   const int64_t nbig = (nq + 127) / 128 * ((ix.C + 127) / 128);
   const int64_t reads = (nq + 15) / 16 * ix.C * int64_t(ix.d) * (Qf ? 4 : 2);
   if ((Qf || ix.d % kLdsK == 0) &&
-      (nq <= 32 || 8 * nbig <= ix.n_cu || (4 * nbig <= ix.n_cu && reads <= (int64_t(32) << 20)))) {
+      (nq <= 32 || 8 * nbig <= ix.n_cu || (4 * nbig <= ix.n_cu && reads <= (int64_t(Qf ? 128 : 32) << 20)))) {
     const unsigned l1b = la ? unsigned((la->nq * la->H + 255) / 256) : 0u;
     const dim3 grid(l1b + unsigned((nq + 15) / 16 * ((ix.C + 15) / 16)));
     if (Qf)
