@@ -44,6 +44,12 @@ __device__ inline void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo) {
   }
 }
 
+// Zeros past dim d of the eight values from dim k on.
+__device__ inline void mask8(float (&v)[8], int32_t k, int32_t d) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = k + e < d ? v[e] : 0.f;
+}
+
 // The centroids split into h = bf16(mu) and l = bf16(mu - h) in the operand
 // order of the assignment product: per 16-centroid block and 32-dim step the
 // h part and the l part, 1 KB each, lane i + 16 s holding dims [8 s, 8 s + 8)
@@ -213,19 +219,18 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int32_t at = xo[a] + 4 * h, kd = 32 * kc + 8 * s + 4 * h;
+        // inside the point; values past it become zeros where they are used (at
+        // the load that would wait for the load)
         if (MODE == 2) {  // d % 32 == 0
           xa[a][h] = *reinterpret_cast<const float4*>(xk + at);
         } else if (MODE == 1) {  // d % 4 == 0: a whole float4 lies inside the point or past it
-          const float4 v = *reinterpret_cast<const float4*>(xk + at - max(kd - (d - 4), 0));
-          xa[a][h] = kd < d ? v : float4{0.f, 0.f, 0.f, 0.f};
+          xa[a][h] = *reinterpret_cast<const float4*>(xk + at - max(kd - (d - 4), 0));
         } else {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = xk[at + e - max(kd + e - (d - 1), 0)];
-          xa[a][h].x = kd < d ? v[0] : 0.f;
-          xa[a][h].y = kd + 1 < d ? v[1] : 0.f;
-          xa[a][h].z = kd + 2 < d ? v[2] : 0.f;
-          xa[a][h].w = kd + 3 < d ? v[3] : 0.f;
+          const float* p = xk + at;
+          xa[a][h].x = p[-max(kd - (d - 1), 0)];
+          xa[a][h].y = p[1 - max(kd + 1 - (d - 1), 0)];
+          xa[a][h].z = p[2 - max(kd + 2 - (d - 1), 0)];
+          xa[a][h].w = p[3 - max(kd + 3 - (d - 1), 0)];
         }
       }
   };
@@ -257,8 +262,9 @@ __global__ __launch_bounds__(512, 2) void assign_kernel(
       bf16x8 ah[4], al[4];
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        const float v[8] = {xa[a][0].x, xa[a][0].y, xa[a][0].z, xa[a][0].w,
-                            xa[a][1].x, xa[a][1].y, xa[a][1].z, xa[a][1].w};
+        float v[8] = {xa[a][0].x, xa[a][0].y, xa[a][0].z, xa[a][0].w,
+                      xa[a][1].x, xa[a][1].y, xa[a][1].z, xa[a][1].w};
+        if (MODE != 2) mask8(v, 32 * kc + 8 * s, d);
         split8(v, ah[a], al[a]);
         if (t == t0) {
 #pragma unroll
@@ -374,16 +380,13 @@ __global__ __launch_bounds__(256) void assign_narrow_kernel(
         if (MODE == 2) {
           x[a][h] = *reinterpret_cast<const float4*>(xk + at);
         } else if (MODE == 1) {
-          const float4 v = *reinterpret_cast<const float4*>(xk + at - max(kd - (d - 4), 0));
-          x[a][h] = kd < d ? v : float4{0.f, 0.f, 0.f, 0.f};
+          x[a][h] = *reinterpret_cast<const float4*>(xk + at - max(kd - (d - 4), 0));
         } else {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = xk[at + e - max(kd + e - (d - 1), 0)];
-          x[a][h].x = kd < d ? v[0] : 0.f;
-          x[a][h].y = kd + 1 < d ? v[1] : 0.f;
-          x[a][h].z = kd + 2 < d ? v[2] : 0.f;
-          x[a][h].w = kd + 3 < d ? v[3] : 0.f;
+          const float* p = xk + at;
+          x[a][h].x = p[-max(kd - (d - 1), 0)];
+          x[a][h].y = p[1 - max(kd + 1 - (d - 1), 0)];
+          x[a][h].z = p[2 - max(kd + 2 - (d - 1), 0)];
+          x[a][h].w = p[3 - max(kd + 3 - (d - 1), 0)];
         }
       }
   };
@@ -415,8 +418,9 @@ __global__ __launch_bounds__(256) void assign_narrow_kernel(
     bf16x8 ah[RB], al[RB];
 #pragma unroll
     for (int a = 0; a < RB; ++a) {
-      const float v[8] = {xa[u][a][0].x, xa[u][a][0].y, xa[u][a][0].z, xa[u][a][0].w,
-                          xa[u][a][1].x, xa[u][a][1].y, xa[u][a][1].z, xa[u][a][1].w};
+      float v[8] = {xa[u][a][0].x, xa[u][a][0].y, xa[u][a][0].z, xa[u][a][0].w,
+                    xa[u][a][1].x, xa[u][a][1].y, xa[u][a][1].z, xa[u][a][1].w};
+      if (MODE != 2) mask8(v, 32 * kc + 8 * s, d);
       split8(v, ah[a], al[a]);
 #pragma unroll
       for (int e = 0; e < 8; ++e) ss[a] += v[e] * v[e];

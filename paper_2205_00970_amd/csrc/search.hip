@@ -2920,14 +2920,13 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       if constexpr (SPLIT) {
-        // PAD, d a multiple of 4: a float4 lies inside the row or past it (zeros)
+        // PAD, d a multiple of 4: a float4 lies inside the row or past it (zeros
+        // from lstore on: made here, they would wait for the loads)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int at = kc * KCH + lc + 4 * h, back = PAD ? max(at - (d - 4), 0) : 0;
-          const float4 a = *reinterpret_cast<const float4*>(qsrc[j] + kc * KCH + 4 * h - back);
-          const float4 b = *reinterpret_cast<const float4*>(csrc[j] + kc * KCH + 4 * h - back);
-          fa4[j][h] = !PAD || at < d ? a : float4{0.f, 0.f, 0.f, 0.f};
-          fb4[j][h] = !PAD || at < d ? b : float4{0.f, 0.f, 0.f, 0.f};
+          fa4[j][h] = *reinterpret_cast<const float4*>(qsrc[j] + kc * KCH + 4 * h - back);
+          fb4[j][h] = *reinterpret_cast<const float4*>(csrc[j] + kc * KCH + 4 * h - back);
         }
       } else {
         ra[j] = *reinterpret_cast<const bf16x8*>(qsrc[j] + kc * KCH);
@@ -2935,11 +2934,16 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
       }
     }
   };
-  auto lstore = [&]() {
+  auto lstore = [&](int kc) {  // chunk kc
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int o = (lr + RPP * j) * ROW + lc;
       if constexpr (SPLIT) {
+        if constexpr (PAD) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (kc * KCH + lc + 4 * h >= d) fa4[j][h] = fb4[j][h] = float4{0.f, 0.f, 0.f, 0.f};
+        }
         bf16x8 h, l;
         split_bf16x8(fa4[j][0], fa4[j][1], h, l);
         *reinterpret_cast<bf16x8*>(&sa[0][o]) = h;
@@ -2961,7 +2965,7 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
     for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
   const int nk = (d + KCH - 1) / KCH;
   gload(0);
-  lstore();
+  lstore(0);
   __syncthreads();
   for (int kc = 0; kc < nk; ++kc) {
     if (kc + 1 < nk) gload(kc + 1);  // in flight while this chunk is consumed
@@ -2997,7 +3001,7 @@ __global__ __launch_bounds__(256, 3) void l1_gemm_lds_kernel(
     }
     __syncthreads();  // every wave is done with this chunk before it is overwritten
     if (kc + 1 < nk) {
-      lstore();
+      lstore(kc + 1);
       __syncthreads();
     }
   }
@@ -5067,13 +5071,13 @@ void launch_l1_gemm_bf16(const Index& ix, int64_t nq, const __hip_bfloat16* Qb, 
   // Small tiles while the large ones leave seven of eight CUs idle, or three of
   // four and the centroids, which small tiles read from L2 once per 16 queries
   // instead of 128, come to no more than 32 MB that way (128 MB split, where the
-  // large tiles take longer); and for a first two rows
-  // of small tiles, which read them no more often.  Routing stage, large against
-  // small, split: 1,000 x 768 centroids, 200 queries (16 large tiles) 50.7 and 33.4
-  // us, 700 (48) 52.3 and 53.0; 4,000, 128 (32) 104.6 and 100.8, 256 (64) 106.8 and
-  // 120.9, 512 (128) 124 and 180; 10,000, 32 (79) 216 and 205, 512 (316) 271 and
-  // 443; 1,000 x 100, 700 (48) 31.3 and 26.5; 1,000 x 300, 777 (56) 43 and 32.  bf16: 1,000 x 768, 512 (32) 34.5 and
-  // 33.6, 700 (48) 35.1 and 38.6.
+  // large tiles take longer); and for a first two rows of small tiles, which read
+  // them no more often.  Routing stage, large against small, split: 1,000 x 768
+  // centroids, 200 queries (16 large tiles) 50.7 and 33.4 us, 700 (48) 52.3 and
+  // 53.0; 4,000, 128 (32) 104.6 and 100.8, 256 (64) 106.8 and 120.9, 512 (128) 124
+  // and 180; 10,000, 32 (79) 216 and 205, 512 (316) 271 and 443; 1,000 x 100, 700
+  // (48) 31.3 and 26.5; 1,000 x 300, 777 (56) 39 and 32.  bf16: 1,000 x 768, 512
+  // (32) 34.5 and 33.6, 700 (48) 35.1 and 38.6.
   const int64_t nbig = (nq + 127) / 128 * ((ix.C + 127) / 128);
   const int64_t reads = (nq + 15) / 16 * ix.C * int64_t(ix.d) * (Qf ? 4 : 2);
   if ((Qf || ix.d % kLdsK == 0) &&

@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d,C,batches", [(64, 4200, (32, 33, 129)), (64, 1000, (512, 513, 1024, 1025)),
                                          (768, 1000, (200, 513, 700)), (100, 1000, (700, 1030)),
-                                         (100, 4200, (31, 40)), (128, 300, (1300,))])
+                                         (100, 4200, (31, 40)), (128, 300, (1300,)),
+                                         (300, 1000, (700, 777, 1100)), (300, 2100, (600, 700))])
 def test_routed_clusters(d, C, batches):
     import torch
     from paper_2205_00970_amd import datagen, lider
