@@ -539,7 +539,7 @@ __global__ __launch_bounds__(256) void assign_merge_kernel(const float4* __restr
 // distances would then cost many times the product itself, while this one is
 // bounded by 2 C d FP64 operations a point at the MFMA rate (120,000 x 768,
 // 1,000 centroids, whole call: isotropic rows 17.3 ms with the sequential sums
-// alone, 1.14 ms now; unit rows with a common mean 51.7 and 1.84; d = 64: 0.29
+// alone, 1.14 ms now; unit rows with a common mean 51.7 and 1.82; d = 64: 0.29
 // and 0.18, 0.48 and 0.19).
 // A workgroup of 16 waves takes 32 points (16 while the queue fits the chip that
 // way, for the shorter chain) and sweeps 512 centroids at a time, 32 per wave;
@@ -550,52 +550,17 @@ __global__ __launch_bounds__(256) void assign_merge_kernel(const float4* __restr
 // are exact) and the definition's own sum is within (d + 3) 2^-53 (|x| + M)^2,
 // so values further apart than 4 (d + 3) 2^-53 (|x| + M)^2 are in the
 // definition's order; 16 (d + 8) is used.  The other term covers fp32 subnormals
-// flushed on the way into FP64.
+// flushed on the way into FP64.  For the points that it leaves open (ties, as a
+// rule of equal centroids) a second look lists the centroids within it, and those
+// distances are summed sequentially; past the list's room, all of them.  All
+// points tied (20,000 x 768, 1,000 centroids in 500 equal pairs): 30 ms by a
+// workgroup per point over all distances, 1.8 now.
 constexpr int kF64Waves = 16, kF64Grid = 512;
 
 struct Best64 {
   double bv, sv;
   int32_t bi;
 };
-
-// The definition: a workgroup's threads over the centroids, each distance a
-// sequential sum without contraction, the smallest one's centroid (ties to the
-// smaller id) left in sj[0].
-template <int NT>
-__device__ void assign_sequential(const float* __restrict__ xr, int32_t d,
-                                  const float* __restrict__ cent, int32_t C, double* sd, int32_t* sj) {
-#pragma clang fp contract(off)
-  const int tid = threadIdx.x;
-  double bd = INFINITY;
-  int32_t bj = 0x7fffffff;
-  for (int32_t j = tid; j < C; j += NT) {
-    const float* mu = cent + int64_t(j) * d;
-    double acc = 0.0;
-    for (int l = 0; l < d; ++l) {
-      double df = double(xr[l]) - double(mu[l]);
-      acc = acc + df * df;
-    }
-    if (acc < bd) {
-      bd = acc;
-      bj = j;
-    }
-  }
-  sd[tid] = bd;
-  sj[tid] = bj;
-  __syncthreads();
-#pragma unroll 1
-  for (int o = NT / 2; o > 0; o >>= 1) {
-    if (tid < o) {
-      double od = sd[tid + o];
-      int32_t oj = sj[tid + o];
-      if (od < sd[tid] || (od == sd[tid] && oj < sj[tid])) {
-        sd[tid] = od;
-        sj[tid] = oj;
-      }
-    }
-    __syncthreads();
-  }
-}
 
 __device__ inline Best64 best_merge(const Best64& a, const Best64& b) {
   Best64 r;
@@ -605,17 +570,104 @@ __device__ inline Best64 best_merge(const Best64& a, const Best64& b) {
   return r;
 }
 
+// The definition of one distance: a sequential sum without contraction.
+template <bool VEC>
+__device__ inline double distance_sequential(const float* __restrict__ x, const float* __restrict__ mu,
+                                             int32_t d) {
+#pragma clang fp contract(off)
+  double acc = 0.0;
+  if (VEC) {
+#pragma unroll 4
+    for (int32_t l = 0; l < d; l += 4) {
+      const float4 a = *reinterpret_cast<const float4*>(x + l);
+      const float4 b = *reinterpret_cast<const float4*>(mu + l);
+      const double d0 = double(a.x) - double(b.x), d1 = double(a.y) - double(b.y);
+      const double d2 = double(a.z) - double(b.z), d3 = double(a.w) - double(b.w);
+      acc = acc + d0 * d0;
+      acc = acc + d1 * d1;
+      acc = acc + d2 * d2;
+      acc = acc + d3 * d3;
+    }
+  } else {
+#pragma unroll 4
+    for (int32_t l = 0; l < d; ++l) {
+      const double df = double(x[l]) - double(mu[l]);
+      acc = acc + df * df;
+    }
+  }
+  return acc;
+}
+
+__device__ inline void assign_write(const AssignOut& o, int64_t row, int32_t j) {
+  o.assign[row] = j;
+  if (o.prev && o.prev[row] != j) atomicAdd(o.changed, 1);
+}
+
+// The definition for the points open[0, no) over all centroids: a group of
+// threads per point (as many points at a time as the workgroup holds such
+// groups), ties to the smaller id.  The rows are each thread's own, so their
+// loads bound it: 16 bytes at a time where they are aligned.
+template <bool VEC, int NT>
+__device__ void assign_sequential(const float* __restrict__ X, const int64_t* open, int32_t no,
+                                  const float* __restrict__ cent, const AssignOut& o, double* sd,
+                                  int32_t* sj) {
+  const int tid = threadIdx.x;
+  const int32_t d = o.d, C = o.C;
+  int32_t tg = 32;  // threads per point
+  while (tg < C && tg < NT) tg <<= 1;
+  const int32_t me = tid / tg, lane = tid - me * tg;
+  for (int32_t t0 = 0; t0 < no; t0 += NT / tg) {
+    const bool in = t0 + me < no;
+    double bd = INFINITY;
+    int32_t bj = 0x7fffffff;
+    if (in) {
+      const float* x = X + open[t0 + me] * d;
+      for (int32_t j = lane; j < C; j += tg) {
+        const double v = distance_sequential<VEC>(x, cent + int64_t(j) * d, d);
+        if (v < bd) {
+          bd = v;
+          bj = j;
+        }
+      }
+    }
+    sd[tid] = bd;
+    sj[tid] = bj;
+    __syncthreads();
+#pragma unroll 1
+    for (int32_t h = tg / 2; h > 0; h >>= 1) {
+      if (lane < h) {
+        const double od = sd[tid + h];
+        const int32_t oj = sj[tid + h];
+        if (od < sd[tid] || (od == sd[tid] && oj < sj[tid])) {
+          sd[tid] = od;
+          sj[tid] = oj;
+        }
+      }
+      __syncthreads();
+    }
+    if (in && lane == 0) assign_write(o, open[t0 + me], sj[tid]);
+    __syncthreads();
+  }
+}
+
 template <bool VEC>
 __global__ __launch_bounds__(64 * kF64Waves) void assign_f64_kernel(
     const float* __restrict__ X, const float* __restrict__ cent, const double* __restrict__ cn64,
     AssignOut o) {
   typedef double doublex4 __attribute__((ext_vector_type(4)));
+  constexpr int NT = 64 * kF64Waves;
   __shared__ double sbv[kF64Waves][32], ssv[kF64Waves][32], sss[32];
   __shared__ int32_t sbi[kF64Waves][32];
-  __shared__ double sd[64 * kF64Waves];
-  __shared__ int32_t sj[64 * kF64Waves];
-  __shared__ int64_t open[32];  // points that the bound leaves open
-  __shared__ int32_t nopen;
+  __shared__ double sd[NT];
+  __shared__ int32_t sj[NT];
+  // points that the bound leaves open, the largest value that can win (per point
+  // of the workgroup) and the (point, centroid) pairs at or below it
+  __shared__ int64_t open[32];
+  __shared__ double sthr[32];
+  __shared__ uint64_t smin[32];
+  __shared__ int32_t smj[32];
+  __shared__ int32_t cand_r[NT], cand_j[NT];
+  __shared__ int32_t nopen, ncand;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i = lane & 15, s = lane >> 4;
   const int32_t cnt = *o.amb_count, d = o.d, C = o.C;
@@ -643,47 +695,51 @@ __global__ __launch_bounds__(64 * kF64Waves) void assign_f64_kernel(
 #pragma unroll
     for (int a = 0; a < 2; ++a)
       xr[a] = X + o.amb[min(t0 + (two ? 16 * a : 0) + i, int64_t(cnt) - 1)] * d;
-    bool any = false;  // this wave has columns (wave-uniform)
-    for (int32_t c0 = 32 * wave; c0 < C; c0 += 32 * kF64Waves) {
-      const float* cr[2];
+    // the products with this wave's columns, 32 at a time: done(c0, acc), element
+    // acc[a][b][e] of lane (i, s) for point 16 a + s + 4 e, centroid c0 + 16 b + i
+    auto sweep = [&](auto done) {
+      for (int32_t c0 = 32 * wave; c0 < C; c0 += 32 * kF64Waves) {
+        const float* cr[2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) cr[b] = cent + int64_t(min(c0 + 16 * b + i, C - 1)) * d;
-      doublex4 acc[2][2];
+        for (int b = 0; b < 2; ++b) cr[b] = cent + int64_t(min(c0 + 16 * b + i, C - 1)) * d;
+        doublex4 acc[2][2];
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
-      float4 nx[2], nc[2];
-      auto fetch = [&](int32_t k0) {
+          for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+        float4 nx[2], nc[2];
+        auto fetch = [&](int32_t k0) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          nx[u] = load4(xr[u], k0 + 4 * s);
-          nc[u] = load4(cr[u], k0 + 4 * s);
-        }
-      };
-      if (VEC) fetch(0);
-      for (int32_t k0 = 0; k0 < d; k0 += 16) {
-        if (!VEC) fetch(k0);  // scalar loads a step ahead would spill
-        const float x[2][4] = {{nx[0].x, nx[0].y, nx[0].z, nx[0].w}, {nx[1].x, nx[1].y, nx[1].z, nx[1].w}};
-        const float y[2][4] = {{nc[0].x, nc[0].y, nc[0].z, nc[0].w}, {nc[1].x, nc[1].y, nc[1].z, nc[1].w}};
-        if (VEC) fetch(k0 + 16);  // past the row: zeros
-        __builtin_amdgcn_sched_barrier(0);
+          for (int u = 0; u < 2; ++u) {
+            nx[u] = load4(xr[u], k0 + 4 * s);
+            nc[u] = load4(cr[u], k0 + 4 * s);
+          }
+        };
+        if (VEC) fetch(0);
+        for (int32_t k0 = 0; k0 < d; k0 += 16) {
+          if (!VEC) fetch(k0);  // scalar loads a step ahead would spill
+          const float x[2][4] = {{nx[0].x, nx[0].y, nx[0].z, nx[0].w}, {nx[1].x, nx[1].y, nx[1].z, nx[1].w}};
+          const float y[2][4] = {{nc[0].x, nc[0].y, nc[0].z, nc[0].w}, {nc[1].x, nc[1].y, nc[1].z, nc[1].w}};
+          if (VEC) fetch(k0 + 16);  // past the row: zeros
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const double x0 = double(x[0][e]), x1 = double(x[1][e]);
-          const double y0 = double(y[0][e]), y1 = double(y[1][e]);
-          acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
-          acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
-          if (two) {
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, acc[1][1], 0, 0, 0);
+          for (int e = 0; e < 4; ++e) {
+            const double x0 = double(x[0][e]), x1 = double(x[1][e]);
+            const double y0 = double(y[0][e]), y1 = double(y[1][e]);
+            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
+            if (two) {
+              acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
+              acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, acc[1][1], 0, 0, 0);
+            }
           }
         }
+        done(c0, acc, c0 + i < C ? cn64[c0 + i] : double(INFINITY),
+             c0 + 16 + i < C ? cn64[c0 + 16 + i] : double(INFINITY));
       }
-      // result layout: element e of lane (i, s) is point 16 a + s + 4 e, centroid
-      // c0 + 16 b + i
-      const double n0 = c0 + i < C ? cn64[c0 + i] : double(INFINITY);
-      const double n1 = c0 + 16 + i < C ? cn64[c0 + 16 + i] : double(INFINITY);
+    };
+    bool any = false;  // this wave has columns (wave-uniform)
+    sweep([&](int32_t c0, const doublex4 (&acc)[2][2], double n0, double n1) {
 #pragma unroll
       for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -703,8 +759,8 @@ __global__ __launch_bounds__(64 * kF64Waves) void assign_f64_kernel(
           }
         }
       any = true;
-    }
-    if (tid == 0) nopen = 0;
+    });
+    if (tid == 0) nopen = ncand = 0;
     {  // |x|^2: half a wave per point
       const int r = tid >> 5;
       const float* x = X + o.amb[min(t0 + r, int64_t(cnt) - 1)] * d;
@@ -715,6 +771,11 @@ __global__ __launch_bounds__(64 * kF64Waves) void assign_f64_kernel(
       if ((tid & 31) == 0) sss[r] = q;
     }
     __syncthreads();
+    if (tid < 32) {
+      sthr[tid] = -INFINITY;
+      smin[tid] = ~uint64_t(0);
+      smj[tid] = -1;  // not open
+    }
     if (tid < per && t0 + tid < cnt) {
       Best64 v{sbv[0][tid], ssv[0][tid], sbi[0][tid]};
       for (int w = 1; w < kF64Waves && 32 * w < C; ++w)
@@ -724,22 +785,57 @@ __global__ __launch_bounds__(64 * kF64Waves) void assign_f64_kernel(
       const double E = 16.0 * double(d + 8) * 1.1102230246251565e-16 * r * r +
                        8.0 * sqrt(double(d)) * 1.1754943508222875e-38 * r;
       if (v.sv - v.bv > E) {  // false with a NaN or an infinite bound
-        o.assign[row] = v.bi;
-        if (o.prev && o.prev[row] != v.bi) atomicAdd(o.changed, 1);
+        assign_write(o, row, v.bi);
       } else {
+        sthr[tid] = v.bv + E;
+        smj[tid] = 0x7fffffff;
         open[atomicAdd(&nopen, 1)] = row;
       }
     }
     __syncthreads();
-    const int32_t no = nopen;
-    for (int32_t t = 0; t < no; ++t) {
-      const int64_t row = open[t];
-      assign_sequential<64 * kF64Waves>(X + row * d, d, cent, C, sd, sj);
-      if (tid == 0) {
-        o.assign[row] = sj[0];
-        if (o.prev && o.prev[row] != sj[0]) atomicAdd(o.changed, 1);
-      }
+    if (nopen > 0) {  // workgroup-uniform
+      // the open points' centroids within the bound of the best, by a second look
+      // (a value that is no number counts)
+      sweep([&](int32_t c0, const doublex4 (&acc)[2][2], double n0, double n1) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = 16 * a + s + 4 * e;
+            const double thr = sthr[r];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+              const int32_t j = c0 + 16 * b + i;
+              if (j < C && !((b ? n1 : n0) - 2.0 * acc[a][b][e] > thr)) {
+                const int32_t at = atomicAdd(&ncand, 1);
+                if (at < NT) {
+                  cand_r[at] = r;
+                  cand_j[at] = j;
+                }
+              }
+            }
+          }
+      });
       __syncthreads();
+      const int32_t nc = ncand;
+      if (nc <= NT) {  // a distance per thread, neighbours in the list on different waves
+        const int32_t at = (tid & 63) * kF64Waves + wave;
+        double v = 0.0;
+        int32_t r = 0;
+        if (at < nc) {
+          r = cand_r[at];
+          v = distance_sequential<VEC>(X + o.amb[t0 + r] * d, cent + int64_t(cand_j[at]) * d, d);
+          // the smallest sum, then the smallest id among its equals (a NaN wins nothing)
+          if (v < double(INFINITY))
+            atomicMin(reinterpret_cast<unsigned long long*>(&smin[r]), (unsigned long long)__double_as_longlong(v));
+        }
+        __syncthreads();
+        if (at < nc && uint64_t(__double_as_longlong(v)) == smin[r]) atomicMin(&smj[r], cand_j[at]);
+        __syncthreads();
+        if (tid < 32 && smj[tid] >= 0) assign_write(o, o.amb[t0 + tid], smj[tid]);
+      } else {
+        assign_sequential<VEC, NT>(X, open, nopen, cent, o, sd, sj);
+      }
     }
     __syncthreads();
   }

@@ -44,3 +44,17 @@ def test_equal_to_the_oracle(kind, n, d, C):
     buf[1:] = torch.from_numpy(X.reshape(-1)).cuda()
     got = lider.kmeans_assign(buf[1:].view(n, d), torch.from_numpy(cent).cuda()).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("copies", [2, 3, 40, 200])
+@pytest.mark.parametrize("n,d,C", [(300, 32, 400), (9000, 20, 400), (100, 33, 1200)])
+def test_many_equal_centroids(n, d, C, copies):
+    """Ties of few centroids (listed) and of more than a list holds (all summed)."""
+    import torch
+    from paper_2205_00970_amd import lider
+    g = np.random.default_rng(n + copies)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    cent = np.repeat(g.standard_normal((C // copies + 1, d)), copies, axis=0)[:C].astype(np.float32)
+    cent = cent[g.permutation(C)]
+    got = lider.kmeans_assign(torch.from_numpy(X).cuda(), torch.from_numpy(cent).cuda()).cpu().numpy()
+    assert np.array_equal(got, oracle.kmeans_assign(X, cent))
