@@ -1601,13 +1601,9 @@ static int run_farthest(const float* X, int64_t n, int32_t d, float* cent, int32
   if (hipMalloc(&U, size_t(n) * 4) != hipSuccess || hipMalloc(&sd, size_t(n) * 4) != hipSuccess ||
       hipMalloc(&sid, size_t(n) * 4) != hipSuccess ||
       hipMalloc(&hist, kFFBins * 4) != hipSuccess || hipMalloc(&fs, sizeof(FFState)) != hipSuccess ||
-      hipMalloc(&part, size_t(gmax) * n * sizeof(float4)) != hipSuccess)
+      hipMalloc(&part, size_t(gmax) * n * sizeof(float4)) != hipSuccess ||
+      hipMalloc(&cand, size_t(n) * 8) != hipSuccess || hipMalloc(&dex, size_t(n) * 8) != hipSuccess)
     rc = set_error(LIDER_ENOMEM, "out of device memory: farthest-first buffers");
-  if (rc == LIDER_OK) {  // the product's values are read before a round has candidates: one room
-    static_assert(sizeof(float4) == sizeof(int64_t) + sizeof(double), "a candidate's id and distance per row");
-    cand = reinterpret_cast<int64_t*>(part);
-    dex = reinterpret_cast<double*>(cand + n);
-  }
   // 16-byte loads: rows of both matrices start at multiples of 16 bytes
   const bool vec = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(cent)) & 15) == 0;
   // About 1% of the rows, and at most 8,192 (24 MB of rows at d = 768: the
@@ -1693,7 +1689,7 @@ static int run_farthest(const float* X, int64_t n, int32_t d, float* cent, int32
     }
   }
   if (rc == LIDER_OK) rc = check_hip(hipStreamSynchronize(st), "farthest-first seeding");
-  for (void* p : {(void*)U, (void*)sd, (void*)sid, (void*)hist, (void*)fs, (void*)part})
+  for (void* p : {(void*)U, (void*)sd, (void*)sid, (void*)hist, (void*)fs, (void*)cand, (void*)dex, (void*)part})
     if (p) (void)hipFree(p);
   return rc;
 }
