@@ -70,7 +70,7 @@ struct Plan {
 
 // The split window scores (fp32 search): with many pairs per tile the fp32
 // MFMA rate (1/16 of bf16's) bounds the rerank, so the windows are scored by
-// three bf16 products of the split operands instead (WgPass below) and the rows
+// three bf16 products of the split operands instead (wg_pass below) and the rows
 // within the error bound of the k-th best are rescored by the fp32 product
 // itself, in the same order of operations, so ids and scores keep every bit.
 // The selection and the rescoring, which gathers about k rows per query, then
