@@ -91,6 +91,11 @@ typedef struct lider_index lider_index; /* opaque; owns its device memory */
  *                 assignment repeats the previous one.
  *  storage        LIDER_F32, or LIDER_BF16 to add a bf16 copy of the corpus
  *                 for the precision form (the fp32 copy is always kept).
+ *                 Where memory allows, the index also holds the rows once more
+ *                 in the rerank's operand order: fp32, dimensions padded with
+ *                 zeros to a multiple of 32 and clusters to 16 rows (d = 768:
+ *                 1.0 times the rows' bytes, d = 100: 1.3; none where the padding
+ *                 would add more than half), made last, from what is left.
  *  centroid_storage LIDER_F32, or LIDER_FP8E4M3 to add per-row-scaled fp8
  *                 centroids for precision-form routing.
  *  kmeans_seeding 0: initial centroids are the rows kmeans_init_host[0..C).
@@ -398,8 +403,8 @@ int lider_hash(const float* X_dev, int64_t n, int32_t d, const float* A_dev, con
 
 /* One k-means assignment step (Section 3.2): assign_dev[i] = argmin_j
  * ||X[i] - cent[j]||^2 decided in FP64 (ties to the smaller j); split
- * bf16 MFMA distances, FP64 recompute where the rounding-error bands of the two
- * best overlap.  X_dev [n x d], cent_dev [C x d].  Allocates temporaries;
+ * bf16 MFMA distances, FP64 MFMA where the rounding-error bands of the two best
+ * overlap, sequential FP64 sums where those of FP64 do.  X_dev [n x d], cent_dev [C x d].  Allocates temporaries;
  * synchronises `stream`. */
 int lider_kmeans_assign(const float* X_dev, int64_t n, int32_t d, const float* cent_dev,
                         int32_t C, int32_t* assign_dev, void* stream);
